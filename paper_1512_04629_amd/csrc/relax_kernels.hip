@@ -1,8 +1,9 @@
 // Hybrid Gauss-Seidel sweep: the rows of a block in order, each row's sum in
 // ascending column order (the order and operations of the definition, so the
-// result is the CPU's bit for bit).  One thread per block, reading global
-// memory, or, for blocks of up to 256 rows, a workgroup per chunk of blocks
-// with the terms staged in LDS.
+// result is the CPU's bit for bit).  Three forms: one thread per block, reading
+// global memory (blocks of more than 1,024 rows); one lane per block on terms
+// staged in LDS (small blocks on large levels); 16 or 64 lanes per chunk of
+// blocks, the terms staged by other waves (everything else).
 #include "relax_kernels.hpp"
 
 #include <algorithm>
@@ -34,7 +35,7 @@ __global__ __launch_bounds__(256) void hybrid_gs_kernel(int n, const int32_t* __
     }
 }
 
-// Staged form for blocks of at most kGsMaxRows rows.  A workgroup owns a chunk
+// Staged form, for blocks of fewer than kGsChainMin rows.  A workgroup owns a chunk
 // of R consecutive rows (whole blocks).  First all its threads turn the
 // chunk's entries into terms in LDS with coalesced loads: the product
 // a_ij xold_j for a term with an old value (rounded exactly as the sweep
@@ -43,13 +44,6 @@ __global__ __launch_bounds__(256) void hybrid_gs_kernel(int n, const int32_t* __
 // order from LDS, subtracting the terms in ascending column order: the same
 // operations in the same order as hybrid_gs_kernel.  A chunk whose entries do
 // not fit takes the per-block loop of hybrid_gs_kernel.
-// Largest block the staged form takes (at most kGsMaxRows).  On the 128^3
-// Poisson hierarchy it is faster over whole solves for every block size up
-// to 256 rows, although on the finest level alone blocks of 64 rows and more
-// sweep faster in the per-block kernel.
-#ifndef AMG_GS_STAGED_MAX
-#define AMG_GS_STAGED_MAX 256
-#endif
 constexpr int kGsThreads = 256;
 constexpr int kGsCap = 3072;      // staged terms per chunk
 constexpr int kGsMaxRows = 256;   // rows per chunk
@@ -180,13 +174,369 @@ __global__ __launch_bounds__(kGsThreads) void hybrid_gs_staged_kernel(int n, con
     }
 }
 
+// Chain form, for blocks of up to kGsChainMaxRows rows.  The rows of a block
+// are a serial chain, so what a sweep costs is the time of one row in its
+// chain times the rows, and the instructions that time takes where the chains
+// fill the machine.  A chunk of consecutive rows (whole blocks) belongs to W
+// lanes of a workgroup's first wave: W = 64, one chunk to a workgroup (long
+// rows, few chunks), or W = 16, four chunks side by side in the wave.  The
+// other waves turn the next strip of every chunk (up to W rows and S entries)
+// into terms in LDS, while the first runs the current one: the product
+// a_ij xold_j where the old value is used, a_ij and the row's place in the
+// chunk where the new one is, 0 for the diagonal, whose subtraction changes
+// nothing.  In the chain a row's terms lie one to a lane, loaded two rows
+// ahead, the new values they need one row ahead (the value of the row before
+// from a register), and are subtracted in ascending column order by one
+// multiply-add each, acc = (-1) t + acc, the term taken from its lane by the
+// instruction's own row broadcast: exactly the subtraction, so the operations
+// are those of the definition in its order and the bits those of the per-block
+// kernel.  A row longer than a strip is summed from memory.
+constexpr int kGsChainMaxRows = 1024;   // rows per chunk
+
+// acc - t(lane 0) - t(lane 1) ... of each row of 16 lanes, 8 or 16 lanes in
+// order (v_fmac_f64 with src1 = -1; a DPP source needs two wait states after
+// the instruction that wrote it)
+__device__ __forceinline__ double sub_row8(double acc, double t, double m1) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:0 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:1 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:2 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:3 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:4 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:7 row_mask:0xf bank_mask:0xf"
+        : "+v"(acc) : "v"(t), "v"(m1));
+    return acc;
+}
+
+__device__ __forceinline__ double sub_row8_high(double acc, double t, double m1) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:9 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:10 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:11 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:12 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:13 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:14 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:15 row_mask:0xf bank_mask:0xf"
+        : "+v"(acc) : "v"(t), "v"(m1));
+    return acc;
+}
+
+__device__ __forceinline__ double lane_read(double x, int lane) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// acc minus the first len (<= W) terms of the W lanes in order; lanes past len
+// hold 0.  W = 64: acc is handed from each row of 16 lanes to the next and
+// comes back in every lane.
+template <int W>
+__device__ __forceinline__ double sub_terms(double acc, double t, int len, double m1) {
+    if constexpr (W == 16) {
+        acc = sub_row8(acc, t, m1);
+        if (__any(len > 8)) acc = sub_row8_high(acc, t, m1);
+    } else {
+        for (int r = 0; r < 4; ++r) {
+            if (len <= 16 * r) break;
+            acc = sub_row8(acc, t, m1);
+            if (len > 16 * r + 8) acc = sub_row8_high(acc, t, m1);
+            acc = lane_read(acc, 16 * r);
+        }
+    }
+    return acc;
+}
+
+// a / d from the correctly rounded reciprocal y = 1 / d, correctly rounded
+// (Markstein, IBM J. Res. Dev. 34, 1990: the correction of a quotient within
+// one unit in the last place by an exact remainder is the rounded quotient;
+// the first correction brings it there); far from the ends of the exponent
+// range the remainders are exact, elsewhere (and for 0, infinities and NaN) the
+// division itself.
+__device__ __forceinline__ double quotient(double a, double d, double y) {
+    const double aa = fabs(a), ad = fabs(d);
+    if (aa >= 0x1p-400 && aa <= 0x1p400 && ad >= 0x1p-400 && ad <= 0x1p400) {
+        double q = a * y;
+        q = __builtin_fma(__builtin_fma(-d, q, a), y, q);
+        return __builtin_fma(__builtin_fma(-d, q, a), y, q);
+    }
+    return a / d;
+}
+
+struct __align__(16) GsRow {      // a staged row
+    double b, d, y;               // right-hand side, diagonal, its reciprocal
+    int32_t off, len;             // its terms in the strip; len < 0: too long, not staged
+};
+
+template <bool FORWARD, int W, int NP>
+__global__ __launch_bounds__(64 * (1 + NP)) void hybrid_gs_chain_kernel(
+    int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci, const double* __restrict__ v,
+    const double* __restrict__ b, const double* __restrict__ xold, double* __restrict__ xnew, int block, int chunk) {
+    constexpr int G = 64 / W;               // chunks of the workgroup
+    constexpr int E = 8;                    // entries of a strip per staging lane
+    constexpr int S = W * E * NP;           // entries per strip
+    __shared__ double term[2][G][S];
+    __shared__ int16_t tag[2][G][S];
+    __shared__ GsRow rows[2][G][W];
+    __shared__ int32_t rows_in[2][G];
+    __shared__ int32_t soff[NP][G][W];
+    extern __shared__ double ly_all[];      // new values of the chunks' rows
+    const int g = ((int)threadIdx.x & 63) / W, lane = (int)threadIdx.x & (W - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t start = ((int64_t)blockIdx.x * G + g) * chunk;
+    const int r0 = (int)min(start, (int64_t)n), nr = (int)min((int64_t)chunk, (int64_t)n - r0);
+    double* const ly = ly_all + (size_t)g * chunk;
+    // row visited k-th of the chunk, relative to r0
+    auto row_at = [&](int k) { return FORWARD ? k : nr - 1 - k; };
+    // x of the group's lane l
+    auto from = [&](int x, int l) {
+        if constexpr (W == 64) return __builtin_amdgcn_readlane(x, l);
+        else return __shfl(x, l, W);
+    };
+    int done = 0;                           // rows staged (or left to the long-row path) so far
+    auto produce = [&](int buf) {
+        const int part = wave - 1;
+        const int left = nr - done;
+        const bool have = lane < left;
+        const int il = have ? row_at(done + lane) : 0;
+        const int beg = have ? rp[r0 + il] : 0, end = have ? rp[r0 + il + 1] : 0;
+        const double bi = have ? b[r0 + il] : 0.0;
+        // entries of the strip up to and with this lane's row
+        const int first = from(FORWARD ? beg : end, 0);
+        const int upto = FORWARD ? end - first : first - beg;
+        unsigned long long fit = __ballot(have && upto <= S);
+        if constexpr (W < 64) fit = (fit >> (g * W)) & ((1ull << W) - 1ull);
+        const int R = __popcll(fit);
+        const bool lng = R == 0 && left > 0;
+        const int lastl = max(R - 1, 0);
+        const int p0 = FORWARD ? first : from(beg, lastl);
+        const int total = R > 0 ? from(upto, lastl) : 0;
+        const int ibs = il - il % block;     // the row's block in the chunk
+        soff[part][g][lane] = lane < R ? beg - p0 : INT32_MAX;
+        if (part == 0) {
+            GsRow& q = rows[buf][g][lane];
+            if (lane < R) {
+                q.b = bi;
+                q.off = beg - p0;
+                q.len = end - beg;
+            } else if (lane == 0) {
+                q.len = -1;
+            }
+            if (lane == 0) rows_in[buf][g] = lng ? 1 : R;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        int jj[E], kk[E];
+        double aa[E], xx[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int q = lane + W * (e * NP + part);
+            jj[e] = q < total ? ci[p0 + q] : min(r0, n - 1);
+            aa[e] = q < total ? v[p0 + q] : 0.0;
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) xx[e] = xold[jj[e]];
+        // the strip row (in memory order) holding each entry
+#pragma unroll
+        for (int e = 0; e < E; ++e) kk[e] = 0;
+#pragma unroll
+        for (int step = W / 2; step > 0; step >>= 1) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int m = kk[e] + step;
+                const int st = m < R ? soff[part][g][FORWARD ? m : R - 1 - m] : INT32_MAX;
+                if (st <= lane + W * (e * NP + part)) kk[e] = m;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int k = FORWARD ? kk[e] : max(R - 1 - kk[e], 0);
+            const int bs = __shfl(ibs, k, W);
+            const int q = lane + W * (e * NP + part);
+            if (q < total) {
+                const int i = row_at(done + k), j = jj[e] - r0;
+                if (j == i) {
+                    rows[buf][g][k].d = aa[e];
+                    rows[buf][g][k].y = 1.0 / aa[e];
+                    tag[buf][g][q] = kGsDiag;
+                    term[buf][g][q] = 0.0;
+                } else {
+                    const int be = min(bs + block, nr);
+                    const bool fresh = j >= bs && j < be && (FORWARD ? j < i : j > i);
+                    tag[buf][g][q] = fresh ? (int16_t)j : kGsOld;
+                    term[buf][g][q] = fresh ? aa[e] : aa[e] * xx[e];
+                }
+            }
+        }
+        done += lng ? 1 : R;
+    };
+    double m1 = -1.0;
+    asm("" : "+v"(m1));
+    int at = 0;                             // rows finished
+    // a row too long for a strip: its terms from memory (all of a group's
+    // lanes or none are here)
+    auto long_row = [&]() {
+        const int il = row_at(at), i = r0 + il;
+        const int bs = il - il % block, be = min(bs + block, nr);
+        const int beg = rp[i], end = rp[i + 1];
+        double acc = b[i], d = 0.0;
+        for (int p = beg; p < end; p += W) {
+            const bool in = p + lane < end;
+            const int j = in ? ci[p + lane] - r0 : il;
+            const double a = in ? v[p + lane] : 0.0;
+            const bool fresh = j >= bs && j < be && (FORWARD ? j < il : j > il);
+            const double y = fresh ? ly[j] : xold[r0 + j];
+            const double t = in && j != il ? a * y : 0.0;
+            if (in && j == il) d = a;
+            acc = sub_terms<W>(acc, t, end - p, m1);
+        }
+        // exactly one lane holds the diagonal
+#pragma unroll
+        for (int o = W / 2; o > 0; o >>= 1) d += __shfl_xor(d, o, W);
+        const double xi = acc / d;
+        if (lane == 0) {
+            ly[il] = xi;
+            xnew[i] = xi;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    };
+    auto consume = [&](int buf, int Rmax) {
+        const int R = rows_in[buf][g];
+        const GsRow* const row = rows[buf][g];
+        const double* const tm = term[buf][g];
+        const int16_t* const tg = tag[buf][g];
+        const bool lng = R == 1 && row[0].len < 0;
+        if (__any(lng)) {
+            if (lng) long_row();
+        }
+        const int Rs = lng ? 0 : R;         // staged rows of this group
+        auto load = [&](int k, double& t, int& q, GsRow& h) {
+            const bool have = k < Rs;
+            h = row[have ? k : 0];
+            if (!have) h.len = 0;
+            const bool in = lane < h.len;
+            t = in ? tm[h.off + lane] : 0.0;
+            q = in ? (int)tg[h.off + lane] : (int)kGsOld;
+        };
+        double t0, t1, y0;
+        int q0, q1;
+        GsRow h0, h1;
+        load(0, t0, q0, h0);
+        load(1, t1, q1, h1);
+        y0 = ly[max(q0, 0)];
+        int prev = -1;
+        double prev_x = 0.0;
+        for (int k = 0; k < Rmax; ++k) {
+            const double y1 = ly[max(q1, 0)];
+            double t2;
+            int q2;
+            GsRow h2;
+            load(k + 2, t2, q2, h2);
+            const double t = q0 >= 0 ? t0 * (q0 == prev ? prev_x : y0) : t0;
+            double acc = sub_terms<W>(h0.b, t, h0.len, m1);
+            for (int o = W; __any(o < h0.len); o += W) {
+                const bool in = o + lane < h0.len;
+                double tq = in ? tm[h0.off + o + lane] : 0.0;
+                const int qq = in ? (int)tg[h0.off + o + lane] : (int)kGsOld;
+                const double yq = ly[max(qq, 0)];
+                tq = qq >= 0 ? tq * (qq == prev ? prev_x : yq) : tq;
+                acc = sub_terms<W>(acc, tq, h0.len - o, m1);
+            }
+            const double xi = quotient(acc, h0.d, h0.y);
+            const int il = row_at(at + k);
+            if (lane == 0 && k < Rs) ly[il] = xi;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the store before later rows' loads
+            prev = il;
+            prev_x = xi;
+            t0 = t1;
+            q0 = q1;
+            h0 = h1;
+            y0 = y1;
+            t1 = t2;
+            q1 = q2;
+            h1 = h2;
+        }
+        if (lane < Rs) {
+            const int il = row_at(at + lane);
+            xnew[r0 + il] = ly[il];
+        }
+        at += R;
+    };
+    if (wave > 0) produce(0);
+    else __builtin_amdgcn_s_setprio(2);   // the chain ahead of the staging waves of its SIMD
+    __syncthreads();
+    for (int buf = 0;; buf ^= 1) {
+        int Rmax = 0;
+#pragma unroll
+        for (int c = 0; c < G; ++c) Rmax = max(Rmax, rows_in[buf][c]);
+        Rmax = __builtin_amdgcn_readfirstlane(Rmax);
+        if (Rmax == 0) break;               // every chunk is done, in every wave
+        if (wave > 0) produce(buf ^ 1);
+        else consume(buf, Rmax);
+        __syncthreads();
+    }
+}
+
 }  // namespace
+
+// The chain form takes blocks of at least kGsChainMin rows, and blocks of two
+// rows or more on levels of up to kGsChainRowsFew rows; below that the staged
+// form's one lane per block has chains enough and is faster where rows are
+// short.  A chunk is the whole blocks that fit kGsChainRows rows, fewer where
+// the level has too few rows for kGsChainChunks chunks.  16 lanes to a chunk
+// where rows are short and there are chunks to fill the machine four to a
+// workgroup, else 64.
+// A forward sweep in us, one lane per block (staged form) -> chain form, 3D
+// Poisson hierarchies, levels 0, 1, 2, ...:
+//   64^3, blocks of 64:   102 236 279 779 1298 675 -> 31 53 42 44 62 43
+//   128^3, blocks of 64:  623 1493 942 879 1782 1760 902 -> 153 152 102 45 76 76 50
+//   128^3, blocks of 16:  190 418 254 160 240 222 136 -> 154 152 102 32 27 25 19
+//   128^3, blocks of 8:   126 230 130 76 295 290 80 -> 154 153 102 33 19 17 12
+//   128^3, blocks of 2:   82 124 54 23 91 95 27 -> 153 153 102 30 20 9 9
+//   64^3, blocks of 1024 (per-block form): 4000 11372 15617 13706 9643 996 ->
+//                         374 434 498 569 450 64
+// 64 lanes to a chunk on the two finest levels, blocks of 64: 99 and 77 us at
+// 64^3, 658 and 409 at 128^3; 16 lanes on the third (rows of 32 entries, 342
+// chunks at 64^3): 74 us.
+constexpr int kGsChainMin = 16;
+constexpr int kGsChainRowsFew = 16384;
+constexpr int kGsChainRows = 64;
+constexpr int64_t kGsChainChunks = 2048;
+constexpr int64_t kGsShortRowChunks = 1024;
+constexpr double kGsShortRow = 24.0;
+
+template <int W, int NP>
+static void launch_chain(bool forward, int n, const int32_t* rp, const int32_t* ci, const double* v, const double* b,
+                         const double* xold, double* xnew, int block, int chunk, hipStream_t st) {
+    constexpr int G = 64 / W;
+    const int64_t per = (int64_t)chunk * G;
+    const dim3 grid((unsigned)((n + per - 1) / per)), threads(64 * (1 + NP));
+    const size_t lds = sizeof(double) * (size_t)per;
+    if (forward)
+        hipLaunchKernelGGL((hybrid_gs_chain_kernel<true, W, NP>), grid, threads, lds, st, n, rp, ci, v, b, xold, xnew,
+                           block, chunk);
+    else
+        hipLaunchKernelGGL((hybrid_gs_chain_kernel<false, W, NP>), grid, threads, lds, st, n, rp, ci, v, b, xold, xnew,
+                           block, chunk);
+}
 
 void launch_hybrid_gs(bool forward, int n, const int32_t* rp, const int32_t* ci, const double* v,
                       const double* b, const double* xold, double* xnew, int block, double mean_row,
                       hipStream_t st) {
     if (n <= 0) return;
-    if (block <= kGsMaxRows && block <= AMG_GS_STAGED_MAX) {
+    if (block <= kGsChainMaxRows && (block >= kGsChainMin || (block >= 2 && n <= kGsChainRowsFew))) {
+        const int64_t most = std::max<int64_t>(1, kGsChainRows / block);
+        const int64_t per = std::max<int64_t>(1, std::min<int64_t>(most, n / (kGsChainChunks * block)));
+        const int chunk = (int)(per * block);
+        const int64_t chunks = ((int64_t)n + chunk - 1) / chunk;
+        if (mean_row <= kGsShortRow && chunks >= kGsShortRowChunks)
+            launch_chain<16, 1>(forward, n, rp, ci, v, b, xold, xnew, block, chunk, st);
+        else launch_chain<64, 2>(forward, n, rp, ci, v, b, xold, xnew, block, chunk, st);
+        return;
+    }
+    if (block <= kGsMaxRows) {
         // chunks of whole blocks whose entries usually fit the staging buffer
         const int per = std::max(1, std::min(kGsMaxRows / block,
                                              (int)(kGsCap / (1.15 * std::max(mean_row, 1.0) * block))));

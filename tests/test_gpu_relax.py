@@ -135,3 +135,43 @@ def test_full_size_sweep_bitwise(lib):
         out = torch.zeros(A.n, dtype=torch.float64, device="cuda")
         g.level_op(0, op, dev(b), dev(x), out)
         assert host(out).tobytes() == O.gs_sweep(A, b, x, 64, fwd).tobytes(), op
+
+
+def with_hub(N, degree):
+    """2D Poisson plus one vertex coupled to `degree` of its points, so that one
+    row is far longer than the others (a symmetric M-matrix still)."""
+    A = I.poisson2d(N)
+    import scipy.sparse as sp
+    D, n = A.to_scipy(), A.n
+    at = np.linspace(0, n - 1, degree).astype(np.int64)
+    w = np.full(degree, 0.25)
+    C = sp.coo_matrix((-w, (at, np.zeros(degree, np.int64))), shape=(n, 1))
+    add = np.zeros(n)
+    add[at] = 0.25
+    M = sp.bmat([[D + sp.diags(add), C], [C.T, sp.coo_matrix([[0.25 * degree + 1.0]])]]).tocsr()
+    M.sort_indices()
+    return I.CSR(n + 1, M.indptr.astype(np.int32), M.indices.astype(np.int32), M.data.astype(np.float64))
+
+
+@pytest.mark.parametrize("make,block", [
+    (lambda: I.poisson2d(200), 16), (lambda: I.poisson2d(181), 17), (lambda: I.poisson3d(41), 63),
+    (lambda: I.poisson3d(41), 65), (lambda: I.poisson2d(65), 2), (lambda: I.poisson2d(65), 1024),
+    (lambda: I.poisson2d(65), 1025), (lambda: with_hub(200, 300), 16), (lambda: with_hub(60, 1500), 64),
+    (lambda: with_hub(60, 700), 100)],
+    ids=["16_lanes", "16_lanes_ragged", "block_63", "block_65", "smallest", "largest", "past_largest",
+         "16_lanes_long_row", "row_past_a_strip", "row_of_many_passes"])
+def test_chain_form_bitwise(lib, make, block):
+    """The edges of the chain form: its two widths, ragged last blocks, rows of
+    several passes and rows longer than a strip, the smallest and largest
+    blocks; every sweep bit for bit, like the others."""
+    A = make()
+    g, o = pair(A, block)
+    rng = np.random.default_rng(11)
+    for l in range(o.nlev - 1):
+        n = o.sizes(l)["n"]
+        b, x = rng.standard_normal(n), rng.standard_normal(n)
+        b[n // 2] = 0.0
+        for op, code in (("GS_FORWARD", 7), ("GS_BACKWARD", 8)):
+            out = torch.zeros(n, dtype=torch.float64, device="cuda")
+            g.level_op(l, op, dev(b), dev(x), out)
+            assert host(out).tobytes() == o.level_op(l, code, b, x, n).tobytes(), (l, op)
