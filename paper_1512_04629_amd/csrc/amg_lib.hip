@@ -1312,7 +1312,7 @@ template <class T>
 void block_op_t(amg_ctx* h, int kind, int l, BlockOp op, int k, const DevMat& m, const T* vals, const T* g,
                 const T* u, const T* dinv, T* y, T* y2, double* acc) {
     ProfScope ps(h, kind, l);
-    launch_block_op(op, k, CsrT<T>{m.rp, m.ci, vals, m.rows, 0.0}, g, u, dinv, (T)h->sp.omega, y, y2, acc,
+    launch_block_op(op, k, CsrT<T>{m.rp, m.ci, vals, m.rows, m.view().mean_row}, g, u, dinv, (T)h->sp.omega, y, y2, acc,
                     h->stream, h->scal + S_LIVE);
     check_launch();
 }

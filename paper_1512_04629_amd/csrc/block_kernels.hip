@@ -186,17 +186,89 @@ __device__ __forceinline__ typename Vec16<T>::type row_gather_sum(const CsrT<T>&
     return acc.s0 + acc.s1;
 }
 
-template <class T, int K, int OP>
+// The same sum with the row's entries dealt to SP parts of LPR lanes each (the
+// lanes of one wavefront): the pairs of entries (even, odd position) go round
+// the parts, each part adds its even and odd entries as row_gather_sum does,
+// and the parts' sums are added by a shuffle tree; every part returns the
+// row's sum.  The order depends on neither K nor T, so a column's bits do not
+// depend on the width of its block.  The next entries are loaded before the
+// current ones are used.
+template <class T, int K, int SP, bool DIAG>
+__device__ __forceinline__ typename Vec16<T>::type row_gather_split(const CsrT<T>& a, const T* __restrict__ g,
+                                                                    int beg, int end, int c0, int i,
+                                                                    typename Vec16<T>::type* gd) {
+    using VT = typename Vec16<T>::type;
+    constexpr int V = Vec16<T>::n;
+    constexpr int LPR = K / V;
+    constexpr int PS = LPR == 1 ? 1 : LPR / 2;   // pairs of a part per step
+    constexpr int EL = LPR == 1 ? 2 : 1;         // entries a lane loads per step
+    const int part = ((int)threadIdx.x / LPR) & (SP - 1), q = (int)threadIdx.x & (LPR - 1);
+    const int len = end - beg;
+    const int steps = (len + 2 * SP * PS - 1) / (2 * SP * PS);
+    // entry of step t this lane loads; past the row: its last entry, with value 0
+    int jn[EL];
+    T vn[EL];
+    auto load = [&](int t) {
+#pragma unroll
+        for (int e = 0; e < EL; ++e) {
+            const int pos = 2 * (part + SP * (PS * t + q / 2)) + (LPR == 1 ? e : (q & 1));
+            const int p = beg + min(pos, len - 1);
+            jn[e] = mat_ld(a.ci + p);
+            vn[e] = pos < len ? mat_ld(a.v + p) : T(0);
+        }
+    };
+    RowAcc<T, K, DIAG> acc;
+    if (steps > 0) load(0);
+    for (int t = 0; t < steps; ++t) {
+        int jc[EL];
+        T vc[EL];
+#pragma unroll
+        for (int e = 0; e < EL; ++e) {
+            jc[e] = jn[e];
+            vc[e] = vn[e];
+        }
+        if (t + 1 < steps) load(t + 1);
+#pragma unroll
+        for (int k = 0; k < 2 * PS; k += 2) {
+            int j0, j1;
+            T v0, v1;
+            if constexpr (LPR == 1) {
+                j0 = jc[0];
+                j1 = jc[EL - 1];
+                v0 = vc[0];
+                v1 = vc[EL - 1];
+            } else {
+                j0 = __shfl(jc[0], k, LPR);
+                j1 = __shfl(jc[0], k + 1, LPR);
+                v0 = __shfl(vc[0], k, LPR);
+                v1 = __shfl(vc[0], k + 1, LPR);
+            }
+            const VT g0 = ld16<VT>(g + j0 * K + c0);
+            const VT g1 = ld16<VT>(g + j1 * K + c0);
+            acc.add(false, j0, v0, g0, i);
+            acc.add(true, j1, v1, g1, i);
+        }
+    }
+    VT sum = acc.s0 + acc.s1;
+#pragma unroll
+    for (int o = LPR; o < LPR * SP; o <<= 1)
+#pragma unroll
+        for (int e = 0; e < V; ++e) sum[e] += __shfl_xor(sum[e], o, 64);
+    if constexpr (DIAG) *gd = ld16<VT>(g + i * K + c0);
+    return sum;
+}
+
+// SP = 1: a row has LPR lanes; SP > 1: SP times as many (row_gather_split)
+template <class T, int K, int OP, int SP>
 __global__ __launch_bounds__(kBlk) void block_row_kernel(CsrT<T> a, const T* __restrict__ g, const T* u,
                                                          const T* __restrict__ dinv, T omega, T* y,
                                                          T* __restrict__ y2, double* acc, int ntiles,
                                                          const double* __restrict__ live) {
     using VT = typename Vec16<T>::type;
     constexpr int V = Vec16<T>::n;
-    constexpr int LPR = K / V;          // lanes per row
-    constexpr int RPT = kBlk / LPR;     // rows per tile
-    const int lb = logical_block();
-    const int sub = threadIdx.x / LPR;
+    constexpr int LPR = K / V;                 // lanes per row and part
+    constexpr int RPT = kBlk / (LPR * SP);     // rows per tile
+    const int sub = threadIdx.x / (LPR * SP);
     const int c0 = (threadIdx.x % LPR) * V;
     // columns past the live prefix are left as they are; their lanes still
     // load and hand round their rows' entries (gathering the first columns)
@@ -207,8 +279,10 @@ __global__ __launch_bounds__(kBlk) void block_row_kernel(CsrT<T> a, const T* __r
         if (i >= a.rows) break;
         constexpr bool kSweep = OP == kBJacobi || OP == kBJacobiAccum;
         VT gi;
-        const VT s = row_gather_sum<T, K, kSweep>(a, g, a.rp[i], a.rp[i + 1], dead ? 0 : c0, i, &gi);
-        if (dead) continue;
+        VT s;
+        if constexpr (SP == 1) s = row_gather_sum<T, K, kSweep>(a, g, a.rp[i], a.rp[i + 1], dead ? 0 : c0, i, &gi);
+        else s = row_gather_split<T, K, SP, kSweep>(a, g, a.rp[i], a.rp[i + 1], dead ? 0 : c0, i, &gi);
+        if (dead || (SP > 1 && (threadIdx.x / LPR) % SP != 0)) continue;
         const int o = i * K + c0;
         if constexpr (OP == kBSpmv) {
             st16(y + o, s);
@@ -229,7 +303,7 @@ __global__ __launch_bounds__(kBlk) void block_row_kernel(CsrT<T> a, const T* __r
 
 // Per-column sums over a workgroup.  Each thread holds V consecutive columns
 // c0..c0+V-1 of its rows; threads holding the same columns are LPR = K / V
-// lanes apart.  Writes partials[lb * K + c] (fixed reduction order).
+// lanes apart.  Writes partials[c * kGridCap + lb] (fixed reduction order).
 template <int K, int V>
 __device__ __forceinline__ void store_column_partials(double (&v)[V], double* __restrict__ partials, int lb) {
     constexpr int LPR = K / V;
@@ -247,13 +321,13 @@ __device__ __forceinline__ void store_column_partials(double (&v)[V], double* __
         double tot = lds[0][threadIdx.x];
 #pragma unroll
         for (int k = 1; k < kBlk / 64; ++k) tot += lds[k][threadIdx.x];
-        partials[lb * K + threadIdx.x] = tot;
+        partials[(size_t)threadIdx.x * kGridCap + lb] = tot;
     }
 }
 
 // r = b - A x in FP64 for K columns; rt = (T) r, zt = omega dinvt rt, and r
 // itself when r64 is not null; per workgroup partial sums of r_c^2 per
-// column into partials[lb * K + c]
+// column (store_column_partials)
 template <class T, int K>
 __global__ __launch_bounds__(kBlk) void block_outer_kernel(CsrView a, const double* __restrict__ x,
                                                            const double* __restrict__ b,
@@ -291,44 +365,35 @@ __global__ __launch_bounds__(kBlk) void block_outer_kernel(CsrView a, const doub
     store_column_partials<K, 2>(nn, partials, lb);
 }
 
-// out[c] = sum over workgroups of partials[b * K + c], in a fixed order: one
-// workgroup of kFinishThreads; thread t takes column t % K and the partials
-// b = t / K + S m (S = kFinishThreads / K), into four accumulators (m mod 4)
-// so that four loads are in flight; the four are added, then the S threads
-// of a column in order (the ones in a wave with shuffles, then the waves).
-constexpr int kFinishThreads = 1024;
-
-template <int K>
-__global__ __launch_bounds__(kFinishThreads) void block_norm_finish_kernel(int nparts,
-                                                                           const double* __restrict__ partials,
-                                                                           double* __restrict__ out) {
-    constexpr int S = kFinishThreads / K;
-    constexpr int W = kFinishThreads / 64;
-    __shared__ double wsum[W][K];
-    const int c = threadIdx.x % K;
+// out[c] = the sum of column c's partials in a fixed order: a workgroup per
+// column, thread t adding partials t, t + 256, ... into four accumulators (four
+// loads in flight), then a shuffle tree per wave and the waves in order.  One
+// workgroup for all columns read 4,096 x 16 partials in 9.8 us.
+__global__ __launch_bounds__(kBlk) void block_norm_finish_kernel(int nparts, const double* __restrict__ partials,
+                                                                 double* __restrict__ out) {
+    __shared__ double wsum[kBlk / 64];
+    const double* const col = partials + (size_t)blockIdx.x * kGridCap;
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    int b = threadIdx.x / K;
-    for (; b + 3 * S < nparts; b += 4 * S) {
-        a0 += partials[b * K + c];
-        a1 += partials[(b + S) * K + c];
-        a2 += partials[(b + 2 * S) * K + c];
-        a3 += partials[(b + 3 * S) * K + c];
+    int b = threadIdx.x;
+    for (; b + 3 * kBlk < nparts; b += 4 * kBlk) {
+        a0 += col[b];
+        a1 += col[b + kBlk];
+        a2 += col[b + 2 * kBlk];
+        a3 += col[b + 3 * kBlk];
     }
-    if (b < nparts) a0 += partials[b * K + c];
-    if (b + S < nparts) a1 += partials[(b + S) * K + c];
-    if (b + 2 * S < nparts) a2 += partials[(b + 2 * S) * K + c];
+    if (b < nparts) a0 += col[b];
+    if (b + kBlk < nparts) a1 += col[b + kBlk];
+    if (b + 2 * kBlk < nparts) a2 += col[b + 2 * kBlk];
     double v = (a0 + a1) + (a2 + a3);
-    // lanes of one wave holding the same column are K apart
 #pragma unroll
-    for (int off = K; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
-    const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-    if (lane < K) wsum[w][lane] = v;
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x / 64] = v;
     __syncthreads();
-    if ((int)threadIdx.x < K) {
-        double t = wsum[0][threadIdx.x];
+    if (threadIdx.x == 0) {
+        double t = wsum[0];
 #pragma unroll
-        for (int k = 1; k < W; ++k) t += wsum[k][threadIdx.x];
-        out[threadIdx.x] = t;
+        for (int k = 1; k < kBlk / 64; ++k) t += wsum[k];
+        out[blockIdx.x] = t;
     }
 }
 
@@ -638,10 +703,24 @@ __global__ __launch_bounds__(kBlk) void block_dense_kernel(int n, int k, const d
     if (idx >= n * k) return;
     const int i = idx / k, c = idx % k;
     if (live && c >= (int)*live) return;
+    // four sums (j mod 4), eight loads in flight, where one sum waits for a
+    // load at every step
     const double* row = ainv + (size_t)i * n;
-    double s = 0.0;
-    for (int j = 0; j < n; ++j) s += row[j] * (double)b[j * k + c];
-    y[idx] = (T)s;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    int j = 0;
+    for (; j + 8 <= n; j += 8) {
+        double r[8];
+        T v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            r[u] = row[j + u];
+            v[u] = b[(j + u) * k + c];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s[u & 3] += r[u] * (double)v[u];
+    }
+    for (; j < n; ++j) s[j & 3] += row[j] * (double)b[j * k + c];
+    y[idx] = (T)((s[0] + s[1]) + (s[2] + s[3]));
 }
 
 template <class T>
@@ -675,18 +754,28 @@ int elem_grid(int64_t count) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(2048, (count + kBlk - 1) / kBlk));
 }
 
-template <class T, int K>
-void block_op_k(BlockOp op, const CsrT<T>& a, const T* g, const T* u, const T* dinv, T omega, T* y, T* y2,
-                double* acc, const double* live, hipStream_t st) {
-    constexpr int LPR = K / Vec16<T>::n;
-    constexpr int RPT = kBlk / LPR;
+// Levels of at most kSplitRows rows whose rows hold kSplitLen entries or more
+// on average give a row kSplit parts: with LPR lanes a row such a level has too
+// few wavefronts and each walks its row alone (47^3, level of 248 rows of 66
+// entries: 21 us a sweep).  us per pass, all levels at one part -> this rule
+// (8,192 rows; 100,000; every level): 16-column fv3d 96^3 19372 -> 17410
+// (17917; 17530; 18548), a served queue of 24 on 47^3 6485 -> 5530 (6064; 5814;
+// 5896), 16-column fv3d 40^3 3734 -> 2683 (2737; 2602; 2663).
+constexpr int kSplitRows = 32768;
+constexpr double kSplitLen = 8.0;
+constexpr int kSplit = 8;
+
+template <class T, int K, int SP>
+void block_op_ks(BlockOp op, const CsrT<T>& a, const T* g, const T* u, const T* dinv, T omega, T* y, T* y2,
+                 double* acc, const double* live, hipStream_t st) {
+    constexpr int RPT = kBlk / (K / Vec16<T>::n * SP);
     const int ntiles = std::max(1, (a.rows + RPT - 1) / RPT);
     const int grid = round8(std::min(ntiles, kGridCap));
     switch (op) {
-#define AMG_BLOCK_CASE(OPV)                                                                             \
-    case OPV:                                                                                           \
-        hipLaunchKernelGGL((block_row_kernel<T, K, OPV>), dim3(grid), dim3(kBlk), 0, st, a, g, u, dinv, \
-                           omega, y, y2, acc, ntiles, live);                                            \
+#define AMG_BLOCK_CASE(OPV)                                                                                 \
+    case OPV:                                                                                               \
+        hipLaunchKernelGGL((block_row_kernel<T, K, OPV, SP>), dim3(grid), dim3(kBlk), 0, st, a, g, u, dinv, \
+                           omega, y, y2, acc, ntiles, live);                                                \
         break;
         AMG_BLOCK_CASE(kBSpmv)
         AMG_BLOCK_CASE(kBSpmvScale)
@@ -697,6 +786,14 @@ void block_op_k(BlockOp op, const CsrT<T>& a, const T* g, const T* u, const T* d
 #undef AMG_BLOCK_CASE
         default: break;
     }
+}
+
+template <class T, int K>
+void block_op_k(BlockOp op, const CsrT<T>& a, const T* g, const T* u, const T* dinv, T omega, T* y, T* y2,
+                double* acc, const double* live, hipStream_t st) {
+    if (a.rows <= kSplitRows && a.mean_row >= kSplitLen)
+        block_op_ks<T, K, kSplit>(op, a, g, u, dinv, omega, y, y2, acc, live, st);
+    else block_op_ks<T, K, 1>(op, a, g, u, dinv, omega, y, y2, acc, live, st);
 }
 
 template <class T>
@@ -716,8 +813,7 @@ int fp64_tiles(int rows) {
 
 template <int K>
 void finish(int grid, const ColumnDots& dot, hipStream_t st) {
-    hipLaunchKernelGGL((block_norm_finish_kernel<K>), dim3(1), dim3(kFinishThreads), 0, st, grid, dot.partials,
-                       dot.result);
+    hipLaunchKernelGGL(block_norm_finish_kernel, dim3(K), dim3(kBlk), 0, st, grid, dot.partials, dot.result);
 }
 
 // calls f.template operator()<K>() with the compile-time width

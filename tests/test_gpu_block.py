@@ -300,3 +300,28 @@ def test_block_pcg_zero_and_converged_columns_stay_fixed(lib):
     assert res.converged and res.col_iters[3] == 0 and res.col_relres[3] == 0.0
     assert torch.count_nonzero(X[:, 3]).item() == 0
     assert np.all(np.isfinite(X.cpu().numpy()))
+
+
+@pytest.mark.parametrize("make", [lambda: I.random_graph_laplacian(3000), lambda: I.poisson3d(41),
+                                  lambda: I.random_graph_laplacian(700, degree=30)],
+                         ids=["long_rows", "both_sides_of_the_row_limit", "fine_level_split"])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_rows_in_parts_same_bits_at_every_width(lib, make, dtype):
+    """Rows dealt to several parts of lanes (few, long rows): the FP64 cycle
+    meets the oracle's bar, and a column's bits are the same in blocks of 4, 8
+    and 16 columns."""
+    A = make()
+    g, o = hier(A)
+    B, X0 = block_rhs(A.n, 16, 500), block_rhs(A.n, 16, 600)
+    got = {}
+    for k in (16, 8, 4):
+        X = dev(X0[:, :k], dtype)
+        g.vcycle_block(dev(B[:, :k], dtype), X)
+        torch.cuda.synchronize()
+        got[k] = X.cpu().numpy()
+    for k in (4, 8):
+        assert np.ascontiguousarray(got[16][:, :k]).tobytes() == got[k].tobytes(), k
+    for c in (0, 15):
+        ref = o.vcycle(B[:, c], X0[:, c])
+        bar = 1e-12 if dtype == torch.float64 else 2e-5
+        assert np.linalg.norm(got[16][:, c] - ref) <= bar * np.linalg.norm(ref), c
