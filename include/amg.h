@@ -395,14 +395,18 @@ amg_status amg_export_split(amg_handle h, int32_t l, int32_t* cf);
    bits when the form is switched off.  amg_index_width reports the bytes
    per column index the FP64 row kernels read for matrix `which` (AMG_MAT_*)
    of level l: 1, 2 or 4 (of the SELL-64 copy where one exists; the FP32
-   cycle reads the CSR form's). */
+   cycle reads the CSR form's).  Operators whose blocks of 256 rows hold few
+   distinct (column - base column, value) pairs are kept as tables of those
+   pairs and a code of 1 (square and interpolation operators) or 2 bytes
+   (restrictions) per entry while the compact form is on; the code's width is
+   then the width reported, and both precisions read it. */
 amg_status amg_set_compact_indices(amg_handle h, int32_t enable);
 amg_status amg_index_width(amg_handle h, int32_t l, int32_t which, int32_t* bytes);
 
 /* Which FP64 row kernel serves matrix `which` (AMG_MAT_*) of level l:
    AMG_FORMAT_ROW, a subgroup of lanes per CSR row (small levels, long rows);
    AMG_FORMAT_STREAM, CSR row blocks staged through LDS (large levels with
-   short rows); AMG_FORMAT_SELL, a SELL-64 copy built at setup (large levels
+   short rows); AMG_FORMAT_SELL, a SELL-64 copy or its pair-coded form built at setup (large levels
    with short rows whose slices pad the entries by at most a tenth: one lane
    per row, a wavefront per slice of 64 rows, coalesced loads of every
    entry).  Results do not depend on it beyond rounding of the row sums. */

@@ -91,13 +91,23 @@ struct DevMat {
     int32_t* sl_tab = nullptr;
     int64_t sl_cap = 0;               // entries the SELL-64 arrays hold
     float* sl_val32 = nullptr;        // FP32 values of the copy (FP32 cycle; built with the FP32 mirror)
+    // pair-coded form, instead of the SELL-64 copy (null: not built); serves both precisions
+    uint32_t* pc_word = nullptr;
+    int32_t* pc_base = nullptr;
+    int32_t* pc_tabo = nullptr;
+    double* pc_tabv = nullptr;
+    double* pc_tabr = nullptr;
+    int pc_stride = 0, pc_words = 0;
+    CodedKind pc_kind = kCodedSquare;
     // direction of this operator's next cycle pass (flipped by every pass),
     // shared with the copies that alias the operator (Ah = A), so that
     // passes alternate whichever copy they go through
     std::shared_ptr<int> next_rev = std::make_shared<int>(0);
+    bool sell() const { return sl_off || pc_word; }   // a SELL-64 form, plain or coded
     CsrView view() const {
         return CsrView{rp, ci, v, rows, rows ? (double)shape_nnz / rows : 1.0, ci16, cbase, idx_rb, 0,
-                       sl_off, sl_col, sl_val, sl_maxw, sl_col16, sl_base, sl_idx8, sl_tab};
+                       sl_off, sl_col, sl_val, sl_maxw, sl_col16, sl_base, sl_idx8, sl_tab,
+                       pc_word, pc_base, pc_tabo, pc_tabv, pc_tabr, pc_stride, pc_words, pc_kind};
     }
 };
 
@@ -257,6 +267,8 @@ void free_mat(amg_ctx* h, DevMat& m) {
     dfree(h, m.sl_idx8);
     dfree(h, m.sl_tab);
     dfree(h, m.sl_val32);
+    for (void* q : {(void*)m.pc_word, (void*)m.pc_base, (void*)m.pc_tabo, (void*)m.pc_tabv, (void*)m.pc_tabr})
+        dfree(h, q);
     m = DevMat{};
 }
 
@@ -408,7 +420,8 @@ void row_op(amg_ctx* h, int kind, int level, RowOp op, const DevMat& m, const fl
     // the SELL-64 copy's FP32 values are the same narrowed values in slice order
     const CsrView32 a32{m.rp, m.ci, vals, m.rows, m.view().mean_row, m.ci16, m.cbase, m.idx_rb, *m.next_rev,
                         m.sl_val32 ? m.sl_off : nullptr, m.sl_col, m.sl_val32, m.sl_maxw, m.sl_col16, m.sl_base,
-                        m.sl_idx8, m.sl_tab};
+                        m.sl_idx8, m.sl_tab, m.pc_word, m.pc_base, m.pc_tabo, m.pc_tabv, m.pc_tabr,
+                        m.pc_stride, m.pc_words, m.pc_kind};
     *m.next_rev ^= 1;
     launch_row_op(op, m.width, a32, g, u, dinv, (float)h->sp.omega, y, y2, h->stream);
     check_launch();
@@ -1175,7 +1188,7 @@ amg_status solve(amg_ctx* h, const double* b, double* x, const amg_solve_params&
             if (window_end) {
                 DevLevel& f0 = h->lv[0];
                 const bool fuse = pcg && !mixed && !gs_on(h) && h->sp.nu_pre == 1 && h->lv.size() > 1 &&
-                                  f0.ah_alias && A.sl_off != nullptr;
+                                  f0.ah_alias && A.sell();
                 if (fuse) {
                     const DotTarget dt = dot_to(h, S_NRT);
                     CsrView cv = A.view();
@@ -2020,6 +2033,69 @@ void build_sell(amg_ctx* h, DevMat& m) {
     }
 }
 
+// Pair-coded form (coded_kernels.hip) where every block of 256 rows holds few
+// distinct (offset, value) pairs.  Square and restriction operators in place of
+// the SELL-64 copy they would get, with its rounding (one byte a code, two for
+// the restrictions, whose blocks hold more pairs); interpolation operators of
+// at least kCodedInterpNnz entries in place of the LDS-staged kernel where
+// that sums a row in one lane, with its rounding (smaller ones stay in the
+// caches and their launches cost more than their entries).  Kept if its bytes
+// are at most kCodedShare of those it replaces: 3D Poisson 128^3 takes it on
+// levels 0 and 1 at a fifth of the bytes (step 4.30 -> 3.03 ms), the aniso 1000^2
+// FP32-cycle solve 11.2 -> 9.6 ms; operators with values of their own in every
+// row (finite volumes, deeper levels) are out after their first blocks' count.
+constexpr int64_t kCodedInterpNnz = 1 << 20;
+constexpr double kCodedShare = 0.6;
+
+void drop_coded(amg_ctx* h, DevMat& m) {
+    for (void* p : {(void*)m.pc_word, (void*)m.pc_base, (void*)m.pc_tabo, (void*)m.pc_tabv, (void*)m.pc_tabr})
+        dfree(h, p);
+    m.pc_word = nullptr;
+    m.pc_base = m.pc_tabo = nullptr;
+    m.pc_tabv = m.pc_tabr = nullptr;
+    m.pc_stride = m.pc_words = 0;
+}
+
+bool build_coded(amg_ctx* h, DevMat& m) {
+    if (!h->compact_idx || m.nnz <= 0) return false;
+    if (m.pc_word) return true;
+    const CodedKind kind = m.rows == m.cols ? kCodedSquare : m.rows > m.cols ? kCodedInterp : kCodedRestrict;
+    if (kind == kCodedInterp ? (m.nnz < kCodedInterpNnz || stream_block_rows(m.view()) != 256)
+                             : !sell_candidate(m.view()))
+        return false;
+    int32_t* most = h->cnt;
+    launch_fill_u32(2, reinterpret_cast<unsigned*>(most), 0u, h->stream);
+    launch_coded_count(m.rows, kind, m.rp, m.ci, m.v, most, h->stream);
+    check_launch();
+    int32_t top[2] = {0, 0};
+    download(h, top, most, 2);
+    sync(h);
+    const int words = coded_words(kind, top[1]);
+    if (top[0] > coded_limit(kind) || words == 0) return false;
+    const int stride = (top[0] + 7) / 8 * 8;
+    const int64_t nb = ((int64_t)m.rows + 255) / 256;
+    const double bytes = 1024.0 * words * nb + (kind == kCodedSquare ? 20.0 : 12.0) * stride * nb +
+                         (kind == kCodedSquare ? 0.0 : 4.0 * m.rows);
+    const double was = kind == kCodedInterp ? 10.0 * m.nnz + 4.0 * m.rows : 9.0 * m.nnz;
+    if (bytes > kCodedShare * was) return false;
+    uint32_t* word = dalloc_n<uint32_t>(h, 256 * words * nb);
+    int32_t* tabo = dalloc_n<int32_t>(h, nb * stride);
+    double* tabv = dalloc_n<double>(h, nb * stride);
+    double* tabr = kind == kCodedSquare ? dalloc_n<double>(h, nb * stride) : nullptr;
+    int32_t* base = kind == kCodedSquare ? nullptr : dalloc_n<int32_t>(h, m.rows);
+    launch_coded_fill(m.rows, kind, m.rp, m.ci, m.v, words, word, base, stride, tabo, tabv, tabr, h->stream);
+    check_launch();
+    m.pc_word = word;
+    m.pc_base = base;
+    m.pc_tabo = tabo;
+    m.pc_tabv = tabv;
+    m.pc_tabr = tabr;
+    m.pc_stride = stride;
+    m.pc_words = words;
+    m.pc_kind = kind;
+    return true;
+}
+
 void drop_sell(amg_ctx* h, DevMat& m) {
     for (void* p : {(void*)m.sl_off, (void*)m.sl_col, (void*)m.sl_val, (void*)m.sl_col16, (void*)m.sl_base,
                     (void*)m.sl_idx8, (void*)m.sl_tab, (void*)m.sl_val32})
@@ -2048,6 +2124,15 @@ void set_compact_indices(amg_ctx* h, bool on) {
     for (auto& d : h->lv) {
         for (DevMat* m : {&d.A, &d.P, &d.R}) {
             if (!m->rp) continue;
+            if (!on && m->pc_word) {
+                drop_coded(h, *m);
+                build_sell(h, *m);
+                if (h->fp32) sell_fp32(h, *m);
+            }
+            if (on && build_coded(h, *m)) {
+                drop_sell(h, *m);
+                continue;
+            }
             if (on) compress_indices(h, *m);
             else drop_indices(h, *m);
             if (m->sl_off && (m->sl_col == nullptr) != on) {
@@ -2072,7 +2157,7 @@ void finish_setup(amg_ctx* h) {
     h->singular = dalloc_n<int>(h, 1);
     int nmax = 0;
     for (auto& d : h->lv) nmax = std::max(nmax, d.n);
-    h->cnt = dalloc_n<int32_t>(h, nmax + 1);
+    h->cnt = dalloc_n<int32_t>(h, nmax + 2);
     h->scan_scratch = dalloc_n<int32_t>(h, scan_scratch_ints(nmax));
     {
         int64_t ncnt = 0, nbsum = 0;
@@ -2094,12 +2179,15 @@ void finish_setup(amg_ctx* h) {
     }
     for (int l = 0; l <= L; ++l) {
         DevLevel& d = h->lv[l];
-        compress_indices(h, d.A);
-        build_sell(h, d.A);
+        auto formats = [&](DevMat& m, bool sell) {
+            if (build_coded(h, m)) return;
+            compress_indices(h, m);
+            if (sell) build_sell(h, m);
+        };
+        formats(d.A, true);
         if (l < L) {
-            compress_indices(h, d.P);
-            compress_indices(h, d.R);
-            build_sell(h, d.R);
+            formats(d.P, false);
+            formats(d.R, true);
         }
         d.Ah = d.A;
         d.ah_alias = true;
@@ -2831,7 +2919,7 @@ amg_status amg_index_width(amg_handle h, int32_t l, int32_t which, int32_t* byte
         return AMG_ERR_INVALID_ARG;
     const DevLevel& d = h->lv[l];
     const DevMat& m = which == AMG_MAT_A ? d.A : which == AMG_MAT_AHAT ? d.Ah : which == AMG_MAT_P ? d.P : d.R;
-    *bytes = m.sl_off ? (m.sl_idx8 ? 1 : m.sl_col16 ? 2 : 4) : m.ci16 ? 2 : 4;
+    *bytes = m.pc_word ? (m.pc_kind == kCodedRestrict ? 2 : 1) : m.sl_off ? (m.sl_idx8 ? 1 : m.sl_col16 ? 2 : 4) : m.ci16 ? 2 : 4;
     return AMG_OK;
 }
 
@@ -2842,7 +2930,7 @@ amg_status amg_row_format(amg_handle h, int32_t l, int32_t which, int32_t* forma
     const DevLevel& d = h->lv[l];
     const DevMat& m = which == AMG_MAT_A ? d.A : which == AMG_MAT_AHAT ? d.Ah : which == AMG_MAT_P ? d.P : d.R;
     if (!m.rp) return AMG_ERR_INVALID_ARG;
-    *format = m.sl_off ? AMG_FORMAT_SELL : stream_block_rows(m.view()) ? AMG_FORMAT_STREAM : AMG_FORMAT_ROW;
+    *format = m.sell() ? AMG_FORMAT_SELL : stream_block_rows(m.view()) ? AMG_FORMAT_STREAM : AMG_FORMAT_ROW;
     return AMG_OK;
 }
 

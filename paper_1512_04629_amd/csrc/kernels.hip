@@ -8,6 +8,7 @@
 // shuffles and the epilogue (residual, Jacobi update, dot products) is fused
 // into the same pass so that every vector is read once.
 #include "kernels.hpp"
+#include "row_common.hpp"
 
 #include <hip/hip_ext.h>
 
@@ -18,8 +19,6 @@
 namespace amg355 {
 namespace {
 
-constexpr int kBlock = 256;
-constexpr int kXcds = 8;            // MI355X: 8 accelerator complex dies, each with its own L2
 #ifndef AMG_ROW_GRID_CAP
 #define AMG_ROW_GRID_CAP 4096
 #endif
@@ -29,8 +28,7 @@ constexpr int kRowGridCap = AMG_ROW_GRID_CAP;   // row kernels loop over tiles b
 // AMG_WIDTH_SCALE (1 = the power of two nearest the mean row length),
 // AMG_RIF is the number of row tiles in flight per subgroup, AMG_MIN_WIDTH the
 // narrowest subgroup, AMG_USE_STREAM selects the LDS-staged kernel (-1: by
-// matrix shape, 0: never, 1: always), AMG_XCD_REMAP toggles
-// the XCD-contiguous block order.
+// matrix shape, 0: never, 1: always).
 #ifndef AMG_WIDTH_SCALE
 #define AMG_WIDTH_SCALE 0.5
 #endif
@@ -42,9 +40,6 @@ constexpr int kRowGridCap = AMG_ROW_GRID_CAP;   // row kernels loop over tiles b
 #endif
 #ifndef AMG_USE_STREAM
 #define AMG_USE_STREAM -1
-#endif
-#ifndef AMG_XCD_REMAP
-#define AMG_XCD_REMAP 1
 #endif
 #ifndef AMG_STREAM_CAP
 #define AMG_STREAM_CAP 2048
@@ -88,20 +83,6 @@ __device__ __forceinline__ T stream_ld(const T* p) {
 #endif
 }
 
-// Workgroups are handed to the XCDs round-robin.  Remap so that XCD x works on
-// a contiguous range of logical blocks: neighbouring rows gather neighbouring
-// entries of x, which then stay in one L2.  The grid is a multiple of 8.
-__device__ __forceinline__ int xcd_logical_block() {
-#if AMG_XCD_REMAP
-    const int per = gridDim.x / kXcds;
-    return (blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
-#else
-    return blockIdx.x;
-#endif
-}
-
-int round_up8(int b) { return (b + kXcds - 1) / kXcds * kXcds; }
-
 // Events armed by set_launch_events: the next row-kernel launch records its
 // own start and end in them (hipExtLaunchKernel), so that a timing of it
 // covers the kernel as a profiler's kernel trace does.
@@ -144,33 +125,6 @@ __device__ __forceinline__ int sub_sum_int(int v) {
 #pragma unroll
     for (int o = W / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, W);
     return v;
-}
-
-// Block-wide sum of v; the total is valid in thread 0.
-__device__ __forceinline__ double block_sum(double v, double* lds) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    const int wid = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) lds[wid] = v;
-    __syncthreads();
-    double t = 0.0;
-    if (threadIdx.x == 0) {
-        t = lds[0];
-#pragma unroll
-        for (int w = 1; w < kBlock / 64; ++w) t += lds[w];
-    }
-    __syncthreads();
-    return t;
-}
-
-// Deterministic grid reduction, first pass: every block stores its partial
-// sum; dot_finish_kernel adds the partials in a fixed order.  (A single-pass
-// last-block scheme would need an agent-scope release fence per block, which
-// on gfx950 writes back the XCD's L2 and stalls the block.)
-__device__ __forceinline__ void store_block_partial(double v, double* partials, int lb) {
-    __shared__ double lds[kBlock / 64];
-    const double t = block_sum(v, lds);
-    if (threadIdx.x == 0) partials[lb] = t;
 }
 
 constexpr int kFinishBlock = 1024;
@@ -2034,6 +1988,7 @@ int row_launch_blocks(int rows, int width) {
 template <class T>
 int launch_row_op_t(RowOp op, int width, const CsrT<T>& a, const T* g, const T* u,
                     const T* dinv, T omega, T* y, T* y2, DotTarget dot, hipStream_t st) {
+    if (a.pc_word) return launch_coded_op(op, a, g, u, dinv, omega, y, y2, dot, st);
     if (AMG_SELL && a.sl_off) return launch_sell(op, a, g, u, dinv, omega, y, y2, dot, st);
     if (use_stream_kernel(a)) return launch_stream_any(op, a, g, u, dinv, omega, y, y2, dot, st);
     switch (width) {
@@ -2063,6 +2018,14 @@ void launch_dot_finish(const DotTarget& dot, int nparts, hipStream_t st) { finis
 void set_launch_events(hipEvent_t start, hipEvent_t stop) {
     t_ev_start = start;
     t_ev_stop = stop;
+}
+
+bool take_launch_events(hipEvent_t* start, hipEvent_t* stop) {
+    if (!t_ev_start) return false;
+    *start = t_ev_start;
+    *stop = t_ev_stop;
+    t_ev_start = t_ev_stop = nullptr;
+    return true;
 }
 
 bool clear_launch_events() {
@@ -2165,6 +2128,7 @@ void launch_dot(int n, const double* a, const double* b, DotTarget dot, hipStrea
 
 int launch_sell_dual_resid(const CsrView& a, const double* g, const double* u, double* y, const double* g2,
                            const double* u2, double* y2, DotTarget dot, hipStream_t st) {
+    if (a.pc_word) return launch_coded_dual_resid(a, g, u, y, g2, u2, y2, dot, st);
     if (!AMG_SELL || !a.sl_off) return 0;
     const int w = a.sl_maxw;
     if (w <= 8) return launch_sell_dual_u<8>(a, g, u, y, g2, u2, y2, dot, st);

@@ -7,6 +7,10 @@
 
 namespace amg355 {
 
+// Which operator a pair-coded form (coded_kernels.hip) stands for: its code
+// width and its rounding.
+enum CodedKind : int { kCodedSquare = 0, kCodedRestrict = 1, kCodedInterp = 2 };
+
 // Read-only view of a device CSR matrix with values of type T.
 template <class T>
 struct CsrT {
@@ -42,6 +46,17 @@ struct CsrT {
     // the column of entry p of row r is r + sl_tab[64 s + sl_idx8[p]]
     const uint8_t* sl_idx8 = nullptr;
     const int32_t* sl_tab = nullptr;
+    // optional pair-coded form, instead of the SELL-64 copy (coded_kernels.hip):
+    // per block of 256 rows a table of (offset, value) pairs, pc_stride places
+    // a block (place 0: padding), and per row pc_words words of codes, one or
+    // two bytes each, its entries' places; row r's entries are at the columns
+    // pc_base[r] + offset (r + offset where pc_base is null)
+    const uint32_t* pc_word = nullptr;
+    const int32_t* pc_base = nullptr;
+    const int32_t* pc_tabo = nullptr;
+    const double* pc_tabv = nullptr;
+    const double* pc_tabr = nullptr;    // reciprocal values (square operators)
+    int pc_stride = 0, pc_words = 0, pc_kind = 0;
 };
 using CsrView = CsrT<double>;
 using CsrView32 = CsrT<float>;
@@ -90,9 +105,32 @@ void launch_dot_finish(const DotTarget& dot, int nparts, hipStream_t st);
 // clear_launch_events disarms them and tells whether they were still armed.
 void set_launch_events(hipEvent_t start, hipEvent_t stop);
 bool clear_launch_events();
+// hands the armed events to a launch in another file (false: none armed)
+bool take_launch_events(hipEvent_t* start, hipEvent_t* stop);
 // single precision: values, vectors and accumulation in FP32 (no dot ops)
 void launch_row_op(RowOp op, int width, const CsrView32& a, const float* g, const float* u,
                    const float* dinv, float omega, float* y, float* y2, hipStream_t st);
+
+// Row operations on the pair-coded form (coded_kernels.hip); returns and
+// partials as launch_row_op.
+int launch_coded_op(RowOp op, const CsrView& a, const double* g, const double* u, const double* dinv, double omega,
+                    double* y, double* y2, DotTarget dot, hipStream_t st);
+int launch_coded_op(RowOp op, const CsrView32& a, const float* g, const float* u, const float* dinv, float omega,
+                    float* y, float* y2, DotTarget dot, hipStream_t st);
+int launch_coded_dual_resid(const CsrView& a, const double* g, const double* u, double* y, const double* g2,
+                            const double* u2, double* y2, DotTarget dot, hipStream_t st);
+// Building it from CSR: the most pairs of a block (the padding's place included)
+// and the longest row in most[0..1] (most[0] > coded_limit: not codable);
+// coded_words gives the words a row of that length takes (0: too long).  Then
+// the codes (whole blocks of rows), base columns (null for square operators) and
+// tables, whose reciprocals tabr may be null.
+int coded_limit(CodedKind kind);
+int coded_words(CodedKind kind, int longest);
+void launch_coded_count(int rows, CodedKind kind, const int32_t* rp, const int32_t* ci, const double* v,
+                        int32_t* most, hipStream_t st);
+void launch_coded_fill(int rows, CodedKind kind, const int32_t* rp, const int32_t* ci, const double* v, int words,
+                       uint32_t* word, int32_t* base, int stride, int32_t* tabo, double* tabv, double* tabr,
+                       hipStream_t st);
 
 // ---- vector kernels -----------------------------------------------------
 // x += alpha p; r -= alpha q; dot -> |r|^2, with alpha = scal[i_num]/scal[i_den];
