@@ -26,6 +26,7 @@
 
 #include "../../include/amg.h"
 #include "block_kernels.hpp"
+#include "grid_kernels.hpp"
 #include "host_setup.hpp"
 #include "kernels.hpp"
 #include "lump_kernels.hpp"
@@ -126,6 +127,11 @@ struct DevLevel {
     int32_t* kcnt = nullptr;      // kept entries per row, and per block of the keep_count launch
     int32_t* kbsum = nullptr;     //   (regions of the handle's sp_cnt / sp_bsum)
     double* rowmax = nullptr;     // m_i of A
+    // index ranges of the level in a grid launch (grid_kernels.hip; null: too
+    // large); the LDS entries a workgroup needs, the entries of A it reads to
+    // form the residual again and those of its share (of the Galerkin operator)
+    int32_t* gwin = nullptr;
+    int gspan = 0, gagain = 0, gshare = 0;
     double* lump_thr = nullptr;   // strong-neighbour lumping: strength thresholds of A's rows
     double* lump_den = nullptr;   //   and share denominators per dropped entry of A
     bool have_m = false;
@@ -213,6 +219,10 @@ struct amg_ctx {
     double *bcg_r = nullptr, *bcg_p = nullptr, *bcg_q = nullptr, *bcg_z = nullptr;
     int blk_pack_k = 0;
     std::string last_error;
+    unsigned* grid_flags = nullptr;   // the grid launches' barrier words, then their failure word
+    double* grid_part = nullptr;      // their partial sums
+    double* grid_out = nullptr;       // host-coherent: results of a grid solve, then its residual norms
+    double* grid_out_dev = nullptr;   // its device address
     bool check_singular = false;   // a device inversion wrote h->singular, not read back yet
     bool profiling = false;
     int prof_kind = -1, prof_level = -1;
@@ -809,6 +819,153 @@ int tail_start(const amg_ctx* h) {
     return 0;
 }
 
+// The levels from `first` to the coarsest run in one launch (grid_kernels.hip):
+// first..tail-1 shared by its workgroups, tail..L in the last one's LDS.
+struct GridPlan {
+    int first = -1, tail = 0;   // first < 0: not used
+    size_t lds = 0;
+};
+
+// Levels of at most kGridRows rows whose share of a workgroup is at most
+// kGridShare entries; their residual is formed again rather than exchanged
+// where that reads at most kGridAgain entries a workgroup.  Beyond, one launch a
+// step over the whole device is faster.  us a solve, launched -> this rule
+// (share 12,000 and again 24,000; 16,384 rows): 2D Poisson 64^2 812 -> 365, 150^2
+// 942 -> 473 (703; 687), 200^2 1109 -> 623 (813; 777), 3D Poisson 16^3 1142 -> 517,
+// 28^3 1135 -> 781 (1048; 893), 47^3 1299 -> 1189 (1280; 1103), random graph of
+// 3,000 vertices 954 -> 575, anisotropic 1000^2 FP32 9577 -> 8990 (8978; 8833),
+// lognormal FV 100^3 5390 -> 5244 (5238; 5220).
+constexpr int kGridRows = 65536;
+constexpr int kGridShare = 6500;
+constexpr int kGridAgain = 12000;
+constexpr int kGridHist = 1024;      // residual norms a grid solve can hand back
+
+inline size_t lds_align(size_t b) { return (b + 15) & ~(size_t)15; }
+
+// LDS layout of the tail levels; fills a.tl and the copy list when a is given
+template <class T>
+size_t grid_tail_layout(amg_ctx* h, int tail, GridArgs<T>* a) {
+    const int L = (int)h->lv.size() - 1;
+    size_t off = 0;
+    int runs = 0;
+    auto place = [&](const void* src, size_t bytes) {
+        const uint32_t at = (uint32_t)off;
+        if (src && a) a->run[runs++] = GridRun{static_cast<const uint32_t*>(src), (uint32_t)(bytes / 4), at};
+        off += lds_align(bytes);
+        return at;
+    };
+    auto mat = [&](const DevMat& m, const T* v, int64_t cap) {
+        GridTailMat t{};
+        t.rp = place(m.rp, ((size_t)m.rows + 1) * 4);
+        t.ci = place(m.ci, (size_t)cap * 4);
+        t.v = place(v, (size_t)cap * sizeof(T));
+        t.rows = m.rows;
+        return t;
+    };
+    for (int l = tail; l <= L; ++l) {
+        LevelView<T> v = level_view(h, l, (T*)nullptr);
+        const size_t vec = (size_t)v.n * sizeof(T);
+        GridTailLevel t{};
+        t.n = v.n;
+        t.A = mat(*v.Ah, v.ahv, v.Ah->shape_nnz);   // a sparsified operator's arrays hold the Galerkin count
+        t.dinv = place(v.dinv, vec);
+        t.b = place(nullptr, vec);
+        t.x = place(nullptr, vec);
+        t.xt = place(nullptr, vec);
+        t.r = place(nullptr, vec);
+        if (l < L) {
+            t.R = mat(*v.R, v.rv, v.R->nnz);
+            t.P = mat(*v.P, v.pv, v.P->nnz);
+        }
+        if (a) a->tl[l - tail] = t;
+    }
+    const uint32_t inv = place(h->coarse_inv, (size_t)h->nL * h->nL * 8);
+    if (a) {
+        a->inv = inv;
+        a->runs = runs;
+    }
+    return off;
+}
+
+// levels of the cycle from `from` on (0: a whole solve, whose finest operator is
+// gathered in FP64)
+template <class T>
+GridPlan grid_plan(amg_ctx* h, int from) {
+    GridPlan p;
+    const int L = (int)h->lv.size() - 1;
+    if (!h->grid_flags || h->sp.nu_pre != 1 || h->sp.nu_post != 1 || L < 1) return p;
+    const size_t limit = grid_lds_limit();
+    int tail = 0;
+    for (int l = std::max(from + 1, L - kGridTailLevels + 1); l <= L; ++l)
+        if (h->lv[l].n <= kTailRows && (p.lds = grid_tail_layout<T>(h, l, nullptr)) <= limit) {
+            tail = l;
+            break;
+        }
+    if (tail == 0) return p;
+    int first = tail;
+    for (int l = tail - 1; l >= from && tail - l <= kGridLevels; --l) {
+        const DevLevel& d = h->lv[l];
+        const size_t win = (l == 0 ? sizeof(double) : sizeof(T)) * (size_t)d.gspan;
+        if (!d.gwin || d.gshare > kGridShare || win > limit) break;
+        p.lds = std::max(p.lds, win);
+        first = l;
+    }
+    if (first == tail || (from == 0 && first != 0)) return p;
+    p.first = first;
+    p.tail = tail;
+    return p;
+}
+
+// most lanes a row is given: no more than it has use for
+int grid_lanes(const DevMat& m) {
+    const double mean = m.rows ? (double)m.shape_nnz / m.rows : 1.0;
+    int w = 1;
+    while (w < 64 && w < mean) w *= 2;
+    return w;
+}
+
+template <class T>
+GridArgs<T> grid_args(amg_ctx* h, const GridPlan& p) {
+    GridArgs<T> a{};
+    const int L = (int)h->lv.size() - 1;
+    auto op = [&](const DevMat& m, const T* v) { return GridOp<T>{m.rp, m.ci, v, m.rows, grid_lanes(m)}; };
+    a.count = p.tail - p.first;
+    for (int k = 0; k < a.count; ++k) {
+        const DevLevel& d = h->lv[p.first + k];
+        LevelView<T> v = level_view(h, p.first + k, (T*)nullptr);
+        a.lv[k] = GridLevel<T>{op(*v.Ah, v.ahv), op(*v.R, v.rv), op(*v.P, v.pv), v.dinv, d.gwin, v.b, v.xt, v.r,
+                               d.gagain <= kGridAgain ? 1 : 0};
+    }
+    a.tail_count = L - p.tail + 1;
+    grid_tail_layout<T>(h, p.tail, &a);
+    LevelView<T> t = level_view(h, p.tail, (T*)nullptr);
+    a.tail_b = t.b;
+    a.tail_out = t.xt;
+    a.omega = (T)h->sp.omega;
+    a.flags = h->grid_flags;
+    a.failed = h->grid_flags + kGridWgs + 1;
+    return a;
+}
+
+template <class T>
+void grid_cycle(amg_ctx* h, const GridPlan& p) {
+    ProfScope ps(h, AMG_K_COARSE, p.first);
+    launch_grid_cycle(grid_args<T>(h, p), p.lds, h->stream);
+    check_launch();
+}
+
+// After a breakdown: whether a grid cycle's barrier ran out of time (its result
+// is then not a number); its words are set back so that the handle stays
+// usable.
+bool grid_failed(amg_ctx* h) {
+    if (!h->grid_flags) return false;
+    unsigned failed = 0;
+    download(h, &failed, h->grid_flags + kGridWgs + 1, 1);
+    sync(h);
+    if (failed) launch_fill_u32(kGridWgs + 2, h->grid_flags, 0u, h->stream);
+    return failed != 0;
+}
+
 // Buffer that receives the zero-guess smoothing sweep omega D^-1 b of level
 // l: on level 0 chosen so that after all later sweeps (each swaps buffers)
 // the result lands in x0.
@@ -842,8 +999,9 @@ void vcycle(amg_ctx* h, const T* b0, T* x0, Guess guess0, int dot_slot, bool l0_
         return;
     }
     std::vector<T*> cur(L + 1), alt(L + 1);
-    const int tail = tail_start(h);
-    const int down_end = tail > 0 ? tail : L;
+    const GridPlan grid = grid_plan<T>(h, 1);
+    const int tail = grid.first > 0 ? 0 : tail_start(h);
+    const int down_end = grid.first > 0 ? grid.first : tail > 0 ? tail : L;
     for (int l = 0; l < down_end; ++l) {
         LevelView<T> v = level_view(h, l, (T*)nullptr);
         const T* b = l == 0 ? b0 : v.b;
@@ -881,7 +1039,10 @@ void vcycle(amg_ctx* h, const T* b0, T* x0, Guess guess0, int dot_slot, bool l0_
         else
             row_op_t(h, AMG_K_RESTRICT, l, kSpmv, *v.R, v.rv, v.r, nullptr, nullptr, nx.b, nullptr, -1);
     }
-    if (tail > 0) {
+    if (grid.first > 0) {
+        grid_cycle<T>(h, grid);
+        cur[grid.first] = level_view(h, grid.first, (T*)nullptr).xt;
+    } else if (tail > 0) {
         // levels tail..L in one workgroup; the level-tail result lands in its xt
         TailArgs<T> ta{};
         ta.count = L - tail + 1;
@@ -1035,6 +1196,19 @@ void ensure_solve_buffers(amg_ctx* h) {
     if (!h->rt) h->rt = dalloc_n<double>(h, n);
 }
 
+// waits until the stream's work has published `seq`
+void await_published(amg_ctx* h, uint32_t seq) {
+    const uint32_t* flag = h->flag_host;
+    for (uint64_t k = 1; __atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq; ++k) {
+        if ((k & 4095) != 0) continue;
+        const hipError_t e = hipStreamQuery(h->stream);
+        if (e == hipErrorNotReady) continue;
+        if (e != hipSuccess) throw AmgFailure{AMG_ERR_DEVICE, std::string("device error: ") + hipGetErrorString(e)};
+        if (__atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq)
+            throw AmgFailure{AMG_ERR_DEVICE, "scalar readback: the stream finished without publishing"};
+    }
+}
+
 // Reads the scalar slots into host memory: a one-workgroup kernel writes
 // them into the handle's host-coherent buffer and then a sequence number;
 // the host polls for that number (a fault or a failed launch ends the wait
@@ -1047,17 +1221,10 @@ const double* read_scalars(amg_ctx* h, const int* extra = nullptr) {
     const uint32_t seq = ++h->pub_seq;
     launch_publish_scalars(S_COUNT, h->scal, h->pinned_dev, h->flag_dev, seq, extra, h->stream);
     check_launch();
-    const uint32_t* flag = h->flag_host;
-    for (uint64_t k = 1; __atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq; ++k) {
-        if ((k & 4095) != 0) continue;
-        const hipError_t e = hipStreamQuery(h->stream);
-        if (e == hipErrorNotReady) continue;
-        if (e != hipSuccess) throw AmgFailure{AMG_ERR_DEVICE, std::string("device error: ") + hipGetErrorString(e)};
-        if (__atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq)
-            throw AmgFailure{AMG_ERR_DEVICE, "scalar readback: the stream finished without publishing"};
-    }
+    await_published(h, seq);
     return h->pinned;
 }
+
 
 amg_status do_reintroduce(amg_ctx* h, int s, double gamma_min, int* first) {
     int ls = -1;
@@ -1079,6 +1246,96 @@ amg_status do_reintroduce(amg_ctx* h, int s, double gamma_min, int* first) {
     }
     sparsify_levels(h, todo);
     return AMG_OK;
+}
+
+// The solve of a system small enough for one launch (grid_kernels.hip): the
+// launch ends converged, broken down, out of iterations, or where an adaptive
+// window asks for a reintroduction, after which it is resumed.
+template <class T>
+amg_status grid_solve(amg_ctx* h, const GridPlan& g, const double* b, double* x, const amg_solve_params& p,
+                      amg_solve_info* info_out, double* hist) {
+    const int n = h->lv[0].n;
+    const DevMat& A = h->lv[0].A;
+    const double* out = h->grid_out;
+    amg_solve_info info{0, 0, 0, 0, 0.0, 0.0};
+    const bool check = h->check_singular;
+    double nr0 = 0.0, nws = 0.0, nrt = 0.0;
+    int status = kGridReintroduce;
+    bool first = true;
+    while (status == kGridReintroduce) {
+        bool any = false;
+        for (size_t l = 1; l < h->lv.size(); ++l) any = any || h->lv[l].gamma > 0.0;
+        GridArgs<T> a = grid_args<T>(h, g);
+        // the residual in the cycle's precision
+        if constexpr (sizeof(T) == 8) a.lv[0].b = h->cg_r;
+        else a.lv[0].b = h->cg_r32;
+        GridSolve s{};
+        s.A = GridOp<double>{A.rp, A.ci, A.v, A.rows, grid_lanes(A)};
+        s.b = b;
+        s.x = x;
+        s.r = h->cg_r;
+        s.p = h->cg_p;
+        s.p2 = h->rt;
+        s.q = h->cg_q;
+        s.xw = h->xw;
+        s.rt = h->cg_q;
+        s.part = h->grid_part;
+        s.out = h->grid_out_dev;
+        s.hist = h->grid_out_dev + kGridOutInts;
+        s.singular = check && first ? h->singular : nullptr;
+        s.done = h->flag_dev;
+        s.seq = ++h->pub_seq;
+        s.rtol = p.rtol;
+        s.rho_pow = std::pow(p.rho_max, (double)p.k);
+        s.nr0 = nr0;
+        s.nws = nws;
+        s.maxit = p.maxit;
+        s.adaptive = p.adaptive;
+        s.k = p.k;
+        s.any_gamma = any ? 1 : 0;
+        s.start = !first ? 2 : p.zero_guess ? 1 : 0;
+        s.iters = info.iters;
+        launch_grid_solve(a, s, g.lds, h->stream);
+        check_launch();
+        await_published(h, s.seq);
+        status = (int)out[kGridOutStatus];
+        if (status < 0) {
+            launch_fill_u32(kGridWgs + 2, h->grid_flags, 0u, h->stream);
+            throw AmgFailure{AMG_ERR_DEVICE, "the solve's workgroups did not meet in time"};
+        }
+        if (first && check) {
+            h->check_singular = false;
+            if (out[kGridOutSingular] != 0.0) throw AmgFailure{AMG_ERR_BAD_MATRIX, "coarsest operator is singular"};
+        }
+        info.iters = (int)out[kGridOutIters];
+        nr0 = out[kGridOutNorm0];
+        nws = out[kGridOutWindow];
+        nrt = out[kGridOutTrue];
+        first = false;
+        if (status == kGridReintroduce) {
+            const amg_status rs = do_reintroduce(h, p.s, p.gamma_min, nullptr);
+            if (rs < 0) {
+                status = kGridBreakdown;
+                break;
+            }
+            info.reintroductions++;
+            info.restarts++;
+            if (nrt > nws) {
+                launch_copy(n, x, h->xw, h->stream);
+                row_op(h, AMG_K_RESIDUAL, 0, kResidNorm, A, x, b, nullptr, h->cg_r, nullptr, S_NRT);
+                nrt = std::sqrt(read_scalars(h)[S_NRT]);
+            } else {
+                launch_copy(n, h->cg_r, s.rt, h->stream);
+            }
+            nws = nrt;
+        }
+    }
+    if (hist) std::copy(out + kGridOutInts, out + kGridOutInts + info.iters + 1, hist);
+    info.converged = status == kGridConverged ? 1 : 0;
+    info.relres = nr0 > 0.0 ? nrt / nr0 : 0.0;
+    info.rho_avg = (info.iters > 0 && info.relres > 0.0) ? std::pow(info.relres, 1.0 / info.iters) : 0.0;
+    if (info_out) *info_out = info;
+    return status == kGridConverged ? AMG_OK : status == kGridBreakdown ? AMG_ERR_BREAKDOWN : AMG_ERR_NOT_CONVERGED;
 }
 
 // z = V(r, 0) for CG, with r.z accumulated into dot_slot.  Mixed: the cycle
@@ -1108,6 +1365,13 @@ amg_status solve(amg_ctx* h, const double* b, double* x, const amg_solve_params&
     const int n = f.n;
     const DevMat& A = f.A;
     const bool pcg = p.method == AMG_PCG;
+    if (pcg && !gs_on(h) && !h->profiling && p.maxit > 0 && p.maxit < kGridHist) {
+        if (p.precision == 32) ensure_fp32(h);
+        const GridPlan g = p.precision == 32 ? grid_plan<float>(h, 0) : grid_plan<double>(h, 0);
+        if (g.first == 0)
+            return p.precision == 32 ? grid_solve<float>(h, g, b, x, p, info_out, hist)
+                                     : grid_solve<double>(h, g, b, x, p, info_out, hist);
+    }
     // FP32 V-cycle as the preconditioner (PCG) or as the correction of
     // iterative refinement (stationary); everything else stays FP64
     const bool mixed = p.precision == 32;
@@ -1264,6 +1528,8 @@ amg_status solve(amg_ctx* h, const double* b, double* x, const amg_solve_params&
             }
         }
     }
+    if (st == AMG_ERR_BREAKDOWN && grid_failed(h))
+        throw AmgFailure{AMG_ERR_DEVICE, "the cycle's workgroups did not meet in time"};
     double nrf = nrf_read;
     if (nrf < 0.0) {
         row_op(h, AMG_K_RESIDUAL, 0, kResidNorm, A, x, b, nullptr, r, nullptr, S_NRT);
@@ -2203,6 +2469,36 @@ void finish_setup(amg_ctx* h) {
         d.xt = dalloc_n<double>(h, d.n);
         d.r = dalloc_n<double>(h, d.n);
     }
+    // the levels a grid launch may take
+    h->grid_flags = dalloc_n<unsigned>(h, kGridWgs + 2);
+    h->grid_part = dalloc_n<double>(h, 4 * kGridWgs);
+    launch_fill_u32(kGridWgs + 2, h->grid_flags, 0u, h->stream);
+    {
+        std::vector<DevLevel*> small;
+        for (int l = 0; l < L; ++l)
+            if (h->lv[l].n <= kGridRows) small.push_back(&h->lv[l]);
+        if (!small.empty()) {
+            const int64_t words = 3 * (int64_t)small.size();
+            int32_t* most = dalloc_n<int32_t>(h, words);
+            launch_fill_u32(words, reinterpret_cast<unsigned*>(most), 0u, h->stream);
+            for (size_t k = 0; k < small.size(); ++k) {
+                DevLevel& d = *small[k];
+                d.gwin = dalloc_n<int32_t>(h, kWinInts * kGridWgs);
+                launch_grid_windows(d.n, d.R.rows, d.A.rp, d.A.ci, d.R.rp, d.R.ci, d.P.rp, d.P.ci, d.gwin, most + 3 * k,
+                                    h->stream);
+            }
+            check_launch();
+            std::vector<int32_t> top(words);
+            download(h, top.data(), most, words);
+            sync(h);
+            dfree(h, most);
+            for (size_t k = 0; k < small.size(); ++k) {
+                small[k]->gspan = top[3 * k];
+                small[k]->gagain = top[3 * k + 1];
+                small[k]->gshare = top[3 * k + 2];
+            }
+        }
+    }
     // sparsified-operator widths are chosen per build; partial buffers cover
     // every width for the largest level
     partial_need = std::max(partial_need, max_row_launch_blocks());
@@ -2219,6 +2515,11 @@ void finish_setup(amg_ctx* h) {
     *h->flag_host = 0;
     HIP_CHECK(hipHostGetDevicePointer((void**)&h->pinned_dev, h->pinned, 0));
     h->flag_dev = reinterpret_cast<uint32_t*>(h->pinned_dev + S_COUNT + 1);
+    if (h->lv[0].gwin) {
+        HIP_CHECK(hipHostMalloc((void**)&h->grid_out, sizeof(double) * (kGridOutInts + kGridHist),
+                                hipHostMallocCoherent | hipHostMallocMapped));
+        HIP_CHECK(hipHostGetDevicePointer((void**)&h->grid_out_dev, h->grid_out, 0));
+    }
     sync(h);
     refresh_coarse_inverse(h);
     h->prof.assign((size_t)AMG_K_NUM * h->lv.size(), ProfAcc{});
@@ -2641,6 +2942,7 @@ void destroy(amg_ctx* h) {
     (void)hipStreamSynchronize(h->stream);
     if (h->batch) destroy_batch(h->batch);
     for (auto& d : h->lv) {
+        dfree(h, d.gwin);
         free_mat(h, d.Ahs);
         free_mat(h, d.A);
         free_mat(h, d.P);
@@ -2670,8 +2972,10 @@ void destroy(amg_ctx* h) {
     for (void* q : {(void*)h->bcg_r, (void*)h->bcg_p, (void*)h->bcg_q, (void*)h->bcg_z}) dfree(h, q);
     for (void* p : {(void*)h->coarse_inv, (void*)h->scal, (void*)h->partials,
                     (void*)h->scan_scratch, (void*)h->cnt, (void*)h->sp_cnt, (void*)h->sp_bsum, (void*)h->missing, (void*)h->singular, (void*)h->cg_r,
-                    (void*)h->cg_z, (void*)h->cg_p, (void*)h->cg_q, (void*)h->xw, (void*)h->rt})
+                    (void*)h->cg_z, (void*)h->cg_p, (void*)h->cg_q, (void*)h->xw, (void*)h->rt, (void*)h->grid_flags})
         dfree(h, p);
+    dfree(h, h->grid_part);
+    if (h->grid_out) (void)hipHostFree(h->grid_out);
     if (h->pinned) (void)hipHostFree(h->pinned);
     for (auto& pe : h->pending) {
         (void)hipEventDestroy(pe.start);
