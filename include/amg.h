@@ -153,10 +153,11 @@ amg_status amg_setup_nongalerkin_from_csr(int64_t n, const int32_t* row_ptr, con
                        beat every undecided strong neighbour (larger weight,
                        ties to the smaller index) become C, then undecided
                        points depending strongly on a C point become F.
-   The products are formed as listed terms sorted stably by (row, column),
-   so each entry sums its terms in the canonical order of the host setup.
-   Temporary device memory of up to ~40 bytes per product term comes from the
-   allocator.  Other arguments and the result as for amg_setup_from_csr. */
+   The products are formed row by row, or, where rows are long, as listed
+   terms sorted stably by (row, column); either way each entry sums its terms
+   in the canonical order of the host setup.  Temporary device memory of up to
+   ~40 bytes per product term comes from the allocator.  Other arguments and
+   the result as for amg_setup_from_csr. */
 enum { AMG_COARSEN_RS = 0, AMG_COARSEN_PMIS = 1 };
 amg_status amg_setup_device(int64_t n, int64_t nnz, const int32_t* row_ptr, const int32_t* col,
                             const double* val, const amg_setup_params* params, int32_t coarsening,
@@ -170,8 +171,9 @@ amg_status amg_setup_device(int64_t n, int64_t nnz, const int32_t* row_ptr, cons
    launch; a sort of m (key, value) pairs counts 32 m, one read and one write
    of each pair).  Enabling resets the totals; enable = 0 stops timing.
    Classes AMG_SK_*: strength pattern, C/F split, interpolation (numbering
-   and P), transpose (R = P^T without its sort), term listing of the
-   products, sorts, combination of sorted terms into CSR, symmetrization. */
+   and P), transpose (R = P^T without its sort), counting of the products'
+   terms (and listing, where they are sorted), sorts, the products' rows
+   (formed in place or from sorted terms), symmetrization. */
 enum {
     AMG_SK_STRENGTH = 0, AMG_SK_SPLIT = 1, AMG_SK_INTERP = 2, AMG_SK_TRANSPOSE = 3,
     AMG_SK_EXPAND = 4, AMG_SK_SORT = 5, AMG_SK_COMBINE = 6, AMG_SK_SYMMETRIZE = 7, AMG_SK_NUM = 8

@@ -15,8 +15,10 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstring>
+#include <initializer_list>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -2415,6 +2417,19 @@ void set_compact_indices(amg_ctx* h, bool on) {
 // everything a hierarchy needs once its levels hold A, P, R, c_points and
 // the split: 1/diag, work vectors, reduction and scan buffers, the coarsest
 // inverse
+// the words the host reads without a copy
+void ensure_published(amg_ctx* h) {
+    if (h->pinned) return;
+    // the scalar slots, then the readback's sequence word, host-coherent so
+    // that the device's writes reach the host without a copy
+    HIP_CHECK(hipHostMalloc((void**)&h->pinned, sizeof(double) * (S_COUNT + 1) + 64,
+                            hipHostMallocCoherent | hipHostMallocMapped));
+    h->flag_host = reinterpret_cast<uint32_t*>(h->pinned + S_COUNT + 1);
+    *h->flag_host = 0;
+    HIP_CHECK(hipHostGetDevicePointer((void**)&h->pinned_dev, h->pinned, 0));
+    h->flag_dev = reinterpret_cast<uint32_t*>(h->pinned_dev + S_COUNT + 1);
+}
+
 void finish_setup(amg_ctx* h) {
     const int L = (int)h->lv.size() - 1;
     const int64_t n = h->lv[0].n;
@@ -2507,14 +2522,7 @@ void finish_setup(amg_ctx* h) {
     h->scal = dalloc_n<double>(h, S_COUNT);
     launch_fill_f64(S_COUNT, h->scal, 0.0, h->stream);
     check_launch();
-    // the scalar slots, then the readback's sequence word, host-coherent so
-    // that the device's writes reach the host without a copy
-    HIP_CHECK(hipHostMalloc((void**)&h->pinned, sizeof(double) * (S_COUNT + 1) + 64,
-                            hipHostMallocCoherent | hipHostMallocMapped));
-    h->flag_host = reinterpret_cast<uint32_t*>(h->pinned + S_COUNT + 1);
-    *h->flag_host = 0;
-    HIP_CHECK(hipHostGetDevicePointer((void**)&h->pinned_dev, h->pinned, 0));
-    h->flag_dev = reinterpret_cast<uint32_t*>(h->pinned_dev + S_COUNT + 1);
+    ensure_published(h);
     if (h->lv[0].gwin) {
         HIP_CHECK(hipHostMalloc((void**)&h->grid_out, sizeof(double) * (kGridOutInts + kGridHist),
                                 hipHostMallocCoherent | hipHostMallocMapped));
@@ -2710,17 +2718,132 @@ DevMat combine_terms(amg_ctx* h, SetupTemps& t, SetupTimer& tm, uint64_t* keys[2
     return out;
 }
 
+// Reads up to four device words once the stream reaches this point (the same
+// wait as read_scalars: no copy, no stream synchronization).
+struct Word {
+    const void* p;
+    int bytes;
+    Word(const int32_t* q) : p(q), bytes(4) {}
+    Word(const int64_t* q) : p(q), bytes(8) {}
+};
+std::array<int64_t, 4> read_words(amg_ctx* h, std::initializer_list<Word> words) {
+    PublishWords w{};
+    for (const Word& x : words) {
+        w.src[w.count] = x.p;
+        w.bytes[w.count++] = x.bytes;
+    }
+    const uint32_t seq = ++h->pub_seq;
+    launch_publish_words(w, reinterpret_cast<int64_t*>(h->pinned_dev), h->flag_dev, seq, h->stream);
+    check_launch();
+    await_published(h, seq);
+    std::array<int64_t, 4> v{};
+    std::memcpy(v.data(), h->pinned, sizeof(int64_t) * w.count);
+    return v;
+}
+
+// A matrix whose row i is the len[i] entries from off[i] on.
+struct LooseMat {
+    int64_t *off = nullptr, *len = nullptr;   // rows + 1 entries, the last length 0
+    int32_t* ci = nullptr;
+    double* v = nullptr;
+};
+
+void release_loose(SetupTemps& t, LooseMat& m) {
+    for (void* q : {(void*)m.off, (void*)m.len, (void*)m.ci, (void*)m.v}) t.release(q);
+    m = LooseMat{};
+}
+
+// One product X Y of the Galerkin step, its rows loose: first the terms of
+// every row (count), then the rows (form).  Rows of more terms than the row
+// kernels take, or of more columns than their tables, are the sorted form's.
+struct RowProduct {
+    amg_ctx* h;
+    SetupTemps& t;
+    SetupTimer& tm;
+    ProductArgs a{};
+    int cols = 0;
+    int64_t xnnz = 0;
+    LooseMat out;
+    int32_t* most = nullptr;     // the largest row's terms, then the lengths of the row kernels' lists
+    RowProduct(amg_ctx* hh, SetupTemps& tt, SetupTimer& ttm) : h(hh), t(tt), tm(ttm) {}
+    void left(const DevMat& x, int ncols) {
+        a.rows = x.rows;
+        a.xrp = x.rp;
+        a.xci = x.ci;
+        a.xv = x.v;
+        xnnz = x.nnz;
+        cols = ncols;
+    }
+    void right(const DevMat& y) {
+        a.yrp = y.rp;
+        a.yci = y.ci;
+        a.yv = y.v;
+    }
+    void right(const LooseMat& y) {
+        a.yoff = y.off;
+        a.ylen = y.len;
+        a.yci = y.ci;
+        a.yv = y.v;
+    }
+    void count() {
+        out.off = t.get<int64_t>(a.rows + 1);
+        out.len = t.get<int64_t>(a.rows + 1);
+        most = t.get<int32_t>(3);
+        tm.begin(AMG_SK_EXPAND, 4.0 * xnnz + 8.0 * a.rows + 8.0 * a.rows + 16.0 * a.rows);
+        launch_fill_u32(3, reinterpret_cast<unsigned*>(most), 0u, h->stream);
+        launch_product_terms(a, out.len, most, h->stream);
+        scan_int64(h, t, out.len, out.off, a.rows);
+        tm.end();
+    }
+    const int64_t* terms() const { return out.off + a.rows; }
+    const int32_t* failed() const { return most + 2; }
+    // m terms, the largest row's `top`; true: the row kernels ran (*failed()
+    // says whether all rows are there)
+    bool form(int64_t m, int64_t top) {
+        a.off = out.off;
+        if (top > kProductRowTerms || (double)m > kProductMeanTerms * a.rows) {
+            sorted(m);
+            return false;
+        }
+        out.ci = t.get<int32_t>(m);
+        out.v = t.get<double>(m);
+        a.olen = out.len;
+        a.oci = out.ci;
+        a.ov = out.v;
+        int32_t* list = t.get<int32_t>(2 * (int64_t)a.rows);
+        tm.begin(AMG_SK_COMBINE, 12.0 * xnnz + 4.0 * a.rows + 16.0 * a.rows + 12.0 * m);
+        launch_row_product(a, (double)m / (double)std::max<int64_t>(xnnz, 1), (double)m / a.rows, list, most + 1,
+                           h->stream);
+        tm.end();
+        check_launch();
+        t.release(list);
+        return true;
+    }
+    // the same through sorted terms
+    void sorted(int64_t m) {
+        for (void* q : {(void*)out.ci, (void*)out.v})
+            if (q) t.release(q);
+        const int cb = bits_for(cols);
+        uint64_t* keys[2] = {t.get<uint64_t>(m + 1), t.get<uint64_t>(m + 1)};
+        double* vals[2] = {t.get<double>(m + 1), t.get<double>(m + 1)};
+        tm.begin(AMG_SK_EXPAND, 12.0 * xnnz + 4.0 * a.rows + 8.0 * a.rows + 12.0 * m + 16.0 * m);
+        launch_expand_terms(a, cb, keys[0], vals[0], h->stream);
+        tm.end();
+        check_launch();
+        DevMat c = combine_terms(h, t, tm, keys, vals, m, a.rows, cols, cb, bits_for(a.rows) + cb);
+        for (void* q : {(void*)keys[0], (void*)keys[1], (void*)vals[0], (void*)vals[1]}) t.release(q);
+        launch_loose_rows(a.rows, c.rp, out.off, out.len, h->stream);
+        check_launch();
+        t.release(c.rp);
+        out.ci = c.ci;
+        out.v = c.v;
+    }
+};
+
 void claim_mat(SetupTemps& t, const DevMat& m) {
     t.claim(m.rp);
     t.claim(m.ci);
     t.claim(m.v);
-}
-
-void release_mat(SetupTemps& t, DevMat& m) {
-    t.release(m.rp);
-    t.release(m.ci);
-    t.release(m.v);
-    m = DevMat{};
 }
 
 // coarsening: AMG_COARSEN_RS (the first pass on the host, from the strength
@@ -2729,6 +2852,7 @@ void release_mat(SetupTemps& t, DevMat& m) {
 void setup_device(amg_ctx* h, int64_t n, int64_t nnz, const int32_t* row_ptr, const int32_t* col,
                   const double* val, int coarsening, uint64_t seed) {
     hipStream_t st = h->stream;
+    ensure_published(h);
     SetupTemps t(h);
     SetupTimer tm(st);
     int* err = t.get<int>(2);
@@ -2736,7 +2860,7 @@ void setup_device(amg_ctx* h, int64_t n, int64_t nnz, const int32_t* row_ptr, co
     upload(h, err, err_init, 2);
     launch_validate_csr((int)n, nnz, row_ptr, col, val, err, st);
     check_launch();
-    check_setup_error(h, err);
+    if (read_words(h, {err})[0]) check_setup_error(h, err);
 
     h->lv.clear();
     h->lv.emplace_back();
@@ -2759,19 +2883,13 @@ void setup_device(amg_ctx* h, int64_t n, int64_t nnz, const int32_t* row_ptr, co
         const DevMat A = h->lv[l].A;
         const double anz = (double)A.nnz, np1 = (double)nl + 1;
         const size_t level_mark = t.mark();
-        // strength pattern and lambda
-        int32_t* cnt = t.get<int32_t>(nl + 1);
-        int32_t* srp = t.get<int32_t>(nl + 1);
-        tm.begin(AMG_SK_STRENGTH, 12 * anz + 4 * np1 + 4.0 * nl + 8 * np1);
-        launch_strength_count(nl, A.rp, A.ci, A.v, h->sp.theta, cnt, st);
-        launch_exclusive_scan(nl, cnt, srp, scan_tmp, st);
-        tm.end();
-        const int32_t snnz = read_scalar(h, srp + nl);
-        int32_t* sci = t.get<int32_t>(snnz);
+        // strength pattern (row i's from A.rp[i] on) and lambda
+        int32_t* scnt = t.get<int32_t>(nl + 1);
+        int32_t* sci = t.get<int32_t>(A.nnz);
         int32_t* lam = t.get<int32_t>(nl);
-        tm.begin(AMG_SK_STRENGTH, 12 * anz + 8 * np1 + 8.0 * snnz + 8.0 * nl);
+        tm.begin(AMG_SK_STRENGTH, 16 * anz + 4 * np1 + 8.0 * nl);
         launch_fill_u32(nl, reinterpret_cast<unsigned*>(lam), 0u, st);
-        launch_strength_fill(nl, A.rp, A.ci, A.v, h->sp.theta, srp, sci, lam, st);
+        launch_strength(nl, A.nnz, A.rp, A.ci, A.v, h->sp.theta, scnt, sci, lam, st);
         tm.end();
         // C/F split
         int32_t* state = t.get<int32_t>(nl);
@@ -2782,72 +2900,114 @@ void setup_device(amg_ctx* h, int64_t n, int64_t nnz, const int32_t* row_ptr, co
             tm.begin(AMG_SK_SPLIT, 4.0 * nl + 16.0 * nl);
             launch_pmis_init(nl, lam, seed + (uint64_t)l, w, state, mark, st);
             tm.end();
-            // every round decides at least the undecided point of largest weight
+            // Every round decides at least the undecided point of largest
+            // weight.  Stencils take 4 to 7 rounds, and a round with nothing
+            // left costs two empty launches (8 us) where a look at the count
+            // costs 12: the first look comes after four rounds, then one after
+            // every second.
+            int look = 4;
             for (int round = 1;; ++round) {
-                if (round > nl + 1) throw AmgFailure{AMG_ERR_DEVICE, "PMIS rounds did not finish"};
-                tm.begin(AMG_SK_SPLIT, 2 * (4.0 * snnz + 4 * np1) + 36.0 * nl);
-                launch_pmis_round(nl, srp, sci, w, state, mark, round, left, st);
+                if (round > nl + 1 + look) throw AmgFailure{AMG_ERR_DEVICE, "PMIS rounds did not finish"};
+                tm.begin(AMG_SK_SPLIT, 2 * (4.0 * anz + 4 * np1) + 28.0 * nl);
+                launch_pmis_round(nl, A.rp, scnt, sci, w, state, mark, round, left, st);
                 tm.end();
-                check_launch();
-                if (read_scalar(h, left) == 0) break;
+                if (round < look) continue;
+                if (read_words(h, {left})[0] == 0) break;
+                look += 2;
             }
         } else {
             tm.begin(AMG_SK_SPLIT, 0.0);
+            std::vector<int32_t> ptr(nl + 1), cnt(nl), cols(A.nnz);
+            download(h, ptr.data(), A.rp, nl + 1);
+            download(h, cnt.data(), scnt, nl);
+            download(h, cols.data(), sci, A.nnz);
+            sync(h);
             HostCsr s;
             s.rows = s.cols = nl;
             s.ptr.resize(nl + 1);
-            s.idx.resize(snnz);
-            download(h, s.ptr.data(), srp, nl + 1);
-            download(h, s.idx.data(), sci, snnz);
-            sync(h);
+            int64_t k = 0;
+            for (int i = 0; i < nl; ++i) {
+                s.ptr[i] = k;
+                for (int q = 0; q < cnt[i]; ++q) cols[k++] = cols[ptr[i] + q];
+            }
+            s.ptr[nl] = k;
+            cols.resize(k);
+            s.idx = std::move(cols);
             const std::vector<int32_t> split = ruge_stueben_split(s);
             upload(h, state, split.data(), nl);
             tm.end();
             sync(h);   // the host copy goes out of scope
         }
-        // coarse numbering
+        // coarse numbering and the rows of P
+        int32_t* flag = t.get<int32_t>(nl + 1);
+        int32_t* pcnt = t.get<int32_t>(nl + 1);
         int32_t* cidx = t.get<int32_t>(nl + 1);
-        tm.begin(AMG_SK_INTERP, 8.0 * nl + 8 * np1);
-        launch_c_flags(nl, state, cnt, st);
-        launch_exclusive_scan(nl, cnt, cidx, scan_tmp, st);
+        DevMat P;
+        P.rows = nl;
+        P.rp = t.get<int32_t>(nl + 1);
+        tm.begin(AMG_SK_INTERP, 4.0 * anz + 8 * np1 + 8.0 * nl + 24 * np1);
+        launch_split_counts(nl, A.rp, scnt, sci, state, flag, pcnt, st);
+        launch_exclusive_scan(nl, flag, cidx, scan_tmp, st);
+        launch_exclusive_scan(nl, pcnt, P.rp, scan_tmp, st);
         tm.end();
-        const int32_t nc = read_scalar(h, cidx + nl);
+        const auto sizes = read_words(h, {cidx + nl, P.rp + nl, err});
+        if (sizes[2]) check_setup_error(h, err);
+        const int32_t nc = (int32_t)sizes[0], pnnz = (int32_t)sizes[1];
         if (nc == 0 || nc == nl) {
             t.rewind(level_mark);
             break;
         }
-        {
-            std::vector<int32_t> cf(nl);
-            download(h, cf.data(), state, nl);
-            sync(h);
-            for (auto& c : cf) c = c == kPtC;
-            h->lv[l].split = std::move(cf);
-        }
+        P.cols = nc;
         h->lv[l].nc = nc;
         h->lv[l].c_points = dalloc_n<int32_t>(h, nc);
         // direct interpolation
-        DevMat P;
-        P.rows = nl;
-        P.cols = nc;
-        P.rp = t.get<int32_t>(nl + 1);
-        tm.begin(AMG_SK_INTERP, 4.0 * snnz + 4 * np1 + 8.0 * nl + 4 * nc + 4 * np1);
-        launch_c_points(nl, state, cidx, h->lv[l].c_points, st);
-        launch_interp_count(nl, srp, sci, state, cnt, st);
-        launch_exclusive_scan(nl, cnt, P.rp, scan_tmp, st);
-        tm.end();
-        const int32_t pnnz = read_scalar(h, P.rp + nl);
         P.ci = t.get<int32_t>(pnnz + kCsrPad);
         P.v = t.get<double>(pnnz + kCsrPad);
         set_shape(P, pnnz);
-        tm.begin(AMG_SK_INTERP, 12 * anz + 4 * np1 + 4.0 * snnz + 4 * np1 + 8.0 * nl + 12.0 * pnnz);
-        launch_interp_fill(nl, A.rp, A.ci, A.v, srp, sci, state, cidx, P.rp, P.ci, P.v, st);
+        int32_t* code = t.get<int32_t>(nl);
+        tm.begin(AMG_SK_INTERP, 16 * anz + 8 * np1 + 16.0 * nl + 4.0 * nc + 12.0 * pnnz);
+        launch_c_points(nl, state, cidx, h->lv[l].c_points, code, st);
+        launch_interp_fill(nl, A.nnz, A.rp, A.ci, A.v, h->sp.theta, code, P.rp, P.ci, P.v, st);
         tm.end();
         check_launch();
         claim_mat(t, P);
         h->lv[l].P = P;
-        const int rb = bits_for(nl), cb = bits_for(nc);
-        // R = P^T: the entries of P sorted by (column, row)
-        {
+        // R = P^T: the places of P's entries in their columns, and T = A P: its terms
+        int32_t* ccnt = t.get<int32_t>(nc + 2);   // and the longest column
+        int32_t* place = t.get<int32_t>(pnnz);
+        DevMat R;
+        R.rows = nc;
+        R.cols = nl;
+        R.rp = dalloc_n<int32_t>(h, nc + 1);
+        h->lv[l].R = R;
+        R.ci = dalloc_n<int32_t>(h, pnnz + kCsrPad);
+        h->lv[l].R = R;
+        R.v = dalloc_n<double>(h, pnnz + kCsrPad);
+        set_shape(R, pnnz);
+        h->lv[l].R = R;
+        tm.begin(AMG_SK_TRANSPOSE, 8.0 * pnnz + 8.0 * nc + 8.0 * nc);
+        launch_fill_u32(nc + 2, reinterpret_cast<unsigned*>(ccnt), 0u, st);
+        launch_column_places(pnnz, P.ci, ccnt, place, ccnt + nc + 1, st);
+        launch_exclusive_scan(nc, ccnt, R.rp, scan_tmp, st);
+        tm.end();
+        RowProduct T(h, t, tm);
+        T.left(A, nc);
+        T.right(P);
+        T.count();
+        const auto tsz = read_words(h, {T.terms(), T.most, ccnt + nc + 1});
+        if (tsz[2] <= kOrderedRow) {
+            int32_t* uci = t.get<int32_t>(pnnz);
+            double* uv = t.get<double>(pnnz);
+            tm.begin(AMG_SK_TRANSPOSE, 28.0 * pnnz + 4 * np1 + 4.0 * nc + 24.0 * pnnz);
+            launch_column_fill(nl, P.rp, P.ci, P.v, place, R.rp, uci, uv, st);
+            launch_order_rows(nc, R.rp, uci, uv, R.ci, R.v, st);
+            tm.end();
+            check_launch();
+            t.release(uci);
+            t.release(uv);
+        } else {
+            // the entries sorted by (column, row)
+            const int rb = bits_for(nl), cb = bits_for(nc);
             uint64_t* keys[2] = {t.get<uint64_t>(pnnz + 1), t.get<uint64_t>(pnnz + 1)};
             double* vals[2] = {t.get<double>(pnnz + 1), t.get<double>(pnnz + 1)};
             tm.begin(AMG_SK_TRANSPOSE, 12.0 * pnnz + 4 * np1 + 16.0 * pnnz);
@@ -2860,74 +3020,59 @@ void setup_device(amg_ctx* h, int64_t n, int64_t nnz, const int32_t* row_ptr, co
             tm.begin(AMG_SK_SORT, 32.0 * pnnz);
             HIP_CHECK(sort_pairs(tmp, bytes, keys, vals, pnnz, rb + cb, res, st));
             tm.end();
-            DevMat R;
-            R.rows = nc;
-            R.cols = nl;
-            R.rp = dalloc_n<int32_t>(h, nc + 1);
-            R.ci = dalloc_n<int32_t>(h, pnnz + kCsrPad);
-            R.v = dalloc_n<double>(h, pnnz + kCsrPad);
-            set_shape(R, pnnz);
-            h->lv[l].R = R;
-            tm.begin(AMG_SK_TRANSPOSE, 16.0 * pnnz + 12.0 * pnnz + 8.0 * pnnz + 4.0 * (nc + 1));
+            tm.begin(AMG_SK_TRANSPOSE, 16.0 * pnnz + 12.0 * pnnz);
             launch_unpack_keys(pnnz, keys[res], vals[res], rb, R.ci, R.v, st);
-            launch_rowptr_from_keys(pnnz, keys[res], rb, nc, R.rp, st);
             tm.end();
             check_launch();
             for (void* q : {(void*)tmp, (void*)keys[0], (void*)keys[1], (void*)vals[0], (void*)vals[1]})
                 t.release(q);
         }
-        // T = A P
-        int64_t* cnt64 = t.get<int64_t>(nl + 1);
-        int64_t* off = t.get<int64_t>(nl + 1);
-        tm.begin(AMG_SK_EXPAND, 4 * np1 + 4 * anz + 4 * np1 + 8 * np1 + 16 * np1);
-        launch_ap_count(nl, A.rp, A.ci, P.rp, cnt64, st);
-        scan_int64(h, t, cnt64, off, nl);
-        tm.end();
-        int64_t m = read_scalar(h, off + nl);
-        DevMat T;
-        {
-            uint64_t* keys[2] = {t.get<uint64_t>(m + 1), t.get<uint64_t>(m + 1)};
-            double* vals[2] = {t.get<double>(m + 1), t.get<double>(m + 1)};
-            tm.begin(AMG_SK_EXPAND, 12 * anz + 4 * np1 + 12.0 * pnnz + 4 * np1 + 8 * np1 + 16.0 * m);
-            launch_ap_expand(nl, A.rp, A.ci, A.v, P.rp, P.ci, P.v, off, cb, keys[0], vals[0], st);
-            tm.end();
-            check_launch();
-            T = combine_terms(h, t, tm, keys, vals, m, nl, nc, cb, rb + cb);
-            for (void* q : {(void*)keys[0], (void*)keys[1], (void*)vals[0], (void*)vals[1]}) t.release(q);
+        t.release(place);
+        bool open = T.form(tsz[0], tsz[1]);   // all rows not known to be there
+        // C = P^T T, terms of each (I, J) in ascending fine row
+        RowProduct C(h, t, tm);
+        C.left(R, nc);
+        C.right(T.out);
+        C.count();
+        auto csz = read_words(h, {C.terms(), C.most, T.failed()});
+        if (open && csz[2] > 0) {
+            T.sorted(tsz[0]);
+            release_loose(t, C.out);
+            C.right(T.out);
+            C.count();
+            csz = read_words(h, {C.terms(), C.most});
         }
-        // C = P^T T, terms of each (I, J) listed in ascending fine row
-        tm.begin(AMG_SK_EXPAND, 8 * np1 + 8 * np1 + 16 * np1);
-        launch_pt_count(nl, P.rp, T.rp, cnt64, st);
-        scan_int64(h, t, cnt64, off, nl);
+        open = C.form(csz[0], csz[1]);
+        int64_t* start = t.get<int64_t>(nc + 1);
+        tm.begin(AMG_SK_COMBINE, 24.0 * nc);
+        scan_int64(h, t, C.out.len, start, nc);
         tm.end();
-        m = read_scalar(h, off + nl);
-        DevMat C;
-        {
-            uint64_t* keys[2] = {t.get<uint64_t>(m + 1), t.get<uint64_t>(m + 1)};
-            double* vals[2] = {t.get<double>(m + 1), t.get<double>(m + 1)};
-            tm.begin(AMG_SK_EXPAND, 12.0 * pnnz + 4 * np1 + 12.0 * T.nnz + 4 * np1 + 8 * np1 + 16.0 * m);
-            launch_pt_expand(nl, P.rp, P.ci, P.v, T.rp, T.ci, T.v, off, cb, keys[0], vals[0], st);
-            tm.end();
-            check_launch();
-            release_mat(t, T);
-            C = combine_terms(h, t, tm, keys, vals, m, nc, nc, cb, 2 * cb);
-            for (void* q : {(void*)keys[0], (void*)keys[1], (void*)vals[0], (void*)vals[1]}) t.release(q);
+        auto nsz = read_words(h, {start + nc, C.failed()});
+        if (open && nsz[1] > 0) {
+            C.sorted(csz[0]);
+            scan_int64(h, t, C.out.len, start, nc);
+            nsz = read_words(h, {start + nc});
         }
+        release_loose(t, T.out);   // (the sorted form reads it again)
+        if (nsz[0] > INT32_MAX) throw AmgFailure{AMG_ERR_INVALID_ARG, "coarse operator exceeds int32 nonzeros"};
         // A_{l+1} = (C + C^T) / 2
-        double* sym = t.get<double>(C.nnz + kCsrPad);
-        tm.begin(AMG_SK_SYMMETRIZE, 12.0 * C.nnz + 4.0 * (nc + 1) + 8.0 * C.nnz);
-        launch_symmetrize(nc, C.rp, C.ci, C.v, sym, err, st);
+        DevMat Ac;
+        Ac.rows = Ac.cols = nc;
+        Ac.rp = t.get<int32_t>(nc + 1);
+        Ac.ci = t.get<int32_t>(nsz[0] + kCsrPad);
+        Ac.v = t.get<double>(nsz[0] + kCsrPad);
+        set_shape(Ac, nsz[0]);
+        tm.begin(AMG_SK_SYMMETRIZE, 24.0 * Ac.nnz + 12.0 * Ac.nnz + 28.0 * nc);
+        launch_pack_symmetrized(nc, C.out.off, C.out.len, C.out.ci, C.out.v, start, Ac.rp, Ac.ci, Ac.v, err, st);
         tm.end();
         check_launch();
-        check_setup_error(h, err);
-        t.release(C.v);
-        C.v = sym;
-        claim_mat(t, C);
+        claim_mat(t, Ac);
         t.rewind(level_mark);
         h->lv.emplace_back();
-        h->lv.back().A = C;
+        h->lv.back().A = Ac;
         h->lv.back().n = nc;
     }
+    if (read_words(h, {err})[0]) check_setup_error(h, err);
     t.rewind(0);
     tm.collect();
     if (h->lv.back().n > kMaxDenseCoarse)
@@ -3638,8 +3783,19 @@ amg_status amg_export_vector(amg_handle h, int32_t l, int32_t which, double* out
 amg_status amg_export_split(amg_handle h, int32_t l, int32_t* cf) {
     if (!h || h->lv.empty()) return AMG_ERR_STATE;
     if (l < 0 || l >= (int)h->lv.size() - 1 || !cf) return AMG_ERR_INVALID_ARG;
-    std::memcpy(cf, h->lv[l].split.data(), sizeof(int32_t) * h->lv[l].split.size());
-    return AMG_OK;
+    const DevLevel& d = h->lv[l];
+    if (!d.split.empty()) {
+        std::memcpy(cf, d.split.data(), sizeof(int32_t) * d.split.size());
+        return AMG_OK;
+    }
+    return guarded(h, [&] {
+        std::vector<int32_t> c(d.nc);
+        download(h, c.data(), d.c_points, d.nc);
+        sync(h);
+        std::fill(cf, cf + d.n, 0);
+        for (int32_t i : c) cf[i] = 1;
+        return AMG_OK;
+    });
 }
 
 amg_status amg_profile_enable(amg_handle h, int32_t enable, int32_t kernel_class, int32_t level) {

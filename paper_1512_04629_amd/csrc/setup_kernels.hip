@@ -4,6 +4,8 @@
 // hierarchy is bitwise the host one (for the same C/F split).
 #include "setup_kernels.hpp"
 
+#include "row_common.hpp"
+
 #include <algorithm>
 #include <climits>
 
@@ -18,11 +20,12 @@ constexpr int kSB = 256;
 
 int grid_of(int64_t n) {
     const int64_t b = (n + kSB - 1) / kSB;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(b, 16384));
+    return round_up8((int)std::max<int64_t>(1, std::min<int64_t>(b, 16384)));
 }
 
-#define GRID_STRIDE(i, n)                                                               \
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)(n); \
+// neighbouring rows on one die: they gather from each other
+#define GRID_STRIDE(i, n)                                                                       \
+    for (int64_t i = (int64_t)xcd_logical_block() * blockDim.x + threadIdx.x; i < (int64_t)(n); \
          i += (int64_t)gridDim.x * blockDim.x)
 
 __device__ inline int64_t find_col(const int32_t* ci, int64_t b, int64_t e, int col) {
@@ -40,18 +43,23 @@ __device__ inline int64_t find_col(const int32_t* ci, int64_t b, int64_t e, int 
 // strictly ascending columns, finite values, positive stored diagonal,
 // bitwise symmetry (a_ji stored with the same bits as a_ij)
 // ---------------------------------------------------------------------------
+// Eight lanes a row, so that neighbouring lanes read neighbouring entries
+// (lognormal FV 120^3: 208 -> 145 us).
+constexpr int kRowLanes = 8;
+
 __global__ void validate_kernel(int n, int64_t nnz, const int32_t* __restrict__ rp,
                                 const int32_t* __restrict__ ci, const double* __restrict__ v,
                                 int* __restrict__ err) {
-    GRID_STRIDE(ii, n) {
-        const int i = (int)ii;
+    const int lane = threadIdx.x % kRowLanes;
+    GRID_STRIDE(t, (int64_t)n * kRowLanes) {
+        const int i = (int)(t / kRowLanes);
         int bits = 0;
         const int64_t b = rp[i], e = rp[i + 1];
         if ((i == 0 && b != 0) || (i == n - 1 && e != nnz) || b < 0 || e < b || e > nnz) {
             bits = kErrRowPtr;
         } else {
-            bool diag = false;
-            for (int64_t p = b; p < e; ++p) {
+            int diag = 0;
+            for (int64_t p = b + lane; p < e; p += kRowLanes) {
                 const int j = ci[p];
                 if (j < 0 || j >= n) {
                     bits |= kErrColRange;
@@ -61,7 +69,7 @@ __global__ void validate_kernel(int n, int64_t nnz, const int32_t* __restrict__ 
                 const double a = v[p];
                 if (!isfinite(a)) bits |= kErrNonFinite;
                 if (j == i) {
-                    diag = true;
+                    diag = 1;
                     if (!(a > 0.0)) bits |= kErrDiagSign;
                 }
                 const int64_t jb = rp[j], je = rp[j + 1];
@@ -69,6 +77,8 @@ __global__ void validate_kernel(int n, int64_t nnz, const int32_t* __restrict__ 
                 const int64_t q = find_col(ci, jb, je, i);
                 if (q < 0 || __double_as_longlong(v[q]) != __double_as_longlong(a)) bits |= kErrAsymmetric;
             }
+#pragma unroll
+            for (int o = kRowLanes / 2; o > 0; o >>= 1) diag |= __shfl_xor(diag, o, kRowLanes);
             if (!diag) bits |= kErrNoDiag;
         }
         if (bits) {
@@ -76,6 +86,29 @@ __global__ void validate_kernel(int n, int64_t nnz, const int32_t* __restrict__ 
             atomicMin(&err[1], i);
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// A wave takes 64 rows, one a lane, whose entries it first brings into LDS with
+// coalesced loads: a lane's walk through its row then costs LDS latency, not a
+// cache line a step.  Rows that do not fit are walked in memory.  Lognormal FV
+// 120^3, the second level (530,000 rows of 18), us: strength 465 + 507 in two
+// walks with a scan and a readback between -> 104 in one, whose lists start where
+// the rows of A do; interpolation 429 -> 111.
+// ---------------------------------------------------------------------------
+constexpr int kWaveRows = 64;
+
+// rows a wave takes (fewer, if long, so that they fit) and the entries it has
+// room for
+struct Staging {
+    int rows, cap;
+};
+Staging staging(int n, int64_t nnz) {
+    const int64_t mean = n > 0 ? (nnz + n - 1) / n : 1;
+    Staging s{kWaveRows, 0};
+    while (s.rows > 4 && s.rows * (mean + mean / 4) > 2048) s.rows /= 2;
+    s.cap = (int)std::min<int64_t>(4096, std::max<int64_t>(256, s.rows * (mean + mean / 4 + 1)));
+    return s;
 }
 
 // ---------------------------------------------------------------------------
@@ -94,36 +127,50 @@ __device__ inline bool strength_threshold(int i, int64_t b, int64_t e, const int
     return big > 0.0;
 }
 
-__global__ void strength_count_kernel(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                                      const double* __restrict__ v, double theta, int32_t* __restrict__ cnt) {
-    GRID_STRIDE(ii, n) {
-        const int i = (int)ii;
-        const int64_t b = rp[i], e = rp[i + 1];
+// the strong columns of row i, ascending, from sci[rp[i]] on (their number in
+// cnt[i]), and lambda
+__global__ __launch_bounds__(kWaveRows) void strength_kernel(int n, const int32_t* __restrict__ rp,
+                                                             const int32_t* __restrict__ ci,
+                                                             const double* __restrict__ v, double theta, Staging sg,
+                                                             int32_t* __restrict__ cnt, int32_t* __restrict__ sci,
+                                                             int32_t* __restrict__ lam) {
+    extern __shared__ __align__(16) char lds[];
+    double* lv = reinterpret_cast<double*>(lds);
+    int32_t* lc = reinterpret_cast<int32_t*>(lv + sg.cap);
+    const int r0 = xcd_logical_block() * sg.rows, r1 = min(n, r0 + sg.rows);
+    if (r0 >= n) return;
+    const int64_t base = rp[r0];
+    const int total = (int)min<int64_t>(rp[r1] - base, INT_MAX);
+    const int i = r0 + (int)threadIdx.x;
+    const bool have = i < r1;
+    const int64_t b = have ? rp[i] : 0, e = have ? rp[i + 1] : 0;
+    // columns c and values w of the row, its list written to out
+    auto row = [&](int64_t lo, int64_t hi, auto* c, auto* w, auto* out) {
         double thr;
-        int c = 0;
-        if (strength_threshold(i, b, e, ci, v, theta, thr))
-            for (int64_t p = b; p < e; ++p) c += (ci[p] != i && -v[p] >= thr);
-        cnt[i] = c;
-    }
-}
-
-__global__ void strength_fill_kernel(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                                     const double* __restrict__ v, double theta, const int32_t* __restrict__ srp,
-                                     int32_t* __restrict__ sci, int32_t* __restrict__ lam) {
-    GRID_STRIDE(ii, n) {
-        const int i = (int)ii;
-        const int64_t b = rp[i], e = rp[i + 1];
-        double thr;
-        if (!strength_threshold(i, b, e, ci, v, theta, thr)) continue;
-        int64_t w = srp[i];
-        for (int64_t p = b; p < e; ++p) {
-            const int j = ci[p];
-            if (j != i && -v[p] >= thr) {
-                sci[w++] = j;
-                atomicAdd(&lam[j], 1);
+        int k = 0;
+        if (strength_threshold(i, lo, hi, c, w, theta, thr))
+            for (int64_t p = lo; p < hi; ++p) {
+                const int j = c[p];
+                if (j != i && -w[p] >= thr) {
+                    out[lo + k++] = j;
+                    atomicAdd(&lam[j], 1);
+                }
             }
-        }
+        if (have) cnt[i] = k;
+    };
+    if (total > sg.cap) {
+        row(b, e, ci, v, sci);
+        return;
     }
+#pragma unroll 4
+    for (int q = threadIdx.x; q < total; q += kWaveRows) {
+        lc[q] = ci[base + q];
+        lv[q] = v[base + q];
+    }
+    __syncthreads();
+    row(b - base, e - base, lc, lv, lc);   // in place: a list is no longer than its row
+    __syncthreads();
+    for (int q = threadIdx.x; q < total; q += kWaveRows) sci[base + q] = lc[q];
 }
 
 // ---------------------------------------------------------------------------
@@ -152,14 +199,16 @@ __global__ void pmis_init_kernel(int n, const int32_t* __restrict__ lam, uint64_
 __device__ inline bool beats(const double* w, int i, int j) { return w[i] > w[j] || (w[i] == w[j] && i < j); }
 
 // every strong edge j -> k between undecided points marks its loser
-__global__ void pmis_mark_kernel(int n, const int32_t* __restrict__ srp, const int32_t* __restrict__ sci,
-                                 const double* __restrict__ w, const int32_t* __restrict__ state,
-                                 int32_t* __restrict__ mark, int round, int32_t* __restrict__ undecided) {
+__global__ void pmis_mark_kernel(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ cnt,
+                                 const int32_t* __restrict__ sci, const double* __restrict__ w,
+                                 const int32_t* __restrict__ state, int32_t* __restrict__ mark, int round,
+                                 int32_t* __restrict__ undecided) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *undecided = 0;
     GRID_STRIDE(jj, n) {
         const int j = (int)jj;
         if (state[j] != kPtUndecided) continue;
-        for (int64_t p = srp[j]; p < srp[j + 1]; ++p) {
+        const int64_t b = rp[j], e = b + cnt[j];
+        for (int64_t p = b; p < e; ++p) {
             const int k = sci[p];
             if (state[k] != kPtUndecided) continue;
             if (beats(w, j, k)) mark[k] = round;
@@ -168,35 +217,70 @@ __global__ void pmis_mark_kernel(int n, const int32_t* __restrict__ srp, const i
     }
 }
 
-__global__ void pmis_select_kernel(int n, int32_t* __restrict__ state, const int32_t* __restrict__ mark,
-                                   int round) {
-    GRID_STRIDE(i, n) {
-        if (state[i] == kPtUndecided && mark[i] != round) state[i] = kPtC;
-    }
-}
-
-// undecided points that depend strongly on a C point become F; the rest are
-// counted.  Only U -> F changes happen here, so the C tests are race free.
-__global__ void pmis_fmark_kernel(int n, const int32_t* __restrict__ srp, const int32_t* __restrict__ sci,
-                                  int32_t* state, int32_t* __restrict__ undecided) {
+// undecided points without a mark of this round become C; those that depend
+// strongly on a C point F; the rest are counted.  A point is C, whether its
+// state says so yet or not, if it was undecided without a mark or C before, so
+// what its neighbours find does not depend on the order of the threads.
+__global__ __launch_bounds__(kSB) void pmis_decide_kernel(int n, const int32_t* __restrict__ rp,
+                                                          const int32_t* __restrict__ cnt,
+                                                          const int32_t* __restrict__ sci, int32_t* state,
+                                                          const int32_t* __restrict__ mark, int round,
+                                                          int32_t* __restrict__ undecided) {
+    __shared__ int left[kSB / 64];
+    int open = 0;
     GRID_STRIDE(jj, n) {
         const int j = (int)jj;
         if (state[j] != kPtUndecided) continue;
+        if (mark[j] != round) {
+            state[j] = kPtC;
+            continue;
+        }
         bool to_f = false;
-        for (int64_t p = srp[j]; p < srp[j + 1] && !to_f; ++p) to_f = state[sci[p]] == kPtC;
+        const int64_t b = rp[j], e = b + cnt[j];
+        for (int64_t p = b; p < e && !to_f; ++p) {
+            const int k = sci[p];
+            const int sk = state[k];
+            to_f = sk == kPtC || (sk == kPtUndecided && mark[k] != round);
+        }
         if (to_f) state[j] = kPtF;
-        else atomicAdd(undecided, 1);
+        else ++open;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) open += __shfl_xor(open, o, 64);
+    if ((threadIdx.x & 63) == 0) left[threadIdx.x >> 6] = open;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < kSB / 64; ++q) open += left[q];
+        if (open) atomicAdd(undecided, open);
     }
 }
 
-__global__ void c_flags_kernel(int n, const int32_t* __restrict__ state, int32_t* __restrict__ cnt) {
-    GRID_STRIDE(i, n) cnt[i] = state[i] == kPtC;
+// a C point's flag, and the entries of each row of P: a C point's one, an F
+// point's strong C neighbours
+__global__ void split_counts_kernel(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ cnt,
+                                    const int32_t* __restrict__ sci, const int32_t* __restrict__ state,
+                                    int32_t* __restrict__ flag, int32_t* __restrict__ pcnt) {
+    GRID_STRIDE(ii, n) {
+        const int i = (int)ii;
+        const bool c = state[i] == kPtC;
+        flag[i] = c;
+        int k = 1;
+        if (!c) {
+            k = 0;
+            const int64_t b = rp[i], e = b + cnt[i];
+            for (int64_t p = b; p < e; ++p) k += state[sci[p]] == kPtC;
+        }
+        pcnt[i] = k;
+    }
 }
 
+// the C points in order; code[i]: point i's coarse number, -1 for F points
 __global__ void c_points_kernel(int n, const int32_t* __restrict__ state, const int32_t* __restrict__ cidx,
-                                int32_t* __restrict__ c_points) {
+                                int32_t* __restrict__ c_points, int32_t* __restrict__ code) {
     GRID_STRIDE(i, n) {
-        if (state[i] == kPtC) c_points[cidx[i]] = (int32_t)i;
+        const bool c = state[i] == kPtC;
+        code[i] = c ? cidx[i] : -1;
+        if (c) c_points[cidx[i]] = (int32_t)i;
     }
 }
 
@@ -206,67 +290,78 @@ __global__ void c_points_kernel(int n, const int32_t* __restrict__ state, const 
 // off-diagonals) / (sum of a_ij over strong C neighbours), d = a_ii + (sum
 // of positive off-diagonals), every sum in ascending column order
 // ---------------------------------------------------------------------------
-__global__ void interp_count_kernel(int n, const int32_t* __restrict__ srp, const int32_t* __restrict__ sci,
-                                    const int32_t* __restrict__ state, int32_t* __restrict__ cnt) {
-    GRID_STRIDE(ii, n) {
-        const int i = (int)ii;
-        if (state[i] == kPtC) {
-            cnt[i] = 1;
-            continue;
-        }
-        int c = 0;
-        for (int64_t p = srp[i]; p < srp[i + 1]; ++p) c += state[sci[p]] == kPtC;
-        cnt[i] = c;
-    }
-}
-
-__global__ void interp_fill_kernel(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                                   const double* __restrict__ v, const int32_t* __restrict__ srp,
-                                   const int32_t* __restrict__ sci, const int32_t* __restrict__ state,
-                                   const int32_t* __restrict__ cidx, const int32_t* __restrict__ prp,
-                                   int32_t* __restrict__ pci, double* __restrict__ pv) {
-    GRID_STRIDE(ii, n) {
-        const int i = (int)ii;
-        int64_t w = prp[i];
-        if (state[i] == kPtC) {
-            pci[w] = cidx[i];
+__global__ __launch_bounds__(kWaveRows) void interp_fill_kernel(int n, const int32_t* __restrict__ rp,
+                                                                const int32_t* __restrict__ ci,
+                                                                const double* __restrict__ v, double theta, Staging sg,
+                                                                const int32_t* __restrict__ code,
+                                                                const int32_t* __restrict__ prp,
+                                                                int32_t* __restrict__ pci, double* __restrict__ pv) {
+    extern __shared__ __align__(16) char lds[];
+    double* lv = reinterpret_cast<double*>(lds);
+    int32_t* lc = reinterpret_cast<int32_t*>(lv + sg.cap);
+    int32_t* lk = lc + sg.cap;
+    const int r0 = xcd_logical_block() * sg.rows, r1 = min(n, r0 + sg.rows);
+    if (r0 >= n) return;
+    const int64_t base = rp[r0];
+    const int total = (int)min<int64_t>(rp[r1] - base, INT_MAX);
+    const int i = r0 + (int)threadIdx.x;
+    const bool have = i < r1;
+    const int64_t b = have ? rp[i] : 0, e = have ? rp[i + 1] : 0;
+    int64_t w = have ? prp[i] : 0;
+    const bool any = have && prp[i + 1] != w;
+    const int mine = have ? code[i] : -1;
+    // columns c, values x, and code_at(p) the code of entry p's column
+    auto row = [&](int64_t lo, int64_t hi, auto* c, auto* x, auto code_at) {
+        if (!any) return;
+        if (mine >= 0) {
+            pci[w] = mine;
             pv[w] = 1.0;
-            continue;
+            return;
         }
-        if (prp[i + 1] == w) continue;
-        const int64_t b = rp[i], e = rp[i + 1];
+        double thr;
+        (void)strength_threshold(i, lo, hi, c, x, theta, thr);
         double dsum = 0.0;
-        for (int64_t p = b; p < e; ++p)
-            if (ci[p] == i) dsum = v[p];
+        for (int64_t p = lo; p < hi; ++p)
+            if (c[p] == i) dsum = x[p];
         double neg = 0.0, strong_c = 0.0;
-        for (int64_t p = b; p < e; ++p) {
-            if (ci[p] == i) continue;
-            const double x = v[p];
-            if (x < 0.0) neg = neg + x;
-            else if (x > 0.0) dsum = dsum + x;
-        }
-        int64_t q = b;
-        for (int64_t s = srp[i]; s < srp[i + 1]; ++s) {
-            const int j = sci[s];
-            while (ci[q] < j) ++q;
-            if (state[j] == kPtC) strong_c = strong_c + v[q];
+        for (int64_t p = lo; p < hi; ++p) {
+            if (c[p] == i) continue;
+            const double t = x[p];
+            if (t < 0.0) neg = neg + t;
+            else if (t > 0.0) dsum = dsum + t;
+            if (-t >= thr && code_at(p) >= 0) strong_c = strong_c + t;
         }
         const double alpha = neg / strong_c;
-        q = b;
-        for (int64_t s = srp[i]; s < srp[i + 1]; ++s) {
-            const int j = sci[s];
-            while (ci[q] < j) ++q;
-            if (state[j] != kPtC) continue;
-            const double t = alpha * v[q];
-            pci[w] = cidx[j];
-            pv[w] = -t / dsum;
+        for (int64_t p = lo; p < hi; ++p) {
+            const double t = x[p];
+            if (c[p] == i || !(-t >= thr)) continue;
+            const int k = code_at(p);
+            if (k < 0) continue;
+            const double s = alpha * t;
+            pci[w] = k;
+            pv[w] = -s / dsum;
             ++w;
         }
+    };
+    if (total > sg.cap) {
+        row(b, e, ci, v, [&](int64_t p) { return code[ci[p]]; });
+        return;
     }
+#pragma unroll 4
+    for (int q = threadIdx.x; q < total; q += kWaveRows) {
+        const int j = ci[base + q];
+        lc[q] = j;
+        lv[q] = v[base + q];
+        lk[q] = code[j];
+    }
+    __syncthreads();
+    row(b - base, e - base, lc, lv, [&](int64_t p) { return lk[p]; });
 }
 
 // ---------------------------------------------------------------------------
-// transposes and products through sorted keys (row << col_bits | col)
+// transposes and products through sorted keys (row << col_bits | col): the
+// general form, for products with rows and transposes with columns too long for
+// the row kernels
 // ---------------------------------------------------------------------------
 __global__ void transpose_keys_kernel(int rows, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
                                       const double* __restrict__ v, int row_bits, uint64_t* __restrict__ keys,
@@ -280,69 +375,33 @@ __global__ void transpose_keys_kernel(int rows, const int32_t* __restrict__ rp, 
     }
 }
 
-// cnt has n + 1 entries; the last is 0 so that the exclusive scan ends on
-// the total
-__global__ void ap_count_kernel(int n, const int32_t* __restrict__ arp, const int32_t* __restrict__ aci,
-                                const int32_t* __restrict__ prp, int64_t* __restrict__ cnt) {
-    GRID_STRIDE(kk, (int64_t)n + 1) {
+// the terms of X Y: row i lists, for each l of X's row in ascending order,
+// x_il y_lJ over Y's row l
+template <bool LOOSE>
+__global__ void expand_terms_kernel(ProductArgs a, int col_bits, uint64_t* __restrict__ keys,
+                                    double* __restrict__ vals) {
+    GRID_STRIDE(kk, a.rows) {
         const int k = (int)kk;
-        int64_t c = 0;
-        if (k < n)
-            for (int64_t p = arp[k]; p < arp[k + 1]; ++p) c += prp[aci[p] + 1] - prp[aci[p]];
-        cnt[k] = c;
-    }
-}
-
-// T = A P: row k lists, for each l of A's row in ascending order, the terms
-// a_kl p_lJ over P's row l
-__global__ void ap_expand_kernel(int n, const int32_t* __restrict__ arp, const int32_t* __restrict__ aci,
-                                 const double* __restrict__ av, const int32_t* __restrict__ prp,
-                                 const int32_t* __restrict__ pci, const double* __restrict__ pv,
-                                 const int64_t* __restrict__ off, int col_bits, uint64_t* __restrict__ keys,
-                                 double* __restrict__ vals) {
-    GRID_STRIDE(kk, n) {
-        const int k = (int)kk;
-        int64_t o = off[k];
+        int64_t o = a.off[k];
         const uint64_t row = (uint64_t)(uint32_t)k << col_bits;
-        for (int64_t p = arp[k]; p < arp[k + 1]; ++p) {
-            const int l = aci[p];
-            const double a = av[p];
-            for (int64_t q = prp[l]; q < prp[l + 1]; ++q) {
-                keys[o] = row | (uint64_t)(uint32_t)pci[q];
-                vals[o] = a * pv[q];
+        for (int64_t p = a.xrp[k]; p < a.xrp[k + 1]; ++p) {
+            const int l = a.xci[p];
+            const double x = a.xv[p];
+            const int64_t b = LOOSE ? a.yoff[l] : a.yrp[l], e = LOOSE ? b + a.ylen[l] : a.yrp[l + 1];
+            for (int64_t q = b; q < e; ++q) {
+                keys[o] = row | (uint64_t)(uint32_t)a.yci[q];
+                vals[o] = x * a.yv[q];
                 ++o;
             }
         }
     }
 }
 
-__global__ void pt_count_kernel(int n, const int32_t* __restrict__ prp, const int32_t* __restrict__ trp,
-                                int64_t* __restrict__ cnt) {
-    GRID_STRIDE(kk, (int64_t)n + 1) {
-        const int k = (int)kk;
-        cnt[k] = k < n ? (int64_t)(prp[k + 1] - prp[k]) * (int64_t)(trp[k + 1] - trp[k]) : 0;
-    }
-}
-
-// C = P^T T: fine row k gives the terms p_kI t_kJ; listing the fine rows in
-// ascending order makes the terms of each (I, J) ascend in k
-__global__ void pt_expand_kernel(int n, const int32_t* __restrict__ prp, const int32_t* __restrict__ pci,
-                                 const double* __restrict__ pv, const int32_t* __restrict__ trp,
-                                 const int32_t* __restrict__ tci, const double* __restrict__ tv,
-                                 const int64_t* __restrict__ off, int col_bits, uint64_t* __restrict__ keys,
-                                 double* __restrict__ vals) {
-    GRID_STRIDE(kk, n) {
-        const int k = (int)kk;
-        int64_t o = off[k];
-        for (int64_t p = prp[k]; p < prp[k + 1]; ++p) {
-            const uint64_t row = (uint64_t)(uint32_t)pci[p] << col_bits;
-            const double x = pv[p];
-            for (int64_t q = trp[k]; q < trp[k + 1]; ++q) {
-                keys[o] = row | (uint64_t)(uint32_t)tci[q];
-                vals[o] = x * tv[q];
-                ++o;
-            }
-        }
+__global__ void loose_rows_kernel(int rows, const int32_t* __restrict__ rp, int64_t* __restrict__ off,
+                                  int64_t* __restrict__ len) {
+    GRID_STRIDE(i, (int64_t)rows + 1) {
+        off[i] = rp[i];
+        len[i] = i < rows ? rp[i + 1] - rp[i] : 0;
     }
 }
 
@@ -391,39 +450,28 @@ __global__ void unpack_keys_kernel(int64_t m, const uint64_t* __restrict__ keys,
     }
 }
 
-__global__ void symmetrize_kernel(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                                  const double* __restrict__ v, double* __restrict__ out, int* __restrict__ err) {
-    GRID_STRIDE(ii, n) {
-        const int i = (int)ii;
-        for (int64_t p = rp[i]; p < rp[i + 1]; ++p) {
-            const int j = ci[p];
-            const int64_t q = find_col(ci, rp[j], rp[j + 1], i);
-            if (q < 0) {
-                atomicOr(err, (int)kErrPattern);
-                out[p] = v[p];
-                continue;
-            }
-            out[p] = 0.5 * (v[p] + v[q]);
-        }
-    }
+__global__ void publish_words_kernel(PublishWords w, int64_t* host, uint32_t* flag, uint32_t seq) {
+    const int t = threadIdx.x;
+    if (t < w.count)
+        host[t] = w.bytes[t] == 8 ? *static_cast<const int64_t*>(w.src[t])
+                                  : (int64_t) * static_cast<const int32_t*>(w.src[t]);
+    __threadfence_system();
+    __syncthreads();
+    if (t == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 }  // namespace
 
 void launch_validate_csr(int n, int64_t nnz, const int32_t* rp, const int32_t* ci, const double* v, int* err,
                          hipStream_t st) {
-    hipLaunchKernelGGL(validate_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, nnz, rp, ci, v, err);
+    hipLaunchKernelGGL(validate_kernel, dim3(grid_of((int64_t)n * kRowLanes)), dim3(kSB), 0, st, n, nnz, rp, ci, v, err);
 }
 
-void launch_strength_count(int n, const int32_t* rp, const int32_t* ci, const double* v, double theta,
-                           int32_t* cnt, hipStream_t st) {
-    hipLaunchKernelGGL(strength_count_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, rp, ci, v, theta, cnt);
-}
-
-void launch_strength_fill(int n, const int32_t* rp, const int32_t* ci, const double* v, double theta,
-                          const int32_t* srp, int32_t* sci, int32_t* lam, hipStream_t st) {
-    hipLaunchKernelGGL(strength_fill_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, rp, ci, v, theta, srp, sci,
-                       lam);
+void launch_strength(int n, int64_t nnz, const int32_t* rp, const int32_t* ci, const double* v, double theta,
+                     int32_t* cnt, int32_t* sci, int32_t* lam, hipStream_t st) {
+    const Staging sg = staging(n, nnz);
+    hipLaunchKernelGGL(strength_kernel, dim3(round_up8((n + sg.rows - 1) / sg.rows)), dim3(kWaveRows), (size_t)sg.cap * 12, st, n,
+                       rp, ci, v, theta, sg, cnt, sci, lam);
 }
 
 void launch_pmis_init(int n, const int32_t* lam, uint64_t seed, double* w, int32_t* state, int32_t* mark,
@@ -431,32 +479,29 @@ void launch_pmis_init(int n, const int32_t* lam, uint64_t seed, double* w, int32
     hipLaunchKernelGGL(pmis_init_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, lam, seed, w, state, mark);
 }
 
-void launch_pmis_round(int n, const int32_t* srp, const int32_t* sci, const double* w, int32_t* state,
-                       int32_t* mark, int round, int32_t* undecided, hipStream_t st) {
-    hipLaunchKernelGGL(pmis_mark_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, srp, sci, w, state, mark, round,
+void launch_pmis_round(int n, const int32_t* rp, const int32_t* cnt, const int32_t* sci, const double* w,
+                       int32_t* state, int32_t* mark, int round, int32_t* undecided, hipStream_t st) {
+    hipLaunchKernelGGL(pmis_mark_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, rp, cnt, sci, w, state, mark, round,
                        undecided);
-    hipLaunchKernelGGL(pmis_select_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, state, mark, round);
-    hipLaunchKernelGGL(pmis_fmark_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, srp, sci, state, undecided);
+    hipLaunchKernelGGL(pmis_decide_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, rp, cnt, sci, state, mark, round,
+                       undecided);
 }
 
-void launch_c_flags(int n, const int32_t* state, int32_t* cnt, hipStream_t st) {
-    hipLaunchKernelGGL(c_flags_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, state, cnt);
+void launch_split_counts(int n, const int32_t* rp, const int32_t* cnt, const int32_t* sci, const int32_t* state,
+                         int32_t* flag, int32_t* pcnt, hipStream_t st) {
+    hipLaunchKernelGGL(split_counts_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, rp, cnt, sci, state, flag, pcnt);
 }
 
-void launch_c_points(int n, const int32_t* state, const int32_t* cidx, int32_t* c_points, hipStream_t st) {
-    hipLaunchKernelGGL(c_points_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, state, cidx, c_points);
+void launch_c_points(int n, const int32_t* state, const int32_t* cidx, int32_t* c_points, int32_t* code,
+                     hipStream_t st) {
+    hipLaunchKernelGGL(c_points_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, state, cidx, c_points, code);
 }
 
-void launch_interp_count(int n, const int32_t* srp, const int32_t* sci, const int32_t* state, int32_t* cnt,
-                         hipStream_t st) {
-    hipLaunchKernelGGL(interp_count_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, srp, sci, state, cnt);
-}
-
-void launch_interp_fill(int n, const int32_t* rp, const int32_t* ci, const double* v, const int32_t* srp,
-                        const int32_t* sci, const int32_t* state, const int32_t* cidx, const int32_t* prp,
-                        int32_t* pci, double* pv, hipStream_t st) {
-    hipLaunchKernelGGL(interp_fill_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, rp, ci, v, srp, sci, state, cidx,
-                       prp, pci, pv);
+void launch_interp_fill(int n, int64_t nnz, const int32_t* rp, const int32_t* ci, const double* v, double theta,
+                        const int32_t* code, const int32_t* prp, int32_t* pci, double* pv, hipStream_t st) {
+    const Staging sg = staging(n, nnz);
+    hipLaunchKernelGGL(interp_fill_kernel, dim3(round_up8((n + sg.rows - 1) / sg.rows)), dim3(kWaveRows), (size_t)sg.cap * 16, st,
+                       n, rp, ci, v, theta, sg, code, prp, pci, pv);
 }
 
 void launch_transpose_keys(int rows, const int32_t* rp, const int32_t* ci, const double* v, int row_bits,
@@ -465,27 +510,15 @@ void launch_transpose_keys(int rows, const int32_t* rp, const int32_t* ci, const
                        keys, vals);
 }
 
-void launch_ap_count(int n, const int32_t* arp, const int32_t* aci, const int32_t* prp, int64_t* cnt,
-                     hipStream_t st) {
-    hipLaunchKernelGGL(ap_count_kernel, dim3(grid_of((int64_t)n + 1)), dim3(kSB), 0, st, n, arp, aci, prp, cnt);
+void launch_expand_terms(const ProductArgs& a, int col_bits, uint64_t* keys, double* vals, hipStream_t st) {
+    if (a.yrp)
+        hipLaunchKernelGGL(expand_terms_kernel<false>, dim3(grid_of(a.rows)), dim3(kSB), 0, st, a, col_bits, keys, vals);
+    else
+        hipLaunchKernelGGL(expand_terms_kernel<true>, dim3(grid_of(a.rows)), dim3(kSB), 0, st, a, col_bits, keys, vals);
 }
 
-void launch_ap_expand(int n, const int32_t* arp, const int32_t* aci, const double* av, const int32_t* prp,
-                      const int32_t* pci, const double* pv, const int64_t* off, int col_bits, uint64_t* keys,
-                      double* vals, hipStream_t st) {
-    hipLaunchKernelGGL(ap_expand_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, arp, aci, av, prp, pci, pv, off,
-                       col_bits, keys, vals);
-}
-
-void launch_pt_count(int n, const int32_t* prp, const int32_t* trp, int64_t* cnt, hipStream_t st) {
-    hipLaunchKernelGGL(pt_count_kernel, dim3(grid_of((int64_t)n + 1)), dim3(kSB), 0, st, n, prp, trp, cnt);
-}
-
-void launch_pt_expand(int n, const int32_t* prp, const int32_t* pci, const double* pv, const int32_t* trp,
-                      const int32_t* tci, const double* tv, const int64_t* off, int col_bits, uint64_t* keys,
-                      double* vals, hipStream_t st) {
-    hipLaunchKernelGGL(pt_expand_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, prp, pci, pv, trp, tci, tv, off,
-                       col_bits, keys, vals);
+void launch_loose_rows(int rows, const int32_t* rp, int64_t* off, int64_t* len, hipStream_t st) {
+    hipLaunchKernelGGL(loose_rows_kernel, dim3(grid_of((int64_t)rows + 1)), dim3(kSB), 0, st, rows, rp, off, len);
 }
 
 void launch_run_heads(int64_t m, const uint64_t* keys, int64_t* flags, hipStream_t st) {
@@ -509,9 +542,8 @@ void launch_unpack_keys(int64_t m, const uint64_t* keys, const double* vals, int
     hipLaunchKernelGGL(unpack_keys_kernel, dim3(grid_of(m)), dim3(kSB), 0, st, m, keys, vals, col_bits, ci, v);
 }
 
-void launch_symmetrize(int n, const int32_t* rp, const int32_t* ci, const double* v, double* out, int* err,
-                       hipStream_t st) {
-    hipLaunchKernelGGL(symmetrize_kernel, dim3(grid_of(n)), dim3(kSB), 0, st, n, rp, ci, v, out, err);
+void launch_publish_words(const PublishWords& w, int64_t* host, uint32_t* flag, uint32_t seq, hipStream_t st) {
+    hipLaunchKernelGGL(publish_words_kernel, dim3(1), dim3(64), 0, st, w, host, flag, seq);
 }
 
 namespace {

@@ -2,10 +2,10 @@
 // C/F split -> interpolation -> Galerkin product) for gfx950.
 //
 // Every step reproduces the host setup's arithmetic bit for bit: per-row
-// sums run in ascending column order in one thread, and the Galerkin
-// products are formed as expand -> stable sort by (row, column) -> ordered
-// sums, so each entry's terms are added in the canonical order (ascending
-// inner index, first term assigned).  The C/F split is either the
+// sums run in ascending column order in one thread, and each entry of the
+// Galerkin products adds its terms in the canonical order (ascending inner
+// index, first term assigned), whether row by row in LDS or listed, sorted
+// stably by (row, column) and summed.  The C/F split is either the
 // Ruge-Stueben first pass (computed elsewhere) or PMIS, the parallel
 // aggressive coarsening Section 1 cites, in rounds on the device.
 #pragma once
@@ -36,13 +36,11 @@ enum SetupError : int {
 void launch_validate_csr(int n, int64_t nnz, const int32_t* rp, const int32_t* ci, const double* v,
                          int* err, hipStream_t st);
 
-// strength (negative couplings, -a_ij >= fl(theta max_{k!=i}(-a_ik))): strong
-// counts per row, then the pattern and lambda_j = #{i : S_ij} (lam zeroed by
-// the caller)
-void launch_strength_count(int n, const int32_t* rp, const int32_t* ci, const double* v, double theta,
-                           int32_t* cnt, hipStream_t st);
-void launch_strength_fill(int n, const int32_t* rp, const int32_t* ci, const double* v, double theta,
-                          const int32_t* srp, int32_t* sci, int32_t* lam, hipStream_t st);
+// strength (negative couplings, -a_ij >= fl(theta max_{k!=i}(-a_ik))): the
+// strong columns of row i from sci[rp[i]] on, their number cnt[i], and
+// lambda_j = #{i : S_ij} (lam zeroed by the caller)
+void launch_strength(int n, int64_t nnz, const int32_t* rp, const int32_t* ci, const double* v, double theta,
+                     int32_t* cnt, int32_t* sci, int32_t* lam, hipStream_t st);
 
 // PMIS: weights w_i = lambda_i + u_i with u_i the top 53 bits of output i+1
 // of the SplitMix64 stream `seed`; lambda_i = 0 points start as F
@@ -50,37 +48,85 @@ void launch_pmis_init(int n, const int32_t* lam, uint64_t seed, double* w, int32
                       hipStream_t st);
 // one round: local maxima among undecided points become C, then undecided
 // points depending strongly on a C point become F; *undecided receives the
-// number left
-void launch_pmis_round(int n, const int32_t* srp, const int32_t* sci, const double* w, int32_t* state,
-                       int32_t* mark, int round, int32_t* undecided, hipStream_t st);
+// number left (a round without undecided points changes nothing)
+void launch_pmis_round(int n, const int32_t* rp, const int32_t* cnt, const int32_t* sci, const double* w,
+                       int32_t* state, int32_t* mark, int round, int32_t* undecided, hipStream_t st);
 
-// cnt[i] = 1 for C points; after the scan cidx, c_points[cidx[i]] = i
-void launch_c_flags(int n, const int32_t* state, int32_t* cnt, hipStream_t st);
-void launch_c_points(int n, const int32_t* state, const int32_t* cidx, int32_t* c_points, hipStream_t st);
+// flag[i] = 1 for C points, pcnt[i] the entries of P's row i; after the scans
+// c_points[cidx[i]] = i, code[i] = cidx[i] for C points and -1 for F points
+void launch_split_counts(int n, const int32_t* rp, const int32_t* cnt, const int32_t* sci, const int32_t* state,
+                         int32_t* flag, int32_t* pcnt, hipStream_t st);
+void launch_c_points(int n, const int32_t* state, const int32_t* cidx, int32_t* c_points, int32_t* code,
+                     hipStream_t st);
 
-// direct interpolation: row sizes, then entries
-void launch_interp_count(int n, const int32_t* srp, const int32_t* sci, const int32_t* state, int32_t* cnt,
-                         hipStream_t st);
-void launch_interp_fill(int n, const int32_t* rp, const int32_t* ci, const double* v, const int32_t* srp,
-                        const int32_t* sci, const int32_t* state, const int32_t* cidx, const int32_t* prp,
-                        int32_t* pci, double* pv, hipStream_t st);
+// direct interpolation: the entries of P
+void launch_interp_fill(int n, int64_t nnz, const int32_t* rp, const int32_t* ci, const double* v, double theta,
+                        const int32_t* code, const int32_t* prp, int32_t* pci, double* pv, hipStream_t st);
 
+// ---- products and transposes row by row (product_kernels.hip) --------------
+// out = X Y: X in CSR, Y in CSR (yrp) or loose rows (row l from yoff[l] on,
+// ylen[l] entries); out's rows loose, row i from off[i] on
+struct ProductArgs {
+    int rows;
+    const int32_t *xrp, *xci;
+    const double* xv;
+    const int32_t* yrp;
+    const int64_t *yoff, *ylen;
+    const int32_t* yci;
+    const double* yv;
+    const int64_t* off;
+    int32_t* oci;
+    double* ov;
+    int64_t* olen;
+};
+// The row kernels take products whose largest row has at most kProductRowTerms
+// terms (the steps of a row follow each other, about 0.4 us each) and whose mean
+// row kProductMeanTerms: beyond, most rows have more columns than a table holds.
+// Sorted, the terms of all rows go in parallel.
+constexpr int kProductRowTerms = 8192;
+constexpr double kProductMeanTerms = 1024.0;
+// most entries of a row of a transpose that is ordered by rank (each entry is
+// compared with all)
+constexpr int kOrderedRow = 2048;
+// terms[i] of every row (terms[rows] = 0), the largest raised in *most
+void launch_product_terms(const ProductArgs& a, int64_t* terms, int32_t* most, hipStream_t st);
+// mean_row: mean length of the rows of Y that are read; mean_terms: of the
+// product's rows; list: 2 rows entries; counts[0..1] zero on entry, counts[1] >
+// 0 on exit: rows with more columns than a table holds, whose result is missing
+void launch_row_product(const ProductArgs& a, double mean_row, double mean_terms, int32_t* list, int32_t* counts,
+                        hipStream_t st);
+// (c_ij + c_ji) / 2 of loose rows in CSR (start: scanned lengths); err |=
+// kErrPattern where (j,i) is missing
+void launch_pack_symmetrized(int n, const int64_t* off, const int64_t* len, const int32_t* lci, const double* lv,
+                             const int64_t* start, int32_t* rp, int32_t* ci, double* v, int* err, hipStream_t st);
+// transpose: places of the entries in their columns (cnt zeroed by the caller,
+// the largest count raised in *most), the entries at their places, the rows in
+// ascending order
+void launch_column_places(int64_t nnz, const int32_t* ci, int32_t* cnt, int32_t* place, int32_t* most, hipStream_t st);
+void launch_column_fill(int rows, const int32_t* rp, const int32_t* ci, const double* v, const int32_t* place,
+                        const int32_t* trp, int32_t* tci, double* tv, hipStream_t st);
+void launch_order_rows(int rows, const int32_t* rp, const int32_t* uci, const double* uv, int32_t* ci, double* v,
+                       hipStream_t st);
+
+// values of up to four device words (int32 or int64 each), then a sequence
+// number, to host-coherent memory
+struct PublishWords {
+    const void* src[4];
+    int bytes[4];
+    int count;
+};
+void launch_publish_words(const PublishWords& w, int64_t* host, uint32_t* flag, uint32_t seq, hipStream_t st);
+
+// ---- the same through sorted terms: rows of any length ----------------------
 // keys (column << row_bits | row) of every entry of a CSR matrix, with values
 void launch_transpose_keys(int rows, const int32_t* rp, const int32_t* ci, const double* v, int row_bits,
                            uint64_t* keys, double* vals, hipStream_t st);
 
-// products of a Galerkin step, per row of the left factor:
-//   AP: row k of A times P (count = sum over A's row of P's row sizes)
-//   PT: fine row k contributes P[k,I] * T[k,J] to (I,J)
-void launch_ap_count(int n, const int32_t* arp, const int32_t* aci, const int32_t* prp, int64_t* cnt,
-                     hipStream_t st);
-void launch_ap_expand(int n, const int32_t* arp, const int32_t* aci, const double* av, const int32_t* prp,
-                      const int32_t* pci, const double* pv, const int64_t* off, int col_bits, uint64_t* keys,
-                      double* vals, hipStream_t st);
-void launch_pt_count(int n, const int32_t* prp, const int32_t* trp, int64_t* cnt, hipStream_t st);
-void launch_pt_expand(int n, const int32_t* prp, const int32_t* pci, const double* pv, const int32_t* trp,
-                      const int32_t* tci, const double* tv, const int64_t* off, int col_bits, uint64_t* keys,
-                      double* vals, hipStream_t st);
+// the terms of a product, row by row in order, from off[row] on
+void launch_expand_terms(const ProductArgs& a, int col_bits, uint64_t* keys, double* vals, hipStream_t st);
+// a CSR row pointer as starts and lengths (rows + 1 entries each, the last
+// length 0)
+void launch_loose_rows(int rows, const int32_t* rp, int64_t* off, int64_t* len, hipStream_t st);
 
 // sorted (key, value) list -> head flags of equal-key runs
 void launch_run_heads(int64_t m, const uint64_t* keys, int64_t* flags, hipStream_t st);
@@ -96,10 +142,6 @@ void launch_rowptr_from_keys(int64_t m, const uint64_t* keys, int col_bits, int 
 // column and value of each sorted (key, value) pair
 void launch_unpack_keys(int64_t m, const uint64_t* keys, const double* vals, int col_bits, int32_t* ci,
                         double* v, hipStream_t st);
-
-// out_ij = (c_ij + c_ji) / 2; err |= kErrPattern where (j,i) is missing
-void launch_symmetrize(int n, const int32_t* rp, const int32_t* ci, const double* v, double* out, int* err,
-                       hipStream_t st);
 
 // stable ascending sort of (key, value) pairs on bits [0, bits) (keys and
 // vals are double buffers; returns which buffer holds the result) and
