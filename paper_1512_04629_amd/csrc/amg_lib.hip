@@ -176,6 +176,10 @@ struct PendingEvent {
 
 struct amg_batch_ctx;
 
+// Who adds a dot product's partials: a launch of its own; the kernel that needs
+// the sum, if they are few; the launch that hands the scalars to the host.
+enum class Finish { kNow, kQuick, kPublish };
+
 struct amg_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -189,7 +193,10 @@ struct amg_ctx {
     double* coarse_inv = nullptr;
     double* scal = nullptr;
     double* partials = nullptr;
-    int partial_cap = 0;
+    int partial_cap = 0;              // and kVecBlocks more
+    Finish finish = Finish::kNow;     // of the next dot products (row_op)
+    DotTarget pend{};                 // one left to whoever takes it: its target and the number of partials
+    int pend_parts = 0;
     double* pinned = nullptr;        // host-coherent: the scalar slots, then the readback sequence word
     double* pinned_dev = nullptr;    // its device address
     uint32_t* flag_host = nullptr;
@@ -407,6 +414,31 @@ void prof_collect(amg_ctx* h) {
 // ---------------------------------------------------------------------------
 DotTarget dot_to(amg_ctx* h, int slot) { return DotTarget{h->partials, h->scal + slot}; }
 
+// adds the partials of a dot product, or leaves them as h->finish says
+void finish_dot(amg_ctx* h, const DotTarget& dt, int nparts) {
+    if (nparts <= 0) return;
+    if (h->finish == Finish::kPublish || (h->finish == Finish::kQuick && nparts <= kQuickParts)) {
+        h->pend = dt;
+        h->pend_parts = nparts;
+        return;
+    }
+    launch_dot_finish(dt, nparts, h->stream);
+    check_launch();
+}
+
+// the partials left for the kernel that needs their sum
+PartialSums take_partials(amg_ctx* h) {
+    PartialSums p{h->pend.partials, h->pend_parts};
+    h->pend_parts = 0;
+    return p;
+}
+
+struct FinishScope {
+    amg_ctx* h;
+    FinishScope(amg_ctx* hh, Finish f) : h(hh) { h->finish = f; }
+    ~FinishScope() { h->finish = Finish::kNow; }
+};
+
 void row_op(amg_ctx* h, int kind, int level, RowOp op, const DevMat& m, const double* g,
             const double* u, const double* dinv, double* y, double* y2, int dot_slot) {
     DotTarget dt = dot_slot >= 0 ? dot_to(h, dot_slot) : DotTarget{nullptr, nullptr};
@@ -420,10 +452,7 @@ void row_op(amg_ctx* h, int kind, int level, RowOp op, const DevMat& m, const do
         nparts = launch_row_op(op, m.width, cv, g, u, dinv, h->sp.omega, y, y2, dt, h->stream);
         check_launch();
     }
-    if (nparts > 0) {
-        launch_dot_finish(dt, nparts, h->stream);
-        check_launch();
-    }
+    finish_dot(h, dt, nparts);
 }
 
 void row_op(amg_ctx* h, int kind, int level, RowOp op, const DevMat& m, const float* vals, const float* g,
@@ -1219,10 +1248,20 @@ void await_published(amg_ctx* h, uint32_t seq) {
 // needs another download complete synchronizes the stream itself.
 // The scalar slots as the device holds them once the stream reaches this
 // point; with extra, slot S_COUNT of the result holds *extra.
-const double* read_scalars(amg_ctx* h, const int* extra = nullptr) {
+uint32_t publish_scalars(amg_ctx* h, const int* extra = nullptr) {
     const uint32_t seq = ++h->pub_seq;
-    launch_publish_scalars(S_COUNT, h->scal, h->pinned_dev, h->flag_dev, seq, extra, h->stream);
+    if (h->pend_parts > 0) {
+        double* result = h->pend.result;
+        launch_finish_publish(take_partials(h), result, S_COUNT, h->scal, h->pinned_dev, h->flag_dev, seq, extra,
+                              h->stream);
+    } else {
+        launch_publish_scalars(S_COUNT, h->scal, h->pinned_dev, h->flag_dev, seq, extra, h->stream);
+    }
     check_launch();
+    return seq;
+}
+const double* read_scalars(amg_ctx* h, const int* extra = nullptr) {
+    const uint32_t seq = publish_scalars(h, extra);
     await_published(h, seq);
     return h->pinned;
 }
@@ -1354,15 +1393,25 @@ void precondition(amg_ctx* h, bool mixed, Guess guess, int dot_slot, bool l0_res
         return;
     }
     if (guess == Guess::kZero) launch_narrow(n, h->cg_r32, h->cg_r, h->stream);
-    vcycle<float>(h, h->cg_r32, h->cg_z32, guess, -1);
+    vcycle<float>(h, h->cg_r32, h->cg_z32, guess, -1, l0_resid_ready);
     ProfScope ps(h, AMG_K_VECTOR, 0);
-    launch_widen_dot(n, h->cg_z, h->cg_z32, h->cg_r, dot_to(h, dot_slot), h->stream);
+    const DotTarget dt = dot_to(h, dot_slot);
+    finish_dot(h, dt, launch_widen_dot(n, h->cg_z, h->cg_z32, h->cg_r, dt, h->stream));
     check_launch();
+}
+
+// the level-0 residual that a cycle with Guess::kPrescaled and one pre-sweep
+// starts from (l0_resid_ready), launched ahead of it
+template <class T>
+void first_residual(amg_ctx* h, const T* b0, T* x0) {
+    LevelView<T> v = level_view(h, 0, (T*)nullptr);
+    row_op_t(h, AMG_K_JACOBI_ZERO, 0, kResid, *v.Ah, v.ahv, zero_start<T>(h, 0, x0), b0, nullptr, v.r, nullptr, -1);
 }
 
 amg_status solve(amg_ctx* h, const double* b, double* x, const amg_solve_params& p,
                  amg_solve_info* info_out, double* hist) {
     ensure_solve_buffers(h);
+    h->pend_parts = 0;
     DevLevel& f = h->lv[0];
     const int n = f.n;
     const DevMat& A = f.A;
@@ -1404,6 +1453,7 @@ amg_status solve(amg_ctx* h, const double* b, double* x, const amg_solve_params&
     int inwin = 0;
     int rz_slot = S_RZ0;
     double nrf_read = -1.0;   // the final true residual norm, when the loop has read it
+    double nr_last = nr0, rate = 1.0;   // of the last iteration
     if (!std::isfinite(nr0)) {
         st = AMG_ERR_BREAKDOWN;
     } else if (nr0 == 0.0) {
@@ -1416,19 +1466,30 @@ amg_status solve(amg_ctx* h, const double* b, double* x, const amg_solve_params&
             launch_copy(n, h->cg_p, h->cg_z, h->stream);
         }
         while (info.iters < p.maxit) {
+            // the last iteration of an adaptive window needs the true
+            // residual whatever its outcome (for the window test, or as the
+            // final residual if it converges): computed before, read back
+            // with the iteration's scalars
+            const bool window_end = p.adaptive && inwin + 1 == p.k;
             if (pcg) {
-                row_op(h, AMG_K_SPMV_DOT, 0, kSpmvDot, A, h->cg_p, nullptr, nullptr, h->cg_q, nullptr, S_PQ);
+                {
+                    FinishScope fs(h, Finish::kQuick);
+                    row_op(h, AMG_K_SPMV_DOT, 0, kSpmvDot, A, h->cg_p, nullptr, nullptr, h->cg_q, nullptr, S_PQ);
+                }
                 {
                     ProfScope ps(h, AMG_K_VECTOR, 0);
                     // also forms the next preconditioner's zero-guess sweep omega D^-1 r
                     const bool pre1 = h->sp.nu_pre >= 1;
-                    launch_cg_update_xr(n, x, r, h->cg_p, h->cg_q, h->scal, rz_slot, S_PQ, h->scal + S_FLAG,
-                                        dot_to(h, S_NR2), f.dinv, h->sp.omega,
-                                        (!mixed && pre1) ? zero_start<double>(h, 0, h->cg_z) : nullptr,
-                                        mixed ? h->cg_r32 : nullptr, f.dinv32,
-                                        (mixed && pre1) ? zero_start<float>(h, 0, h->cg_z32) : nullptr,
-                                        h->stream);
+                    // (the kernel may be adding the first partials when it writes these)
+                    const DotTarget dt{h->partials + h->partial_cap, h->scal + S_NR2};
+                    const int parts = launch_cg_update_xr(
+                        n, x, r, h->cg_p, h->cg_q, h->scal, rz_slot, S_PQ, take_partials(h), h->scal + S_FLAG, dt,
+                        f.dinv, h->sp.omega, (!mixed && pre1) ? zero_start<double>(h, 0, h->cg_z) : nullptr,
+                        mixed ? h->cg_r32 : nullptr, f.dinv32,
+                        (mixed && pre1) ? zero_start<float>(h, 0, h->cg_z32) : nullptr, h->stream);
                     check_launch();
+                    FinishScope fs(h, window_end ? Finish::kNow : Finish::kPublish);
+                    finish_dot(h, dt, parts);
                 }
             } else if (mixed) {
                 // iterative refinement: x += V32(r, 0) with r the current true residual
@@ -1441,11 +1502,6 @@ amg_status solve(amg_ctx* h, const double* b, double* x, const amg_solve_params&
                 else vcycle<double>(h, b, x, Guess::kNonzero, -1);
                 row_op(h, AMG_K_RESIDUAL, 0, kResidNorm, A, x, b, nullptr, r, nullptr, S_NR2);
             }
-            // the last iteration of an adaptive window needs the true
-            // residual whatever its outcome (for the window test, or as the
-            // final residual if it converges): computed before, read back
-            // with the iteration's scalars
-            const bool window_end = p.adaptive && inwin + 1 == p.k;
             // In the FP64 PCG with one pre-sweep, the next preconditioner's
             // first step is the level-0 residual r - A (omega D^-1 r): it is
             // formed in the same pass over A_0's SELL-64 copy as the true
@@ -1467,21 +1523,34 @@ amg_status solve(amg_ctx* h, const double* b, double* x, const amg_solve_params&
                                                         h->rt, dt, h->stream);
                         check_launch();
                     }
-                    if (nparts > 0) {
-                        launch_dot_finish(dt, nparts, h->stream);
-                        check_launch();
-                        l0_ready = true;
-                    }
+                    FinishScope fs(h, Finish::kPublish);
+                    finish_dot(h, dt, nparts);
+                    l0_ready = nparts > 0;
                 }
+                FinishScope fs(h, Finish::kPublish);
                 if (!l0_ready) row_op(h, AMG_K_RESIDUAL, 0, kResidNorm, A, x, b, nullptr, h->rt, nullptr, S_NRT);
             }
-            const double* sc = read_scalars(h);
+            const uint32_t seq = publish_scalars(h);
+            // While the host waits, looks and launches again the device would idle
+            // for 6 to 8 us: the next cycle's first residual is launched before,
+            // unless this iteration looks like the last one (that residual is then
+            // not used).
+            if (pcg && !window_end && !gs_on(h) && h->sp.nu_pre == 1 && h->lv.size() > 1 && !h->profiling &&
+                info.iters + 1 < p.maxit && nr_last * rate > p.rtol * nr0) {
+                if (mixed) first_residual<float>(h, h->cg_r32, h->cg_z32);
+                else first_residual<double>(h, h->cg_r, h->cg_z);
+                l0_ready = true;
+            }
+            await_published(h, seq);
+            const double* sc = h->pinned;
             if (pcg && sc[S_FLAG] != 0.0) { st = AMG_ERR_BREAKDOWN; break; }
             const double nr = std::sqrt(sc[S_NR2]);
             info.iters++;
             inwin++;
             if (hist) hist[info.iters] = nr;
             if (!std::isfinite(nr)) { st = AMG_ERR_BREAKDOWN; break; }
+            rate = nr / nr_last;
+            nr_last = nr;
             if (nr <= p.rtol * nr0) {
                 info.converged = 1;
                 st = AMG_OK;
@@ -1515,13 +1584,17 @@ amg_status solve(amg_ctx* h, const double* b, double* x, const amg_solve_params&
             if (pcg) {
                 const int new_slot = rz_slot == S_RZ0 ? S_RZ1 : S_RZ0;
                 // after a restart r was rebuilt, so the prescaled sweep is stale
-                precondition(h, mixed, restart ? Guess::kZero : Guess::kPrescaled, new_slot, l0_ready && !restart);
+                {
+                    FinishScope fs(h, restart ? Finish::kNow : Finish::kQuick);
+                    precondition(h, mixed, restart ? Guess::kZero : Guess::kPrescaled, new_slot,
+                                 l0_ready && !restart);
+                }
                 if (restart) {
                     info.restarts++;
                     launch_copy(n, h->cg_p, h->cg_z, h->stream);
                 } else {
                     ProfScope ps(h, AMG_K_VECTOR, 0);
-                    launch_cg_update_p(n, h->cg_p, h->cg_z, h->scal, new_slot, rz_slot, h->stream);
+                    launch_cg_update_p(n, h->cg_p, h->cg_z, h->scal, new_slot, rz_slot, take_partials(h), h->stream);
                     check_launch();
                 }
                 rz_slot = new_slot;
@@ -2420,14 +2493,18 @@ void set_compact_indices(amg_ctx* h, bool on) {
 // the words the host reads without a copy
 void ensure_published(amg_ctx* h) {
     if (h->pinned) return;
-    // the scalar slots, then the readback's sequence word, host-coherent so
-    // that the device's writes reach the host without a copy
-    HIP_CHECK(hipHostMalloc((void**)&h->pinned, sizeof(double) * (S_COUNT + 1) + 64,
+    // the scalar slots, the readback's sequence word, the results of a grid
+    // solve: host-coherent so that the device's writes reach the host without a
+    // copy (one allocation: each costs about 120 us)
+    constexpr int kFlagAt = S_COUNT + 1, kGridAt = kFlagAt + 8;
+    HIP_CHECK(hipHostMalloc((void**)&h->pinned, sizeof(double) * (kGridAt + kGridOutInts + kGridHist),
                             hipHostMallocCoherent | hipHostMallocMapped));
-    h->flag_host = reinterpret_cast<uint32_t*>(h->pinned + S_COUNT + 1);
+    h->flag_host = reinterpret_cast<uint32_t*>(h->pinned + kFlagAt);
     *h->flag_host = 0;
     HIP_CHECK(hipHostGetDevicePointer((void**)&h->pinned_dev, h->pinned, 0));
-    h->flag_dev = reinterpret_cast<uint32_t*>(h->pinned_dev + S_COUNT + 1);
+    h->flag_dev = reinterpret_cast<uint32_t*>(h->pinned_dev + kFlagAt);
+    h->grid_out = h->pinned + kGridAt;
+    h->grid_out_dev = h->pinned_dev + kGridAt;
 }
 
 void finish_setup(amg_ctx* h) {
@@ -2518,16 +2595,11 @@ void finish_setup(amg_ctx* h) {
     // every width for the largest level
     partial_need = std::max(partial_need, max_row_launch_blocks());
     h->partial_cap = partial_need;
-    h->partials = dalloc_n<double>(h, partial_need);
+    h->partials = dalloc_n<double>(h, partial_need + kVecBlocks);
     h->scal = dalloc_n<double>(h, S_COUNT);
     launch_fill_f64(S_COUNT, h->scal, 0.0, h->stream);
     check_launch();
     ensure_published(h);
-    if (h->lv[0].gwin) {
-        HIP_CHECK(hipHostMalloc((void**)&h->grid_out, sizeof(double) * (kGridOutInts + kGridHist),
-                                hipHostMallocCoherent | hipHostMallocMapped));
-        HIP_CHECK(hipHostGetDevicePointer((void**)&h->grid_out_dev, h->grid_out, 0));
-    }
     sync(h);
     refresh_coarse_inverse(h);
     h->prof.assign((size_t)AMG_K_NUM * h->lv.size(), ProfAcc{});
@@ -3120,7 +3192,6 @@ void destroy(amg_ctx* h) {
                     (void*)h->cg_z, (void*)h->cg_p, (void*)h->cg_q, (void*)h->xw, (void*)h->rt, (void*)h->grid_flags})
         dfree(h, p);
     dfree(h, h->grid_part);
-    if (h->grid_out) (void)hipHostFree(h->grid_out);
     if (h->pinned) (void)hipHostFree(h->pinned);
     for (auto& pe : h->pending) {
         (void)hipEventDestroy(pe.start);
@@ -3142,7 +3213,7 @@ constexpr int64_t kNoAllocMaxRows = 2097152;     // 2^21: 3D Poisson 128^3
 constexpr int64_t kNoAllocScalars = 256;         // >= S_COUNT
 constexpr int64_t kNoAllocPartials = 65536;      // >= every launch's workgroup count
 constexpr int64_t kNoAllocVectors = 6;
-constexpr int64_t kNoAllocDoubles = kNoAllocScalars + kNoAllocPartials + kNoAllocVectors * kNoAllocMaxRows + 32;
+constexpr int64_t kNoAllocDoubles = kNoAllocScalars + kNoAllocPartials + kVecBlocks + kNoAllocVectors * kNoAllocMaxRows + 32;
 static_assert(S_COUNT <= kNoAllocScalars, "scalar slots do not fit the allocation-free work memory");
 
 static __device__ __align__(256) double scratch[kNoAllocDoubles];
@@ -3181,7 +3252,7 @@ struct NoAllocWork {
         r = h->cg_r; z = h->cg_z; p = h->cg_p; q = h->cg_q; xw = h->xw; rt = h->rt;
         partials = h->partials; scal = h->scal;
         const int64_t stride = (n + 31) / 32 * 32;
-        double* v = base + kNoAllocScalars + kNoAllocPartials;
+        double* v = base + kNoAllocScalars + kNoAllocPartials + kVecBlocks;
         h->scal = base;
         h->partials = base + kNoAllocScalars;
         h->cg_r = v;

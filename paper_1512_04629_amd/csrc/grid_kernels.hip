@@ -644,8 +644,8 @@ __global__ __launch_bounds__(kThreads) void grid_solve_kernel(GridArgs<T> a, Gri
         to_host(s.out + kGridOutTrue, nrt);
         to_host(s.out + kGridOutWindow, nws);
         to_host(s.out + kGridOutSingular, s.singular ? (double)*s.singular : 0.0);
-        __threadfence_system();
-        __hip_atomic_store(s.done, s.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        stores_done();
+        to_host(s.done, s.seq);
     }
 }
 

@@ -129,8 +129,8 @@ __device__ __forceinline__ int sub_sum_int(int v) {
 
 constexpr int kFinishBlock = 1024;
 
-__global__ __launch_bounds__(kFinishBlock) void dot_finish_kernel(int nparts, const double* __restrict__ partials,
-                                                                  double* __restrict__ result) {
+// the sum, in thread 0
+__device__ __forceinline__ double finish_sum(int nparts, const double* __restrict__ partials) {
     __shared__ double wsum[kFinishBlock / 64];
     // thread t takes partials t, t + 1024, ... into four accumulators in turn
     // (independent loads in flight), adds them pairwise, then a fixed shuffle
@@ -151,12 +151,37 @@ __global__ __launch_bounds__(kFinishBlock) void dot_finish_kernel(int nparts, co
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = s;
     __syncthreads();
+    double tot = 0.0;
     if (threadIdx.x == 0) {
-        double tot = wsum[0];
+        tot = wsum[0];
 #pragma unroll
         for (int w = 1; w < kFinishBlock / 64; ++w) tot += wsum[w];
-        *result = tot;
     }
+    return tot;
+}
+
+__global__ __launch_bounds__(kFinishBlock) void dot_finish_kernel(int nparts, const double* __restrict__ partials,
+                                                                  double* __restrict__ result) {
+    const double tot = finish_sum(nparts, partials);
+    if (threadIdx.x == 0) *result = tot;
+}
+
+// The same, then the n scalar slots to the host (publish_scalars_kernel): one
+// launch of 4 us where the host waits for a sum, before two of 4.5 and 3.5.
+__global__ __launch_bounds__(kFinishBlock) void finish_publish_kernel(int nparts, const double* __restrict__ partials,
+                                                                      double* result, int n, const double* scal,
+                                                                      double* host, uint32_t* flag, uint32_t seq,
+                                                                      const int* extra) {
+    const double tot = finish_sum(nparts, partials);
+    const int slot = (int)(result - scal);
+    for (int i = threadIdx.x; i < n; i += kFinishBlock)
+        if (i != slot) host_store(host + i, scal[i]);
+    if (threadIdx.x == 0) {
+        *result = tot;
+        host_store(host + slot, tot);
+        host_store(host + n, extra ? (double)*extra : 0.0);
+    }
+    host_flag(flag, seq);
 }
 
 void finish_dot(const DotTarget& dot, int nparts, hipStream_t st) {
@@ -1038,22 +1063,48 @@ __global__ __launch_bounds__(kBlock) void sell_compress_kernel(int rows, const i
 
 // ---- vector kernels --------------------------------------------------------
 
-constexpr int kVecGrid = 2048;
+constexpr int kVecGrid = kVecBlocks;
 
 int vec_grid(int n) { return std::max(1, std::min(kVecGrid, (n + kBlock - 1) / kBlock)); }
+
+// Sum of at most kQuickParts partials by a whole workgroup, in every thread: a
+// kernel that needs a dot product adds it itself where that costs less than the
+// launch that would (8 KB a workgroup from its L2, about 1 us, against 4).
+__device__ __forceinline__ double quick_sum(int nparts, const double* __restrict__ partials) {
+    static_assert(kQuickParts == 4 * kBlock);
+    __shared__ double wsum[kBlock / 64];
+    double v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int i = k * kBlock + threadIdx.x;
+        v[k] = i < nparts ? partials[i] : 0.0;
+    }
+    double s = (v[0] + v[1]) + (v[2] + v[3]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = s;
+    __syncthreads();
+    double tot = wsum[0];
+#pragma unroll
+    for (int w = 1; w < kBlock / 64; ++w) tot += wsum[w];
+    return tot;
+}
 
 __global__ __launch_bounds__(kBlock) void cg_update_xr_kernel(int n, double* __restrict__ x,
                                                               double* __restrict__ r,
                                                               const double* __restrict__ p,
                                                               const double* __restrict__ q,
-                                                              const double* scal, int i_num,
-                                                              int i_den, double* flag, DotTarget dot,
+                                                              double* scal, int i_num,
+                                                              int i_den, int nparts,
+                                                              const double* __restrict__ parts,
+                                                              double* flag, DotTarget dot,
                                                               const double* __restrict__ dinv,
                                                               double omega, double* __restrict__ zs,
                                                               float* __restrict__ r32,
                                                               const float* __restrict__ dinv32,
                                                               float* __restrict__ zs32) {
-    const double num = scal[i_num], den = scal[i_den];
+    const double num = scal[i_num], den = nparts > 0 ? quick_sum(nparts, parts) : scal[i_den];
+    if (nparts > 0 && blockIdx.x == 0 && threadIdx.x == 0) scal[i_den] = den;
     const bool ok = den > 0.0 && std::isfinite(den);
     double contrib = 0.0;
     if (ok) {
@@ -1079,8 +1130,11 @@ __global__ __launch_bounds__(kBlock) void cg_update_xr_kernel(int n, double* __r
 
 __global__ __launch_bounds__(kBlock) void cg_update_p_kernel(int n, double* __restrict__ p,
                                                              const double* __restrict__ z,
-                                                             const double* scal, int i_num, int i_den) {
-    const double beta = scal[i_num] / scal[i_den];
+                                                             double* scal, int i_num, int i_den, int nparts,
+                                                             const double* __restrict__ parts) {
+    const double num = nparts > 0 ? quick_sum(nparts, parts) : scal[i_num];
+    if (nparts > 0 && blockIdx.x == 0 && threadIdx.x == 0) scal[i_num] = num;
+    const double beta = num / scal[i_den];
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock)
         p[i] = z[i] + beta * p[i];
 }
@@ -2034,19 +2088,18 @@ bool clear_launch_events() {
     return pending;
 }
 
-void launch_cg_update_xr(int n, double* x, double* r, const double* p, const double* q,
-                         const double* scal, int i_num, int i_den, double* flag, DotTarget dot,
-                         const double* dinv, double omega, double* zs, float* r32,
-                         const float* dinv32, float* zs32, hipStream_t st) {
+int launch_cg_update_xr(int n, double* x, double* r, const double* p, const double* q, double* scal, int i_num,
+                        int i_den, const PartialSums& den, double* flag, DotTarget dot, const double* dinv,
+                        double omega, double* zs, float* r32, const float* dinv32, float* zs32, hipStream_t st) {
     hipLaunchKernelGGL(cg_update_xr_kernel, dim3(vec_grid(n)), dim3(kBlock), 0, st, n, x, r, p, q,
-                       scal, i_num, i_den, flag, dot, dinv, omega, zs, r32, dinv32, zs32);
-    finish_dot(dot, vec_grid(n), st);
+                       scal, i_num, i_den, den.count, den.partials, flag, dot, dinv, omega, zs, r32, dinv32, zs32);
+    return vec_grid(n);
 }
 
-void launch_cg_update_p(int n, double* p, const double* z, const double* scal, int i_num,
-                        int i_den, hipStream_t st) {
+void launch_cg_update_p(int n, double* p, const double* z, double* scal, int i_num, int i_den,
+                        const PartialSums& num, hipStream_t st) {
     hipLaunchKernelGGL(cg_update_p_kernel, dim3(vec_grid(n)), dim3(kBlock), 0, st, n, p, z, scal,
-                       i_num, i_den);
+                       i_num, i_den, num.count, num.partials);
 }
 
 void launch_scaled_copy(int n, double* y, const double* dinv, const double* x, double omega,
@@ -2057,17 +2110,20 @@ void launch_scaled_copy(int n, double* y, const double* dinv, const double* x, d
 __global__ __launch_bounds__(256) void publish_scalars_kernel(int n, const double* __restrict__ scal,
                                                             double* host, uint32_t* flag, uint32_t seq,
                                                             const int* extra) {
-    for (int i = threadIdx.x; i < n; i += 256) host[i] = scal[i];
-    if (threadIdx.x == 0) host[n] = extra ? (double)*extra : 0.0;
-    // every thread's writes reach the system before the workgroup's flag
-    __threadfence_system();
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    for (int i = threadIdx.x; i < n; i += 256) host_store(host + i, scal[i]);
+    if (threadIdx.x == 0) host_store(host + n, extra ? (double)*extra : 0.0);
+    host_flag(flag, seq);
 }
 
 void launch_publish_scalars(int n, const double* scal, double* host, uint32_t* flag, uint32_t seq,
                             const int* extra, hipStream_t st) {
     hipLaunchKernelGGL(publish_scalars_kernel, dim3(1), dim3(256), 0, st, n, scal, host, flag, seq, extra);
+}
+
+void launch_finish_publish(const PartialSums& sum, double* result, int n, const double* scal, double* host,
+                           uint32_t* flag, uint32_t seq, const int* extra, hipStream_t st) {
+    hipLaunchKernelGGL(finish_publish_kernel, dim3(1), dim3(kFinishBlock), 0, st, sum.count, sum.partials, result, n,
+                       scal, host, flag, seq, extra);
 }
 
 void launch_copy(int n, double* y, const double* x, hipStream_t st) {
@@ -2089,9 +2145,9 @@ void launch_narrow(int64_t n, float* y, const double* x, hipStream_t st) {
     hipLaunchKernelGGL(narrow_kernel, dim3(g), dim3(kBlock), 0, st, n, y, x);
 }
 
-void launch_widen_dot(int n, double* y, const float* x, const double* u, DotTarget dot, hipStream_t st) {
+int launch_widen_dot(int n, double* y, const float* x, const double* u, DotTarget dot, hipStream_t st) {
     hipLaunchKernelGGL(widen_dot_kernel, dim3(vec_grid(n)), dim3(kBlock), 0, st, n, y, x, u, dot);
-    finish_dot(dot, vec_grid(n), st);
+    return vec_grid(n);
 }
 
 void launch_add_widened(int n, double* x, const float* e, hipStream_t st) {

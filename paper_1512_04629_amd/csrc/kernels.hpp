@@ -85,6 +85,14 @@ struct DotTarget {
     double* result;       // receives the sum
 };
 
+// Partials that the next kernel adds itself (count 0: the sum is in its slot).
+constexpr int kQuickParts = 1024;
+constexpr int kVecBlocks = 2048;     // most workgroups, and partials, of a vector kernel
+struct PartialSums {
+    const double* partials = nullptr;
+    int count = 0;
+};
+
 // Lanes per row for a matrix with the given mean row length.
 int pick_width(double mean_row_len);
 
@@ -139,13 +147,15 @@ void launch_coded_fill(int rows, CodedKind kind, const int32_t* rp, const int32_
 // *flag = 1.0.
 // With r32 not null also r32 = (float) r and zs32 = omega dinv32 r32 (the
 // FP32 preconditioner's right-hand side and zero-guess sweep).
-void launch_cg_update_xr(int n, double* x, double* r, const double* p, const double* q,
-                         const double* scal, int i_num, int i_den, double* flag, DotTarget dot,
-                         const double* dinv, double omega, double* zs, float* r32,
-                         const float* dinv32, float* zs32, hipStream_t st);
-// p = z + beta p with beta = scal[i_num]/scal[i_den]; if restart, p = z.
-void launch_cg_update_p(int n, double* p, const double* z, const double* scal, int i_num,
-                        int i_den, hipStream_t st);
+// den: partials of scal[i_den] not summed yet.  Returns the number of partials
+// of dot, which are not summed.
+int launch_cg_update_xr(int n, double* x, double* r, const double* p, const double* q, double* scal, int i_num,
+                        int i_den, const PartialSums& den, double* flag, DotTarget dot, const double* dinv,
+                        double omega, double* zs, float* r32, const float* dinv32, float* zs32, hipStream_t st);
+// p = z + beta p with beta = scal[i_num]/scal[i_den]; num: partials of
+// scal[i_num] not summed yet
+void launch_cg_update_p(int n, double* p, const double* z, double* scal, int i_num, int i_den,
+                        const PartialSums& num, hipStream_t st);
 // y = omega dinv x (zero-guess smoothing of one sweep without residual)
 void launch_scaled_copy(int n, double* y, const double* dinv, const double* x, double omega,
                         hipStream_t st);
@@ -155,6 +165,9 @@ void launch_copy(int n, double* y, const double* x, hipStream_t st);
 // visible to the host before the flag)
 void launch_publish_scalars(int n, const double* scal, double* host, uint32_t* flag, uint32_t seq,
                             const int* extra, hipStream_t st);
+// the same with *result (one of the slots) first set to the sum of the partials
+void launch_finish_publish(const PartialSums& sum, double* result, int n, const double* scal, double* host,
+                           uint32_t* flag, uint32_t seq, const int* extra, hipStream_t st);
 void launch_fill_f64(int64_t n, double* p, double v, hipStream_t st);
 // dot -> sum_i a_i b_i
 void launch_dot(int n, const double* a, const double* b, DotTarget dot, hipStream_t st);
@@ -183,7 +196,8 @@ void launch_inverse_diagonal(const CsrView& a, double* dinv, float* dinv32, hipS
 void launch_dense_matvec(int n, const double* ainv, const float* b, float* y, hipStream_t st);
 // precision conversions and FP32 vector helpers
 void launch_narrow(int64_t n, float* y, const double* x, hipStream_t st);
-void launch_widen_dot(int n, double* y, const float* x, const double* u, DotTarget dot, hipStream_t st);
+// returns the number of partials of dot, which are not summed
+int launch_widen_dot(int n, double* y, const float* x, const double* u, DotTarget dot, hipStream_t st);
 void launch_add_widened(int n, double* x, const float* e, hipStream_t st);
 void launch_scaled_copy(int n, float* y, const float* dinv, const float* x, float omega, hipStream_t st);
 void launch_copy(int n, float* y, const float* x, hipStream_t st);

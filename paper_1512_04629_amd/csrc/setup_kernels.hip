@@ -453,11 +453,9 @@ __global__ void unpack_keys_kernel(int64_t m, const uint64_t* __restrict__ keys,
 __global__ void publish_words_kernel(PublishWords w, int64_t* host, uint32_t* flag, uint32_t seq) {
     const int t = threadIdx.x;
     if (t < w.count)
-        host[t] = w.bytes[t] == 8 ? *static_cast<const int64_t*>(w.src[t])
-                                  : (int64_t) * static_cast<const int32_t*>(w.src[t]);
-    __threadfence_system();
-    __syncthreads();
-    if (t == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        host_store(host + t, w.bytes[t] == 8 ? *static_cast<const int64_t*>(w.src[t])
+                                             : (int64_t) * static_cast<const int32_t*>(w.src[t]));
+    host_flag(flag, seq);
 }
 
 }  // namespace
