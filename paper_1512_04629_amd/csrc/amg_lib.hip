@@ -135,7 +135,8 @@ struct DevLevel {
     int32_t* gwin = nullptr;
     int gspan = 0, gagain = 0, gshare = 0;
     double* lump_thr = nullptr;   // strong-neighbour lumping: strength thresholds of A's rows
-    double* lump_den = nullptr;   //   and share denominators per dropped entry of A
+    double* lump_den = nullptr;   //   share denominators per dropped entry of A
+    int32_t* lump_dropped = nullptr;   //   and the dropped entries' positions
     bool have_m = false;
     bool m_hybrid = false;        // in_m currently holds the Hybrid Galerkin pattern
     bool keep_valid = false;
@@ -647,6 +648,7 @@ void sparsify_levels(amg_ctx* h, const std::vector<std::pair<int, double>>& todo
         if (h->lumping == AMG_LUMP_STRONG && !c.lump_thr) {
             c.lump_thr = dalloc_n<double>(h, c.n);
             c.lump_den = dalloc_n<double>(h, c.A.nnz);
+            c.lump_dropped = dalloc_n<int32_t>(h, c.A.nnz);
         }
     }
     bool coarse_changed = false;
@@ -689,16 +691,17 @@ void sparsify_levels(amg_ctx* h, const std::vector<std::pair<int, double>>& todo
                 launch_exclusive_scan(c.n, c.kcnt, c.Ahs.rp, h->scan_scratch, h->stream);
                 // Algorithm 3's second loop: dropped entries shared among strong neighbours
                 const DevMat& a = c.A;
-                launch_compact_copy(c.n, a.rp, a.ci, a.v, c.keep, c.Ahs.rp, c.Ahs.ci, c.Ahs.v, h->stream);
+                const LumpLists lists{c.lump_dropped, c.kcnt};   // (the counts are scanned)
+                launch_compact_copy(c.n, a.rp, a.ci, a.v, c.keep, c.Ahs.rp, c.Ahs.ci, c.Ahs.v, lists, h->stream);
                 launch_lump_threshold(c.n, a.rp, a.ci, a.v, h->sp.theta, c.lump_thr, h->stream);
                 {
                     ProfScope pd(h, AMG_K_LUMP_DEN, l);
-                    launch_lump_den(c.n, a.rp, a.ci, a.v, c.keep, c.lump_thr, c.lump_den, a.view().mean_row,
-                                    h->lump_shapes, h->stream);
+                    launch_lump_den(c.n, a.rp, a.ci, a.v, c.keep, c.Ahs.rp, c.Ahs.ci, lists, c.lump_thr, c.lump_den,
+                                    a.view().mean_row, h->lump_shapes, h->stream);
                 }
                 {
                     ProfScope pl(h, AMG_K_LUMP_SHARES, l);
-                    launch_strong_lump(c.n, a.rp, a.ci, a.v, c.keep, c.lump_thr, c.lump_den, c.Ahs.rp, c.Ahs.ci,
+                    launch_strong_lump(c.n, a.rp, a.ci, a.v, c.keep, lists, c.lump_thr, c.lump_den, c.Ahs.rp, c.Ahs.ci,
                                        c.Ahs.v, a.view().mean_row, h->lump_shapes, h->stream);
                 }
                 launch_inverse_diagonal(c.Ahs.view(), c.dinv, h->fp32 ? c.dinv32 : nullptr, h->stream);
@@ -3171,6 +3174,7 @@ void destroy(amg_ctx* h) {
         dfree(h, d.rowmax);
         dfree(h, d.lump_thr);
         dfree(h, d.lump_den);
+        dfree(h, d.lump_dropped);
         dfree(h, d.b);
         dfree(h, d.x);
         dfree(h, d.xt);

@@ -1,11 +1,15 @@
 // Strong-neighbour lumping kernels: every sum and share in the order the
 // definition fixes (ascending columns; shares of a target in ascending order
 // of their source entry), contraction off.  The threshold and the copy run
-// one wave per row; the shares a workgroup per row with the row staged in
-// LDS, the denominators the same or, on levels of short rows, a wave per row
-// with its own stage (rows longer than the stage, and a launch forced to it,
-// one wave per row without a stage).
+// one wave per row; the copy also lists every row's dropped entries, from
+// rp[i] - new_rp[i] on.  The shares run a wave per row by those lists, rows of
+// many dropped entries a workgroup with the row staged in LDS; the denominators
+// the same or, on levels of short rows, a wave per row with its own stage (rows
+// longer than the stage, and a launch forced to it, one wave per row without a
+// stage or lists).
 #include "lump_kernels.hpp"
+
+#include "row_common.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -27,7 +31,7 @@ constexpr int kWideCap = 256;   // row entries a workgroup stages in LDS (15 KB:
 constexpr double kDenWaveMeanRow = 80.0;
 constexpr int kDenWaveMinRows = 16384;
 
-int wave_grid_of(int n) { return std::max(1, std::min((n + kWaves - 1) / kWaves, 65536)); }
+int wave_grid_of(int n) { return round_up8(std::max(1, std::min((n + kWaves - 1) / kWaves, 65536))); }
 
 __device__ inline int find_in_row(const int32_t* ci, int b, int e, int col) {
     int lo = b, hi = e;
@@ -44,8 +48,9 @@ __device__ inline bool strong_at(const int32_t* ci, const double* v, const doubl
 }
 
 // one wave per row i (kWaves per workgroup), lanes over the row's entries
-#define WAVE_ROW_LOOP(i, n)                                                                         \
-    for (int i = blockIdx.x * kWaves + (int)(threadIdx.x >> 6); i < (n); i += gridDim.x * kWaves)
+// (neighbouring rows on one die: they read each other's rows)
+#define WAVE_ROW_LOOP(i, n)                                                                               \
+    for (int i = xcd_logical_block() * kWaves + (int)(threadIdx.x >> 6); i < (n); i += gridDim.x * kWaves)
 
 // one wave per row: the kept entries of each 64-entry chunk go to the next
 // free places in order (ballot, count of the lower lanes' kept entries)
@@ -54,9 +59,11 @@ __global__ void __launch_bounds__(kLB) compact_copy_kernel(int n, const int32_t*
                                                            const double* __restrict__ v,
                                                            const uint8_t* __restrict__ keep,
                                                            const int32_t* __restrict__ new_rp,
-                                                           int32_t* __restrict__ new_ci, double* __restrict__ new_v) {
+                                                           int32_t* __restrict__ new_ci, double* __restrict__ new_v,
+                                                           int32_t* __restrict__ dropped, int32_t* heavy_count) {
     const int lane = threadIdx.x & 63;
     const uint64_t below = (1ull << lane) - 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *heavy_count = 0;
     WAVE_ROW_LOOP(i, n) {
         const int ie = rp[i + 1];
         int w = new_rp[i];
@@ -64,10 +71,12 @@ __global__ void __launch_bounds__(kLB) compact_copy_kernel(int n, const int32_t*
             const int p = p0 + lane;
             const bool kp = p < ie && keep[p];
             const uint64_t mask = __ballot(kp);
+            const int at = w + __popcll(mask & below);   // kept entries before p
             if (kp) {
-                const int at = w + __popcll(mask & below);
                 new_ci[at] = ci[p];
                 new_v[at] = v[p];
+            } else if (p < ie) {
+                dropped[p - at] = p;
             }
             w += __popcll(mask);
         }
@@ -134,10 +143,18 @@ __device__ inline int lower_bound_lds(const int32_t* a, int len, int col) {
     return lo;
 }
 
+__device__ inline double lane_value(double x, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
+                            __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+
 // Ordered sum of the lanes' x where has is set, in lane order, onto acc
-// (the same value in every lane).
+// (the same value in every lane).  The sum is a chain; a term read with
+// readlane (the lane's number is uniform) joins it in tens of cycles where a
+// shuffle through LDS took more than a hundred.
 __device__ inline double ordered_add(double acc, bool has, double x) {
-    for (uint64_t mask = __ballot(has); mask != 0; mask &= mask - 1) acc = acc + __shfl(x, __builtin_ctzll(mask));
+    for (uint64_t mask = __ballot(has); mask != 0; mask &= mask - 1)
+        acc = acc + lane_value(x, __builtin_ctzll(mask));
     return acc;
 }
 
@@ -195,7 +212,8 @@ __global__ void __launch_bounds__(kLB) lump_den_wide_kernel(int n, const int32_t
 
 // Short rows: the same per dropped entry, but one wave per row (each wave
 // its own slice of LDS, so four rows of a workgroup are in flight at once);
-// a row's stage is written and read by its own wave only.
+// a row's stage is written and read by its own wave only, and its dropped
+// entries come from their list.
 __device__ inline void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -206,29 +224,28 @@ __global__ void __launch_bounds__(kLB) lump_den_wave_kernel(int n, const int32_t
                                                             const int32_t* __restrict__ ci,
                                                             const double* __restrict__ v,
                                                             const uint8_t* __restrict__ keep,
+                                                            const int32_t* __restrict__ hrp,
+                                                            const int32_t* __restrict__ hci,
+                                                            const int32_t* __restrict__ dropped,
                                                             const double* __restrict__ thr,
                                                             double* __restrict__ den) {
     __shared__ int32_t scw[kWaves][kWideCap];
-    __shared__ uint8_t skw[kWaves][kWideCap];
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    int32_t* sc = scw[wave];
-    uint8_t* sk = skw[wave];
+    int32_t* sc = scw[threadIdx.x >> 6];   // the row's kept columns
     WAVE_ROW_LOOP(i, n) {
-        const int ib = rp[i], ie = rp[i + 1], len = ie - ib;
-        if (len > kWideCap) {
+        const int ib = rp[i], ie = rp[i + 1], hb = hrp[i], he = hrp[i + 1], nk = he - hb;
+        if (ie - ib == nk) continue;
+        if (nk > kWideCap) {
             lump_den_row(i, lane, rp, ci, v, keep, thr, den);
             continue;
         }
         wave_lds_sync();   // the previous row's reads are done
-        for (int t = lane; t < len; t += 64) {
-            sc[t] = ci[ib + t];
-            sk[t] = keep[ib + t];
-        }
+        for (int t = lane; t < nk; t += 64) sc[t] = hci[hb + t];
         wave_lds_sync();
-        for (int u = 0; u < len; ++u) {
-            const int j = sc[u];
-            if (j == i || sk[u]) continue;
+        for (int o = ib - hb; o < ie - he; ++o) {
+            const int p = dropped[o];
+            const int j = ci[p];
+            if (j == i) continue;
             const int jb = rp[j], je = rp[j + 1];
             const double t = thr[j];
             double d = 0.0;
@@ -240,13 +257,13 @@ __global__ void __launch_bounds__(kLB) lump_den_wave_kernel(int n, const int32_t
                     const int m = ci[r];
                     a = v[r];
                     if (m != j && -a >= t) {
-                        const int w = lower_bound_lds(sc, len, m);
-                        has = w < len && sc[w] == m && sk[w];
+                        const int w = lower_bound_lds(sc, nk, m);
+                        has = w < nk && sc[w] == m;
                     }
                 }
                 d = ordered_add(d, has, fabs(a));
             }
-            if (lane == 0) den[ib + u] = d;
+            if (lane == 0) den[p] = d;
         }
     }
 }
@@ -358,7 +375,215 @@ __global__ void __launch_bounds__(kLB) strong_lump_kernel(int n, const int32_t* 
     WAVE_ROW_LOOP(k, n) { strong_lump_row(k, lane, rp, ci, v, keep, thr, den, hrp, hci, hv); }
 }
 
-// One workgroup per row k, row k of A (columns, values, keep flags,
+// Row k of the lumped operator by the lists of dropped entries, one wave.  Few
+// entries are dropped (gamma 0.1: 4 % on the finest sparsified level, a quarter
+// on the next), and only they give shares, so the work follows them and not the
+// rows: with D_i row i's list,
+// * (k,m), m > k, a lane each: the shares of D_k, one j after the other for all
+//   lanes, row j staged in LDS and searched for m; then those of D_m, each lane
+//   along its own list, j searched in the staged row k.  A lane adds its shares
+//   one by one, so nothing has to be brought into order; pairs without shares
+//   are left as copied;
+// * the diagonal: the lists of the kept rows end to end, 64 at a time, a lane an
+//   entry; the wave adds the chunk's shares in lane order.
+// Rows longer than the stage (or next to one) and of more than kListDrops
+// dropped entries go to the workgroup form below (`heavy`).  3D Poisson 90^3, us, workgroup form ->
+// this: 60,749 rows of 33 entries (4 % dropped) 604 -> 234, 9,351 of 55 (28 %)
+// 192 -> 153.
+constexpr int kListCap = 128;
+constexpr int kListDrops = 32;       // 16: 2.77 ms a step with its solve, 8: 2.87, this 2.65
+constexpr int kListMinRows = 8192;   // fewer rows leave the device to one wave's latency
+
+__global__ void __launch_bounds__(kLB) strong_lump_list_kernel(int n, const int32_t* __restrict__ rp,
+                                                               const int32_t* __restrict__ ci,
+                                                               const double* __restrict__ v,
+                                                               const int32_t* __restrict__ dropped,
+                                                               const double* __restrict__ thr,
+                                                               const double* __restrict__ den,
+                                                               const int32_t* __restrict__ hrp,
+                                                               const int32_t* __restrict__ hci, double* hv,
+                                                               int32_t* __restrict__ heavy, int32_t* heavy_count) {
+    __shared__ double jvw[kWaves][kListCap];
+    __shared__ double kvw[kWaves][kListCap];
+    __shared__ int32_t kcw[kWaves][kListCap];        // row k's columns (and values)
+    __shared__ int32_t jcw[kWaves][kListCap];        // row j's columns (and values)
+    __shared__ int32_t ksw[kWaves][kListCap];        // the kept columns s of row k
+    __shared__ int32_t dsw[kWaves][kListCap];        // where their lists start
+    __shared__ int32_t offw[kWaves][kListCap + 1];   // the lists' offsets, end to end
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double *jv = jvw[wave], *kv = kvw[wave];
+    int32_t *kc = kcw[wave], *jc = jcw[wave], *ks = ksw[wave], *ds = dsw[wave], *off = offw[wave];
+    WAVE_ROW_LOOP(k, n) {
+        const int kb = rp[k], ke = rp[k + 1], len = ke - kb;
+        const int hb = hrp[k], he = hrp[k + 1], nk = he - hb, nd = len - nk;
+        // the row's dropped entries (k,j), a lane each: row j's place and length (0
+        // where it has no strong neighbour), j's threshold, den, a_kj
+        bool fits = len <= kListCap && nd <= kListDrops;
+        int jb_l = 0, lj_l = 0;
+        double th_l = 0.0, d_l = 0.0, a_l = 0.0;
+        if (fits && nd > 0) {
+            if (lane < nd) {
+                const int p = dropped[kb - hb + lane];
+                const int j = ci[p];
+                jb_l = rp[j];
+                lj_l = rp[j + 1] - jb_l;
+                th_l = thr[j];
+                d_l = den[p];
+                a_l = v[p];
+                if (j == k || !(th_l > 0.0)) lj_l = 0;
+            }
+            fits = __ballot(lj_l > kListCap) == 0;
+        }
+        if (!fits) {
+            if (lane == 0) heavy[atomicAdd(heavy_count, 1)] = k;
+            continue;
+        }
+        wave_lds_sync();   // the previous row's reads are done
+        int total = 0;
+        for (int base = 0; base < nk; base += 64) {
+            const int idx = base + lane;
+            int x = 0;
+            if (idx < nk) {
+                const int s = hci[hb + idx];
+                const int s0 = rp[s], h0 = hrp[s];
+                x = (rp[s + 1] - s0) - (hrp[s + 1] - h0);
+                ks[idx] = s;
+                ds[idx] = s0 - h0;
+            }
+            int incl = x;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(incl, o);
+                if (lane >= o) incl += y;
+            }
+            if (idx < nk) off[idx] = total + incl - x;
+            total += __shfl(incl, 63);
+        }
+        if (total == 0) continue;   // nothing dropped here or beside
+        if (lane == 0) off[nk] = total;
+        for (int t = lane; t < len; t += 64) {
+            kc[t] = ci[kb + t];
+            kv[t] = v[kb + t];
+        }
+        wave_lds_sync();
+        const int dpos = lower_bound_lds(ks, nk, k);
+        if (dpos >= nk || ks[dpos] != k) continue;   // every operator stores its diagonal; never taken
+        for (int t0 = dpos + 1; t0 < nk; t0 += 64) {
+            const int t = t0 + lane;
+            const bool have = t < nk;
+            const int m = have ? ks[t] : -1;
+            double acc = have ? hv[hb + t] : 0.0;
+            bool changed = false;
+            // (k,j) dropped, (j,m) strong; the next row j is requested before this one is searched
+            int c0 = -1, c1 = -1;
+            double w0 = 0.0, w1 = 0.0;
+            auto request = [&](int o) {
+                const int jb = __builtin_amdgcn_readlane(jb_l, o), lj = __builtin_amdgcn_readlane(lj_l, o);
+                if (lane < lj) {
+                    c0 = ci[jb + lane];
+                    w0 = v[jb + lane];
+                }
+                if (lane + 64 < lj) {
+                    c1 = ci[jb + 64 + lane];
+                    w1 = v[jb + 64 + lane];
+                }
+            };
+            if (nd > 0) request(0);
+            for (int o = 0; o < nd; ++o) {
+                const int lj = __builtin_amdgcn_readlane(lj_l, o);
+                wave_lds_sync();   // the last row j's reads are done
+                if (lane < lj) {
+                    jc[lane] = c0;
+                    jv[lane] = w0;
+                }
+                if (lane + 64 < lj) {
+                    jc[lane + 64] = c1;
+                    jv[lane + 64] = w1;
+                }
+                wave_lds_sync();
+                if (o + 1 < nd) request(o + 1);
+                const double th = lane_value(th_l, o);
+                const int w = lower_bound_lds(jc, lj, m);
+                if (have && w < lj && jc[w] == m && th > 0.0 && -jv[w] >= th) {
+                    acc = acc + (fabs(jv[w]) / lane_value(d_l, o)) * lane_value(a_l, o);
+                    changed = true;
+                }
+            }
+            // (m,j) dropped, (j,k) strong: a_jk read as a_kj
+            const int ob = have ? ds[t] : 0, cnt = have ? off[t + 1] - off[t] : 0;
+            for (int e0 = 0; e0 < cnt; e0 += 4) {
+                // four entries' loads in flight (the list's last one stands for those past it)
+                int j[4];
+                double d[4], a[4], th[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int p = dropped[ob + min(e0 + u, cnt - 1)];
+                    j[u] = ci[p];
+                    d[u] = den[p];
+                    a[u] = v[p];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) th[u] = thr[j[u]];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (e0 + u >= cnt || j[u] == m) continue;
+                    const int w = lower_bound_lds(kc, len, j[u]);
+                    if (w >= len || kc[w] != j[u]) continue;
+                    const double akj = kv[w];
+                    if (th[u] > 0.0 && -akj >= th[u]) {
+                        acc = acc + (fabs(akj) / d[u]) * a[u];
+                        changed = true;
+                    }
+                }
+            }
+            if (changed) {
+                hv[hb + t] = acc;
+                const int tm = find_in_row(hci, hrp[m], hrp[m + 1], k);
+                if (tm >= 0) hv[tm] = acc;   // always found: the kept pattern is symmetric
+            }
+        }
+        // the diagonal
+        double acc = hv[hb + dpos];
+        for (int f0 = 0; f0 < total; f0 += 64) {
+            const int f = f0 + lane;
+            bool has = false;
+            double c = 0.0;
+            if (f < total) {
+                int lo = 0, hi = nk;   // off[lo] <= f < off[lo + 1]
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (off[mid] <= f) lo = mid;
+                    else hi = mid;
+                }
+                const int s = ks[lo], p = dropped[ds[lo] + f - off[lo]];
+                const int j = ci[p];
+                const double d = den[p], a = v[p];
+                if (j != s && s == k) {
+                    const double th = thr[j];
+                    if (d == 0.0) {
+                        c = a;   // no strong neighbour kept: the whole entry
+                        has = true;
+                    } else if (th > 0.0 && -a >= th) {
+                        c = (fabs(a) / d) * a;   // the share to k itself, a_jk = a_kj
+                        has = true;
+                    }
+                } else if (j != s && d != 0.0) {
+                    const int r = lower_bound_lds(kc, len, j);
+                    if (r < len && kc[r] == j) {
+                        const double th = thr[j], akj = kv[r];
+                        if (th > 0.0 && -akj >= th) {
+                            c = -((fabs(akj) / d) * a);   // a - c == a + (-c) exactly
+                            has = true;
+                        }
+                    }
+                }
+            }
+            acc = ordered_add(acc, has, c);
+        }
+        if (lane == 0) hv[hb + dpos] = acc;
+    }
+}
+
+// One workgroup per row k (the listed ones, or all), row k of A (columns, values, keep flags,
 // denominators, and the thresholds of its columns) staged in LDS.
 // * (k,m), m > k, one wave each, its lanes over row m (coalesced): a lane
 //   finds its column j in the staged row k by a binary search in LDS and
@@ -384,7 +609,9 @@ __global__ void __launch_bounds__(LB) __attribute__((amdgpu_waves_per_eu(8, 8)))
                                                                const double* __restrict__ den,
                                                                const int32_t* __restrict__ hrp,
                                                                const int32_t* __restrict__ hci,
-                                                               double* __restrict__ hv) {
+                                                               double* __restrict__ hv,
+                                                               const int32_t* __restrict__ heavy,
+                                                               const int32_t* __restrict__ heavy_count) {
     __shared__ int32_t kc[kWideCap];
     __shared__ double kv[kWideCap];
     __shared__ double kd[kWideCap];
@@ -398,7 +625,9 @@ __global__ void __launch_bounds__(LB) __attribute__((amdgpu_waves_per_eu(8, 8)))
     __shared__ int wsum[(LB / 64)];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    for (int k = blockIdx.x; k < n; k += gridDim.x) {
+    const int todo = heavy ? *heavy_count : n;   // listed rows, or all
+    for (int it = blockIdx.x; it < todo; it += gridDim.x) {
+        const int k = heavy ? heavy[it] : it;
         const int kb = rp[k], ke = rp[k + 1], len = ke - kb;
         if (len > kWideCap) {
             if (wave == 0) strong_lump_row(k, lane, rp, ci, v, keep, thr, den, hrp, hci, hv);
@@ -625,9 +854,10 @@ __global__ void __launch_bounds__(LB) __attribute__((amdgpu_waves_per_eu(8, 8)))
 }  // namespace
 
 void launch_compact_copy(int n, const int32_t* rp, const int32_t* ci, const double* v, const uint8_t* keep,
-                         const int32_t* new_rp, int32_t* new_ci, double* new_v, hipStream_t st) {
+                         const int32_t* new_rp, int32_t* new_ci, double* new_v, const LumpLists& lists,
+                         hipStream_t st) {
     hipLaunchKernelGGL(compact_copy_kernel, dim3(wave_grid_of(n)), dim3(kLB), 0, st, n, rp, ci, v, keep, new_rp,
-                       new_ci, new_v);
+                       new_ci, new_v, lists.dropped, lists.heavy + n);
 }
 
 void launch_lump_threshold(int n, const int32_t* rp, const int32_t* ci, const double* v, double theta,
@@ -649,10 +879,11 @@ int row_grid_of(int n) { return std::max(1, std::min(n, 65536)); }
 }  // namespace
 
 void launch_lump_den(int n, const int32_t* rp, const int32_t* ci, const double* v, const uint8_t* keep,
-                     const double* thr, double* den, double mean_row, const LumpShapes& ls, hipStream_t st) {
+                     const int32_t* hrp, const int32_t* hci, const LumpLists& lists, const double* thr, double* den,
+                     double mean_row, const LumpShapes& ls, hipStream_t st) {
     if (use_wide(ls, mean_row) && use_den_wave(ls, n, mean_row))
-        hipLaunchKernelGGL(lump_den_wave_kernel, dim3(wave_grid_of(n)), dim3(kLB), 0, st, n, rp, ci, v, keep, thr,
-                           den);
+        hipLaunchKernelGGL(lump_den_wave_kernel, dim3(wave_grid_of(n)), dim3(kLB), 0, st, n, rp, ci, v, keep, hrp, hci,
+                           lists.dropped, thr, den);
     else if (use_wide(ls, mean_row))
         hipLaunchKernelGGL(lump_den_wide_kernel, dim3(row_grid_of(n)), dim3(kLB), 0, st, n, rp, ci, v, keep, thr,
                            den);
@@ -661,17 +892,27 @@ void launch_lump_den(int n, const int32_t* rp, const int32_t* ci, const double* 
 }
 
 void launch_strong_lump(int n, const int32_t* rp, const int32_t* ci, const double* v, const uint8_t* keep,
-                        const double* thr, const double* den, const int32_t* hrp, const int32_t* hci, double* hv,
-                        double mean_row, const LumpShapes& ls, hipStream_t st) {
-    if (use_wide(ls, mean_row) && n < ls.small_rows)
-        hipLaunchKernelGGL(strong_lump_wide_kernel<1024>, dim3(row_grid_of(n)), dim3(1024), 0, st, n, rp, ci, v, keep,
-                           thr, den, hrp, hci, hv);
-    else if (use_wide(ls, mean_row))
-        hipLaunchKernelGGL(strong_lump_wide_kernel<kLB>, dim3(row_grid_of(n)), dim3(kLB), 0, st, n, rp, ci, v, keep,
-                           thr, den, hrp, hci, hv);
-    else
+                        const LumpLists& lists, const double* thr, const double* den, const int32_t* hrp,
+                        const int32_t* hci, double* hv, double mean_row, const LumpShapes& ls, hipStream_t st) {
+    if (!use_wide(ls, mean_row)) {
         hipLaunchKernelGGL(strong_lump_kernel, dim3(wave_grid_of(n)), dim3(kLB), 0, st, n, rp, ci, v, keep, thr, den,
                            hrp, hci, hv);
+        return;
+    }
+    int32_t *heavy = nullptr, *count = nullptr;
+    if (n >= kListMinRows) {
+        heavy = lists.heavy;
+        count = lists.heavy + n;
+        hipLaunchKernelGGL(strong_lump_list_kernel, dim3(wave_grid_of(n)), dim3(kLB), 0, st, n, rp, ci, v,
+                           lists.dropped, thr, den, hrp, hci, hv, heavy, count);
+    }
+    const dim3 grid(heavy ? std::min(row_grid_of(n), 4096) : row_grid_of(n));
+    if (n < ls.small_rows)
+        hipLaunchKernelGGL(strong_lump_wide_kernel<1024>, grid, dim3(1024), 0, st, n, rp, ci, v, keep, thr, den, hrp,
+                           hci, hv, heavy, count);
+    else
+        hipLaunchKernelGGL(strong_lump_wide_kernel<kLB>, grid, dim3(kLB), 0, st, n, rp, ci, v, keep, thr, den, hrp,
+                           hci, hv, heavy, count);
 }
 
 }  // namespace amg355

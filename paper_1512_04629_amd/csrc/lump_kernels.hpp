@@ -14,13 +14,12 @@
 namespace amg355 {
 
 // Launch shapes of the lumping kernels; every choice gives the same bits.
-// Rows of mean length >= wide_mean_row run a workgroup per row with the row
-// staged in LDS (default 0: every level; it was the faster on every level of
-// the 3D Poisson hierarchies measured, 34 to 108 entries a row), shorter
-// ones a wave per row.  Denominators: a wave per row with its own LDS stage
-// on levels of at least 16,384 rows of fewer than 80 entries on average, or,
-// if den_wave_mean_row >= 0, wherever mean_row < den_wave_mean_row.  The
-// share kernel's workgroups have 1,024 threads on levels of fewer than
+// Levels of mean row length >= wide_mean_row run by the lists of dropped
+// entries, rows of many a workgroup each with the row staged in LDS (default 0:
+// every level), others a wave per row.  Denominators: a wave per row with its
+// own LDS stage on levels of at least 16,384 rows of fewer than 80 entries on
+// average, or, if den_wave_mean_row >= 0, wherever mean_row < den_wave_mean_row.
+// The share kernel's workgroups have 1,024 threads on levels of fewer than
 // small_rows rows (measured on 3D Poisson: 821 and 129 rows 263 -> 156 and
 // 141 -> 90 us; 5,191 rows 372 -> 542 us), 256 otherwise.
 struct LumpShapes {
@@ -29,10 +28,18 @@ struct LumpShapes {
     int small_rows = 4096;
 };
 
+// The positions of the dropped entries, row i's from rp[i] - new_rp[i] on (as
+// many entries as a), and the rows of many (n entries, then their number).
+struct LumpLists {
+    int32_t *dropped, *heavy;
+};
+
 // kept entries of a (keep flags per entry) copied unchanged into the
-// pattern new_rp / new_ci / new_v (new_rp: scan of the kept counts)
+// pattern new_rp / new_ci / new_v (new_rp: scan of the kept counts), the others
+// listed; heavy[n] = 0
 void launch_compact_copy(int n, const int32_t* rp, const int32_t* ci, const double* v, const uint8_t* keep,
-                         const int32_t* new_rp, int32_t* new_ci, double* new_v, hipStream_t st);
+                         const int32_t* new_rp, int32_t* new_ci, double* new_v, const LumpLists& lists,
+                         hipStream_t st);
 // thr[j] = theta * max_{m != j}(-a_jm), or -1 if that maximum is not positive
 // (the strength of the setup: (j,m) strong iff m != j and -a_jm >= thr[j] > 0)
 void launch_lump_threshold(int n, const int32_t* rp, const int32_t* ci, const double* v, double theta,
@@ -40,12 +47,13 @@ void launch_lump_threshold(int n, const int32_t* rp, const int32_t* ci, const do
 // den[p] for every dropped off-diagonal entry p = (i,j): the sum, in
 // ascending m, of |a_jm| over m strong for j and kept in row i (0: none)
 void launch_lump_den(int n, const int32_t* rp, const int32_t* ci, const double* v, const uint8_t* keep,
-                     const double* thr, double* den, double mean_row, const LumpShapes& ls, hipStream_t st);
+                     const int32_t* hrp, const int32_t* hci, const LumpLists& lists, const double* thr, double* den,
+                     double mean_row, const LumpShapes& ls, hipStream_t st);
 // adds every row's shares to the copied kept entries hrp / hci / hv; a must
 // be bitwise symmetric with a symmetric keep set (a_jm is read as a_mj).
 // Launch shapes as LumpShapes selects.
 void launch_strong_lump(int n, const int32_t* rp, const int32_t* ci, const double* v, const uint8_t* keep,
-                        const double* thr, const double* den, const int32_t* hrp, const int32_t* hci, double* hv,
-                        double mean_row, const LumpShapes& ls, hipStream_t st);
+                        const LumpLists& lists, const double* thr, const double* den, const int32_t* hrp,
+                        const int32_t* hci, double* hv, double mean_row, const LumpShapes& ls, hipStream_t st);
 
 }  // namespace amg355
