@@ -184,7 +184,8 @@ __global__ __launch_bounds__(kGsThreads) void hybrid_gs_staged_kernel(int n, con
 // into terms in LDS, while the first runs the current one: the product
 // a_ij xold_j where the old value is used, a_ij and the row's place in the
 // chunk where the new one is, 0 for the diagonal, whose subtraction changes
-// nothing.  In the chain a row's terms lie one to a lane, loaded two rows
+// nothing; and subtract, lane by row, the terms that come before a row's first
+// new value.  In the chain a row's other terms lie one to a lane, loaded two rows
 // ahead, the new values they need one row ahead (the value of the row before
 // from a register), and are subtracted in ascending column order by one
 // multiply-add each, acc = (-1) t + acc, the term taken from its lane by the
@@ -255,10 +256,12 @@ __device__ __forceinline__ double sub_terms(double acc, double t, int len, doubl
 // one unit in the last place by an exact remainder is the rounded quotient;
 // the first correction brings it there); far from the ends of the exponent
 // range the remainders are exact, elsewhere (and for 0, infinities and NaN) the
-// division itself.
+// division itself.  y = 0 says that d is not in the range.
+__device__ __forceinline__ bool mid_range(double a) {   // exponents -400 to 399, from the bits
+    return (unsigned)((__double2hiint(a) & 0x7fffffff) - (623 << 20)) < (800u << 20);
+}
 __device__ __forceinline__ double quotient(double a, double d, double y) {
-    const double aa = fabs(a), ad = fabs(d);
-    if (aa >= 0x1p-400 && aa <= 0x1p400 && ad >= 0x1p-400 && ad <= 0x1p400) {
+    if (mid_range(a) && __double2hiint(y) != 0) {
         double q = a * y;
         q = __builtin_fma(__builtin_fma(-d, q, a), y, q);
         return __builtin_fma(__builtin_fma(-d, q, a), y, q);
@@ -267,20 +270,21 @@ __device__ __forceinline__ double quotient(double a, double d, double y) {
 }
 
 struct __align__(16) GsRow {      // a staged row
-    double b, d, y;               // right-hand side, diagonal, its reciprocal
+    double b, d, y;               // right-hand side, diagonal, its reciprocal (0: divide)
     int32_t off, len;             // its terms in the strip; len < 0: too long, not staged
 };
 
-template <bool FORWARD, int W, int NP>
+template <bool FORWARD, int W, int NP, bool AHEAD>
 __global__ __launch_bounds__(64 * (1 + NP)) void hybrid_gs_chain_kernel(
     int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci, const double* __restrict__ v,
     const double* __restrict__ b, const double* __restrict__ xold, double* __restrict__ xnew, int block, int chunk) {
     constexpr int G = 64 / W;               // chunks of the workgroup
     constexpr int E = 8;                    // entries of a strip per staging lane
     constexpr int S = W * E * NP;           // entries per strip
-    __shared__ double term[2][G][S];
-    __shared__ int16_t tag[2][G][S];
-    __shared__ GsRow rows[2][G][W];
+    // one more of each: what a lane without an entry, or a step without a row, reads
+    __shared__ double term[2][G][S + 1];
+    __shared__ int16_t tag[2][G][S + 1];
+    __shared__ GsRow rows[2][G][W + 1];
     __shared__ int32_t rows_in[2][G];
     __shared__ int32_t soff[NP][G][W];
     extern __shared__ double ly_all[];      // new values of the chunks' rows
@@ -288,7 +292,15 @@ __global__ __launch_bounds__(64 * (1 + NP)) void hybrid_gs_chain_kernel(
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int64_t start = ((int64_t)blockIdx.x * G + g) * chunk;
     const int r0 = (int)min(start, (int64_t)n), nr = (int)min((int64_t)chunk, (int64_t)n - r0);
-    double* const ly = ly_all + (size_t)g * chunk;
+    double* const ly = ly_all + (size_t)g * (chunk + 1);   // ly[chunk]: not a row
+    if (threadIdx.x < 2 * G) {
+        const int u = (int)threadIdx.x / G, w = (int)threadIdx.x % G;
+        term[u][w][S] = 0.0;
+        tag[u][w][S] = kGsOld;
+        rows[u][w][W] = GsRow{0.0, 1.0, 1.0, 0, 0};
+    }
+    // strip entries of a staging wave: alternate rows of W, or its share end to end
+    auto place = [&](int e, int part) { return lane + W * (AHEAD ? e + part * E : e * NP + part); };
     // row visited k-th of the chunk, relative to r0
     auto row_at = [&](int k) { return FORWARD ? k : nr - 1 - k; };
     // x of the group's lane l
@@ -317,22 +329,21 @@ __global__ __launch_bounds__(64 * (1 + NP)) void hybrid_gs_chain_kernel(
         const int ibs = il - il % block;     // the row's block in the chunk
         soff[part][g][lane] = lane < R ? beg - p0 : INT32_MAX;
         if (part == 0) {
-            GsRow& q = rows[buf][g][lane];
-            if (lane < R) {
+            if (lane >= R) rows[buf][g][lane] = GsRow{0.0, 1.0, 1.0, 0, R == 0 && lane == 0 ? -1 : 0};
+            if (lane == 0) rows_in[buf][g] = lng ? 1 : R;
+            if (!AHEAD && lane < R) {
+                GsRow& q = rows[buf][g][lane];
                 q.b = bi;
                 q.off = beg - p0;
                 q.len = end - beg;
-            } else if (lane == 0) {
-                q.len = -1;
             }
-            if (lane == 0) rows_in[buf][g] = lng ? 1 : R;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         int jj[E], kk[E];
         double aa[E], xx[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            const int q = lane + W * (e * NP + part);
+            const int q = place(e, part);
             jj[e] = q < total ? ci[p0 + q] : min(r0, n - 1);
             aa[e] = q < total ? v[p0 + q] : 0.0;
         }
@@ -347,19 +358,29 @@ __global__ __launch_bounds__(64 * (1 + NP)) void hybrid_gs_chain_kernel(
             for (int e = 0; e < E; ++e) {
                 const int m = kk[e] + step;
                 const int st = m < R ? soff[part][g][FORWARD ? m : R - 1 - m] : INT32_MAX;
-                if (st <= lane + W * (e * NP + part)) kk[e] = m;
+                if (st <= place(e, part)) kk[e] = m;
             }
         }
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const int k = FORWARD ? kk[e] : max(R - 1 - kk[e], 0);
             const int bs = __shfl(ibs, k, W);
-            const int q = lane + W * (e * NP + part);
+            const int q = place(e, part);
             if (q < total) {
                 const int i = row_at(done + k), j = jj[e] - r0;
                 if (j == i) {
                     rows[buf][g][k].d = aa[e];
-                    rows[buf][g][k].y = 1.0 / aa[e];
+                    // With many chunks of 64 lanes the registers bound the chains in
+                    // flight: divided without a branch (82 registers, 104 with;
+                    // 101 and 114 us on 2,731 chunks).  Elsewhere the branch, which
+                    // shortens the staging (64^3, blocks of 64, a solve: 5.82 and
+                    // 5.94 ms).
+                    if constexpr (W == 64 && !AHEAD) {
+                        const double y = 1.0 / aa[e];
+                        rows[buf][g][k].y = mid_range(aa[e]) ? y : 0.0;
+                    } else {
+                        rows[buf][g][k].y = mid_range(aa[e]) ? 1.0 / aa[e] : 0.0;
+                    }
                     tag[buf][g][q] = kGsDiag;
                     term[buf][g][q] = 0.0;
                 } else {
@@ -368,6 +389,43 @@ __global__ __launch_bounds__(64 * (1 + NP)) void hybrid_gs_chain_kernel(
                     tag[buf][g][q] = fresh ? (int16_t)j : kGsOld;
                     term[buf][g][q] = fresh ? aa[e] : aa[e] * xx[e];
                 }
+            }
+        }
+        // AHEAD: a row's terms before the first that waits for a new value are
+        // subtracted here (a lane a row, in order): the chain starts at that one.
+        // A row whose entries two waves staged keeps them all.
+        if (AHEAD && lane < R) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const int off = beg - p0, len = end - beg;
+            // (the wave that staged its first entry keeps the row)
+            const bool mine = off + len <= (part + 1) * (W * E);
+            if (part == min(off / (W * E), NP - 1)) {
+                double acc = bi;
+                int o = off;
+                const int stop = off + len;
+                bool open = mine;
+                while (open && o < stop) {
+                    double t[4];
+                    int a[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int at = min(o + u, stop - 1);
+                        t[u] = term[buf][g][at];
+                        a[u] = o + u < stop ? (int)tag[buf][g][at] : 0;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        open = open && a[u] < 0;
+                        if (open) {
+                            acc = acc - t[u];
+                            ++o;
+                        }
+                    }
+                }
+                GsRow& q = rows[buf][g][lane];
+                q.b = acc;
+                q.off = o;
+                q.len = stop - o;
             }
         }
         done += lng ? 1 : R;
@@ -412,19 +470,21 @@ __global__ __launch_bounds__(64 * (1 + NP)) void hybrid_gs_chain_kernel(
             if (lng) long_row();
         }
         const int Rs = lng ? 0 : R;         // staged rows of this group
-        auto load = [&](int k, double& t, int& q, GsRow& h) {
-            const bool have = k < Rs;
-            h = row[have ? k : 0];
-            if (!have) h.len = 0;
-            const bool in = lane < h.len;
-            t = in ? tm[h.off + lane] : 0.0;
-            q = in ? (int)tg[h.off + lane] : (int)kGsOld;
+        // headers three rows ahead, terms two, new values one: nothing a row asks
+        // for is waited for in the same step.  No branches either: lanes and steps
+        // without an entry read and write spare places, so that the compiler
+        // counts what is in flight.
+        auto head = [&](int k) { return row[min(k, W)]; };
+        auto load = [&](const GsRow& h, double& t, int& q) {
+            const int p = lane < h.len ? h.off + lane : S;
+            t = tm[p];
+            q = (int)tg[p];
         };
         double t0, t1, y0;
         int q0, q1;
-        GsRow h0, h1;
-        load(0, t0, q0, h0);
-        load(1, t1, q1, h1);
+        GsRow h0 = head(0), h1 = head(1), h2 = head(2);
+        load(h0, t0, q0);
+        load(h1, t1, q1);
         y0 = ly[max(q0, 0)];
         int prev = -1;
         double prev_x = 0.0;
@@ -432,8 +492,8 @@ __global__ __launch_bounds__(64 * (1 + NP)) void hybrid_gs_chain_kernel(
             const double y1 = ly[max(q1, 0)];
             double t2;
             int q2;
-            GsRow h2;
-            load(k + 2, t2, q2, h2);
+            load(h2, t2, q2);
+            const GsRow h3 = head(k + 3);
             const double t = q0 >= 0 ? t0 * (q0 == prev ? prev_x : y0) : t0;
             double acc = sub_terms<W>(h0.b, t, h0.len, m1);
             for (int o = W; __any(o < h0.len); o += W) {
@@ -446,7 +506,7 @@ __global__ __launch_bounds__(64 * (1 + NP)) void hybrid_gs_chain_kernel(
             }
             const double xi = quotient(acc, h0.d, h0.y);
             const int il = row_at(at + k);
-            if (lane == 0 && k < Rs) ly[il] = xi;
+            ly[k < Rs ? il : chunk] = xi;      // every lane the same
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the store before later rows' loads
             prev = il;
             prev_x = xi;
@@ -457,6 +517,7 @@ __global__ __launch_bounds__(64 * (1 + NP)) void hybrid_gs_chain_kernel(
             t1 = t2;
             q1 = q2;
             h1 = h2;
+            h2 = h3;
         }
         if (lane < Rs) {
             const int il = row_at(at + lane);
@@ -490,13 +551,13 @@ __global__ __launch_bounds__(64 * (1 + NP)) void hybrid_gs_chain_kernel(
 // workgroup, else 64.
 // A forward sweep in us, one lane per block (staged form) -> chain form, 3D
 // Poisson hierarchies, levels 0, 1, 2, ...:
-//   64^3, blocks of 64:   102 236 279 779 1298 675 -> 31 53 42 44 62 43
-//   128^3, blocks of 64:  623 1493 942 879 1782 1760 902 -> 153 152 102 45 76 76 50
-//   128^3, blocks of 16:  190 418 254 160 240 222 136 -> 154 152 102 32 27 25 19
+//   64^3, blocks of 64:   102 236 279 779 1298 675 -> 28 35 38 40 56 42
+//   128^3, blocks of 64:  623 1493 942 879 1782 1760 902 -> 146 152 101 43 74 74 46
+//   128^3, blocks of 16:  190 418 254 160 240 222 136 -> 149 152 101 31 26 25 19
 //   128^3, blocks of 8:   126 230 130 76 295 290 80 -> 154 153 102 33 19 17 12
 //   128^3, blocks of 2:   82 124 54 23 91 95 27 -> 153 153 102 30 20 9 9
 //   64^3, blocks of 1024 (per-block form): 4000 11372 15617 13706 9643 996 ->
-//                         374 434 498 569 450 64
+//                         336 348 405 500 412 59
 // 64 lanes to a chunk on the two finest levels, blocks of 64: 99 and 77 us at
 // 64^3, 658 and 409 at 128^3; 16 lanes on the third (rows of 32 entries, 342
 // chunks at 64^3): 74 us.
@@ -506,19 +567,32 @@ constexpr int kGsChainRows = 64;
 constexpr int64_t kGsChainChunks = 2048;
 constexpr int64_t kGsShortRowChunks = 1024;
 constexpr double kGsShortRow = 24.0;
+// More staging waves where a chunk takes several strips and the chunks do not
+// fill the machine (then they only share its instructions): 16 lanes, one wave or
+// two (rows of 8: sixteen rows, a strip, fit one wave's); 64 lanes, two or four.
+// Terms are subtracted ahead there and on rows of up to 8, not where the chunk is
+// one strip, which the chain would only wait for.  us, one wave (16 lanes) or two
+// and nothing ahead -> this rule: 64^3, blocks of 64, levels 0 to 4: 31 53 42 44 62
+// -> 28 35 38 40 56.  Where the rule says no: four waves on 2,731 chunks of 64 rows
+// 103 -> 233; terms ahead on 16,384 chunks of rows above 8 155 -> 173, on short
+// chunks (blocks of 2, 128^3, level 4) 20 -> 46.
+constexpr double kGsOneWaveRow = 8.0;
+constexpr int kGsLongChunk = 32;
+constexpr double kGsStage16 = 256.0, kGsStage64 = 1024.0;   // entries of two waves' strip
+constexpr int64_t kGsFewChunks16 = 4096, kGsFewChunks64 = 512;
 
-template <int W, int NP>
+template <int W, int NP, bool AHEAD>
 static void launch_chain(bool forward, int n, const int32_t* rp, const int32_t* ci, const double* v, const double* b,
                          const double* xold, double* xnew, int block, int chunk, hipStream_t st) {
     constexpr int G = 64 / W;
     const int64_t per = (int64_t)chunk * G;
     const dim3 grid((unsigned)((n + per - 1) / per)), threads(64 * (1 + NP));
-    const size_t lds = sizeof(double) * (size_t)per;
+    const size_t lds = sizeof(double) * (size_t)(G * (chunk + 1));
     if (forward)
-        hipLaunchKernelGGL((hybrid_gs_chain_kernel<true, W, NP>), grid, threads, lds, st, n, rp, ci, v, b, xold, xnew,
+        hipLaunchKernelGGL((hybrid_gs_chain_kernel<true, W, NP, AHEAD>), grid, threads, lds, st, n, rp, ci, v, b, xold, xnew,
                            block, chunk);
     else
-        hipLaunchKernelGGL((hybrid_gs_chain_kernel<false, W, NP>), grid, threads, lds, st, n, rp, ci, v, b, xold, xnew,
+        hipLaunchKernelGGL((hybrid_gs_chain_kernel<false, W, NP, AHEAD>), grid, threads, lds, st, n, rp, ci, v, b, xold, xnew,
                            block, chunk);
 }
 
@@ -531,9 +605,19 @@ void launch_hybrid_gs(bool forward, int n, const int32_t* rp, const int32_t* ci,
         const int64_t per = std::max<int64_t>(1, std::min<int64_t>(most, n / (kGsChainChunks * block)));
         const int chunk = (int)(per * block);
         const int64_t chunks = ((int64_t)n + chunk - 1) / chunk;
-        if (mean_row <= kGsShortRow && chunks >= kGsShortRowChunks)
-            launch_chain<16, 1>(forward, n, rp, ci, v, b, xold, xnew, block, chunk, st);
-        else launch_chain<64, 2>(forward, n, rp, ci, v, b, xold, xnew, block, chunk, st);
+        // (blocks of a few rows: the chain is short, whatever the staging)
+        const double entries = chunk >= kGsLongChunk ? mean_row * chunk : 0.0;
+        if (mean_row <= kGsShortRow && chunks >= kGsShortRowChunks) {
+            if (mean_row > kGsOneWaveRow && entries > kGsStage16 && chunks <= kGsFewChunks16)
+                launch_chain<16, 2, true>(forward, n, rp, ci, v, b, xold, xnew, block, chunk, st);
+            else if (mean_row <= kGsOneWaveRow && entries > kGsStage16)
+                launch_chain<16, 1, true>(forward, n, rp, ci, v, b, xold, xnew, block, chunk, st);
+            else launch_chain<16, 1, false>(forward, n, rp, ci, v, b, xold, xnew, block, chunk, st);
+        } else if (entries > kGsStage64 && chunks <= kGsFewChunks64) {
+            launch_chain<64, 4, true>(forward, n, rp, ci, v, b, xold, xnew, block, chunk, st);
+        } else {
+            launch_chain<64, 2, false>(forward, n, rp, ci, v, b, xold, xnew, block, chunk, st);
+        }
         return;
     }
     if (block <= kGsMaxRows) {
