@@ -390,9 +390,20 @@ __global__ void __launch_bounds__(kLB) strong_lump_kernel(int n, const int32_t* 
 // dropped entries go to the workgroup form below (`heavy`).  3D Poisson 90^3, us, workgroup form ->
 // this: 60,749 rows of 33 entries (4 % dropped) 604 -> 234, 9,351 of 55 (28 %)
 // 192 -> 153.
+// Where more than a third of a level's entries are dropped all its rows go there:
+// a wave's work grows with its row's drops, the workgroup's hardly.  A level's
+// sparsification in us, workgroup form and lists, by the share dropped: 59,438
+// rows of 27, 27 % 609 and 524, 37 % 604 and 601, 56 % 612 and 747; 27,542 of 57,
+// 27 % 721 and 567, 39 % 724 and 705, 49 % 714 and 823; 174,772 of 34, 39 % 2324
+// and 2187, 50 % 2385 and 2595; 9,318 of 40, 20 % 194 and 166, 43 % 196 and 253.
 constexpr int kListCap = 128;
 constexpr int kListDrops = 32;       // 16: 2.77 ms a step with its solve, 8: 2.87, this 2.65
 constexpr int kListMinRows = 8192;   // fewer rows leave the device to one wave's latency
+
+// (the same answer in every workgroup of both kernels, from counts on the device)
+__device__ __forceinline__ bool mostly_dropped(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ hrp) {
+    return 3 * (int64_t)(rp[n] - hrp[n]) > (int64_t)rp[n];
+}
 
 __global__ void __launch_bounds__(kLB) strong_lump_list_kernel(int n, const int32_t* __restrict__ rp,
                                                                const int32_t* __restrict__ ci,
@@ -413,6 +424,7 @@ __global__ void __launch_bounds__(kLB) strong_lump_list_kernel(int n, const int3
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double *jv = jvw[wave], *kv = kvw[wave];
     int32_t *kc = kcw[wave], *jc = jcw[wave], *ks = ksw[wave], *ds = dsw[wave], *off = offw[wave];
+    if (mostly_dropped(n, rp, hrp)) return;
     WAVE_ROW_LOOP(k, n) {
         const int kb = rp[k], ke = rp[k + 1], len = ke - kb;
         const int hb = hrp[k], he = hrp[k + 1], nk = he - hb, nd = len - nk;
@@ -610,7 +622,7 @@ __global__ void __launch_bounds__(LB) __attribute__((amdgpu_waves_per_eu(8, 8)))
                                                                const int32_t* __restrict__ hrp,
                                                                const int32_t* __restrict__ hci,
                                                                double* __restrict__ hv,
-                                                               const int32_t* __restrict__ heavy,
+                                                               const int32_t* heavy,
                                                                const int32_t* __restrict__ heavy_count) {
     __shared__ int32_t kc[kWideCap];
     __shared__ double kv[kWideCap];
@@ -625,6 +637,7 @@ __global__ void __launch_bounds__(LB) __attribute__((amdgpu_waves_per_eu(8, 8)))
     __shared__ int wsum[(LB / 64)];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
+    if (heavy && mostly_dropped(n, rp, hrp)) heavy = nullptr;
     const int todo = heavy ? *heavy_count : n;   // listed rows, or all
     for (int it = blockIdx.x; it < todo; it += gridDim.x) {
         const int k = heavy ? heavy[it] : it;
@@ -906,7 +919,10 @@ void launch_strong_lump(int n, const int32_t* rp, const int32_t* ci, const doubl
         hipLaunchKernelGGL(strong_lump_list_kernel, dim3(wave_grid_of(n)), dim3(kLB), 0, st, n, rp, ci, v,
                            lists.dropped, thr, den, hrp, hci, hv, heavy, count);
     }
-    const dim3 grid(heavy ? std::min(row_grid_of(n), 4096) : row_grid_of(n));
+    // a workgroup a row also where few rows may be listed: 4,096 looping took
+    // 2569 instead of 2373 us where all rows come here (174,772), and save 10
+    // where none does
+    const dim3 grid(row_grid_of(n));
     if (n < ls.small_rows)
         hipLaunchKernelGGL(strong_lump_wide_kernel<1024>, grid, dim3(1024), 0, st, n, rp, ci, v, keep, thr, den, hrp,
                            hci, hv, heavy, count);
