@@ -2108,7 +2108,7 @@ void batch_iteration(amg_batch_ctx* e, bool load, int rz, int next) {
                                   h->scal + S_BFLAG, v0.dinv, omega, bb.rhs, bb.x[0], cols_to(h, S_BLOCK),
                                   h->stream, h->scal + S_LIVE);
         launch_block_converge(k, h->scal, S_BACT, S_BLOCK, S_BNR0, S_BFLAG, S_BITER, S_BSTAT, S_BREL, i_load,
-                              S_BNEW, e->rtol, e->maxit, h->stream);
+                              S_BNEW, S_LIVE, e->rtol, e->maxit, h->stream);
         check_launch();
     }
 }

@@ -272,6 +272,7 @@ __global__ __launch_bounds__(kBlk) void block_row_kernel(CsrT<T> a, const T* __r
     const int c0 = (threadIdx.x % LPR) * V;
     // columns past the live prefix are left as they are; their lanes still
     // load and hand round their rows' entries (gathering the first columns)
+    if (live && *live == 0.0) return;   // every column is finished
     const bool dead = live && c0 >= (int)*live;
     for (TileWalk w = tile_walk(ntiles); w.t < w.end; w.t += w.stride) {
         const int t = w.t;
@@ -341,6 +342,7 @@ __global__ __launch_bounds__(kBlk) void block_outer_kernel(CsrView a, const doub
     const int lb = logical_block();
     const int sub = threadIdx.x / LPR;
     const int c0 = (threadIdx.x % LPR) * 2;
+    if (live && *live == 0.0) return;   // every column is finished
     const bool dead = live && c0 >= (int)*live;   // see block_row_kernel
     double n0 = 0.0, n1 = 0.0;
     for (TileWalk w = tile_walk(ntiles); w.t < w.end; w.t += w.stride) {
@@ -408,6 +410,7 @@ __global__ __launch_bounds__(kBlk) void block_spmv_dot_kernel(CsrView a, const d
     const int lb = logical_block();
     const int sub = threadIdx.x / LPR;
     const int c0 = (threadIdx.x % LPR) * 2;
+    if (live && *live == 0.0) return;   // every column is finished
     const bool dead = live && c0 >= (int)*live;   // see block_row_kernel
     double d[2] = {0.0, 0.0};
     for (TileWalk w = tile_walk(ntiles); w.t < w.end; w.t += w.stride) {
@@ -601,6 +604,7 @@ __global__ __launch_bounds__(kBlk) void block_sweep_dot_kernel(CsrT<T> a, const 
     const int lb = logical_block();
     const int sub = threadIdx.x / LPR;
     const int c0 = (threadIdx.x % LPR) * V;
+    if (live && *live == 0.0) return;   // every column is finished
     const bool dead = live && c0 >= (int)*live;   // see block_row_kernel
     double d[V];
 #pragma unroll
@@ -663,36 +667,43 @@ __global__ __launch_bounds__(kBlk) void block_copy_dot_kernel(int n, const T* __
 // reset; with a zero right-hand side it stops at once with x = 0.  State per
 // column: scal[i_stat+c] = 0 running, 1 converged, 2 maxit reached,
 // 3 breakdown; scal[i_rel+c] = ||r|| / ||b|| after the iteration.
+// When no column is active any more the live count becomes 0 and the row kernels
+// of the step's remaining iterations return: a step holds a whole number of
+// iterations (8 and 8 where a request on 47^3 needs 10).  Without -> with, 20
+// requests on 47^3 in FP64 6.33 -> 4.93 ms, 24 in FP32 5.59 -> 4.51.
 __global__ __launch_bounds__(64) void block_converge_kernel(int k, double* __restrict__ scal, int i_act,
                                                             int i_norm, int i_nr0, int i_flag, int i_iter,
                                                             int i_stat, int i_rel, int i_load, int i_new,
-                                                            double rtol, int maxit) {
+                                                            int i_live, double rtol, int maxit) {
     const int c = threadIdx.x;
-    if (c >= k || scal[i_act + c] == 0.0) return;
-    if (i_load >= 0 && scal[i_load + c] != 0.0) {
-        scal[i_nr0 + c] = scal[i_new + c];
-        scal[i_iter + c] = 0.0;
-        scal[i_stat + c] = 0.0;
+    bool on = c < k && scal[i_act + c] != 0.0;
+    if (on) {
+        if (i_load >= 0 && scal[i_load + c] != 0.0) {
+            scal[i_nr0 + c] = scal[i_new + c];
+            scal[i_iter + c] = 0.0;
+            scal[i_stat + c] = 0.0;
+        }
+        const double n0 = sqrt(scal[i_nr0 + c]);
+        double stat = 0.0, rel = 0.0;
+        if (n0 == 0.0) {
+            stat = 1.0;
+        } else {
+            const double it = scal[i_iter + c] + 1.0;
+            scal[i_iter + c] = it;
+            const double nr = sqrt(scal[i_norm + c]);
+            if (scal[i_flag + c] != 0.0 || !isfinite(nr) || !isfinite(n0)) stat = 3.0;
+            else if (nr <= rtol * n0) stat = 1.0;
+            else if (it >= (double)maxit) stat = 2.0;
+            rel = nr / n0;
+        }
+        scal[i_rel + c] = rel;
+        if (stat != 0.0) {
+            scal[i_stat + c] = stat;
+            scal[i_act + c] = 0.0;
+            on = false;
+        }
     }
-    const double n0 = sqrt(scal[i_nr0 + c]);
-    if (n0 == 0.0) {
-        scal[i_act + c] = 0.0;
-        scal[i_stat + c] = 1.0;
-        scal[i_rel + c] = 0.0;
-        return;
-    }
-    const double it = scal[i_iter + c] + 1.0;
-    scal[i_iter + c] = it;
-    const double nr = sqrt(scal[i_norm + c]);
-    double stat = 0.0;
-    if (scal[i_flag + c] != 0.0 || !isfinite(nr) || !isfinite(n0)) stat = 3.0;
-    else if (nr <= rtol * n0) stat = 1.0;
-    else if (it >= (double)maxit) stat = 2.0;
-    scal[i_rel + c] = nr / n0;
-    if (stat != 0.0) {
-        scal[i_stat + c] = stat;
-        scal[i_act + c] = 0.0;
-    }
+    if (__ballot(on) == 0 && c == 0) scal[i_live] = 0.0;
 }
 
 template <class T>
@@ -976,9 +987,9 @@ void launch_block_load_columns(int n, int k, const double* scal, int i_load, con
 }
 
 void launch_block_converge(int k, double* scal, int i_act, int i_norm, int i_nr0, int i_flag, int i_iter, int i_stat,
-                           int i_rel, int i_load, int i_new, double rtol, int maxit, hipStream_t st) {
+                           int i_rel, int i_load, int i_new, int i_live, double rtol, int maxit, hipStream_t st) {
     hipLaunchKernelGGL(block_converge_kernel, dim3(1), dim3(64), 0, st, k, scal, i_act, i_norm, i_nr0, i_flag,
-                       i_iter, i_stat, i_rel, i_load, i_new, rtol, maxit);
+                       i_iter, i_stat, i_rel, i_load, i_new, i_live, rtol, maxit);
 }
 
 void launch_block_column_in(int n, int k, int c, const double* v, double* blk, hipStream_t st) {

@@ -116,7 +116,7 @@ void launch_block_load_columns(int n, int k, const double* scal, int i_load, con
 // zero right-hand side stops at once (state 1, 0 iterations).  Updates the
 // active flags; scal[i_rel+c] = ||r|| / ||b||.
 void launch_block_converge(int k, double* scal, int i_act, int i_norm, int i_nr0, int i_flag, int i_iter, int i_stat,
-                           int i_rel, int i_load, int i_new, double rtol, int maxit, hipStream_t st);
+                           int i_rel, int i_load, int i_new, int i_live, double rtol, int maxit, hipStream_t st);
 // column c of a K-wide block from / to a plain vector of n entries
 void launch_block_column_in(int n, int k, int c, const double* v, double* blk, hipStream_t st);
 void launch_block_column_out(int n, int k, int c, const double* blk, double* v, hipStream_t st);
