@@ -772,7 +772,14 @@ int elem_grid(int64_t count) {
 // (8,192 rows; 100,000; every level): 16-column fv3d 96^3 19372 -> 17410
 // (17917; 17530; 18548), a served queue of 24 on 47^3 6485 -> 5530 (6064; 5814;
 // 5896), 16-column fv3d 40^3 3734 -> 2683 (2737; 2602; 2663).
+// FP64 rows have twice the lanes, and eight parts of them fill the machine
+// earlier: with 32,768 rows small engines waited for each other's workgroups
+// where fourteen share the device (requests at 475/s, median latency 142 ms; one
+// part 134; this limit 132; four parts 140).  Alone, 32,768 -> 4,096 rows (one
+// part): 16 columns of fv3d 70^3 10.73 -> 10.13 ms (11.39), 40^3 3.17 -> 3.01
+// (3.75), 8 of 60^3 2.37 -> 2.48 (3.58).
 constexpr int kSplitRows = 32768;
+constexpr int kSplitRows64 = 4096;
 constexpr double kSplitLen = 8.0;
 constexpr int kSplit = 8;
 
@@ -802,7 +809,7 @@ void block_op_ks(BlockOp op, const CsrT<T>& a, const T* g, const T* u, const T* 
 template <class T, int K>
 void block_op_k(BlockOp op, const CsrT<T>& a, const T* g, const T* u, const T* dinv, T omega, T* y, T* y2,
                 double* acc, const double* live, hipStream_t st) {
-    if (a.rows <= kSplitRows && a.mean_row >= kSplitLen)
+    if (a.rows <= (sizeof(T) == 8 ? kSplitRows64 : kSplitRows) && a.mean_row >= kSplitLen)
         block_op_ks<T, K, kSplit>(op, a, g, u, dinv, omega, y, y2, acc, live, st);
     else block_op_ks<T, K, 1>(op, a, g, u, dinv, omega, y, y2, acc, live, st);
 }
