@@ -1519,7 +1519,7 @@ def bench_serve(args):
             if c and (dom is None or ms > dom[2]):
                 dom = (kern, l, ms)
     hb.profile_enable(True, dom[0], dom[1])
-    bt.step(8)
+    bt.step(5)   # ten iterations in all, fewer than a request needs: a finished engine's launches are empty
     bt.poll(True)
     cnt, ms_total = hb.profile_read(dom[0], dom[1])
     hb.profile_enable(False)
