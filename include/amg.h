@@ -293,8 +293,27 @@ amg_status amg_solve(amg_handle h, const double* b, double* x, const amg_solve_p
 amg_status amg_solve_noalloc(amg_handle h, const double* b, double* x, const amg_solve_params* params,
                              amg_solve_info* info, double* hist);
 
-/* One V-cycle (Section 2, amg_solve) in place: x <- V(b, x); device arrays. */
+/* One V-cycle (Section 2, amg_solve) in place: x <- V(b, x); device arrays.
+   Asynchronous on the handle's stream. */
 amg_status amg_vcycle(amg_handle h, const double* b, double* x);
+
+/* Small levels, and whole PCG solves of small systems, run in one launch whose
+   workgroups wait for each other.  Where they do not get onto the device
+   together within 0.1 s (other streams or processes hold it) the cycle is done
+   by one workgroup and a solve is launched step by step, with the same result
+   to rounding, and the handle keeps to one launch per step from then on.
+   Should workgroups that did meet lose each other (6 s), the result is not a
+   number, and AMG_ERR_DEVICE comes from that solve or, for an asynchronous
+   cycle, from the next cycle or solve on the handle; later calls work, launched
+   step by step.
+   amg_grid_use: 2 whole solves, 1 small levels, 0 neither.
+   amg_set_grid_wait is a testing hook: the wait at the start of a launch in
+   microseconds, the polls of every later one, and whether to wait for a
+   workgroup that does not come (absent 1: at the start, 2: later, 3: at the
+   start of a launch that resumes a solve after a reintroduction).  It
+   synchronizes, and lets the handle use such launches again. */
+amg_status amg_grid_use(amg_handle h, int32_t* use);
+amg_status amg_set_grid_wait(amg_handle h, double gate_us, int32_t polls, int32_t absent);
 
 /* The same cycle in FP32 (values, vectors, accumulation; FP64 coarsest
    inverse): x <- V32(b, x), device float arrays.  The first call builds the

@@ -38,6 +38,7 @@ ABI_SYMBOLS = (
     "amg_setup_params_default", "amg_solve_params_default", "amg_setup_from_csr",
     "amg_setup_nongalerkin_from_csr", "amg_setup_device", "amg_setup_profile_enable", "amg_setup_profile_read",
     "amg_sparsify", "amg_sparsify_levels", "amg_set_method", "amg_set_relaxation", "amg_set_lumping", "amg_set_lump_shapes", "amg_reintroduce", "amg_solve", "amg_solve_noalloc", "amg_vcycle",
+    "amg_grid_use", "amg_set_grid_wait",
     "amg_vcycle32",
     "amg_solve_block", "amg_vcycle_block", "amg_vcycle_block32", "amg_batch_bytes", "amg_batch_create",
     "amg_batch_submit", "amg_batch_step", "amg_batch_poll", "amg_batch_collect", "amg_batch_slots",
@@ -126,6 +127,8 @@ def load_library():
     lib.amg_set_relaxation.argtypes = [vp, i32, i32]
     lib.amg_set_lumping.argtypes = [vp, i32]
     lib.amg_set_lump_shapes.argtypes = [vp, f64, f64, i32]
+    lib.amg_grid_use.argtypes = [vp, P(i32)]
+    lib.amg_set_grid_wait.argtypes = [vp, f64, i32, i32]
     lib.amg_solve.argtypes = [vp, vp, vp, P(SolveParams), P(SolveInfo), vp]
     lib.amg_solve_noalloc.argtypes = [vp, vp, vp, P(SolveParams), P(SolveInfo), vp]
     lib.amg_vcycle.argtypes = [vp, vp, vp]
@@ -164,6 +167,7 @@ def load_library():
     for name in ("amg_setup_from_csr", "amg_setup_nongalerkin_from_csr", "amg_setup_device",
                  "amg_setup_profile_enable", "amg_setup_profile_read", "amg_sparsify", "amg_sparsify_levels", "amg_set_method",
                  "amg_set_relaxation", "amg_set_lumping", "amg_set_lump_shapes", "amg_reintroduce",
+                 "amg_grid_use", "amg_set_grid_wait",
                  "amg_solve", "amg_solve_noalloc", "amg_vcycle", "amg_vcycle32", "amg_solve_block", "amg_vcycle_block",
                  "amg_vcycle_block32", "amg_batch_bytes", "amg_batch_create", "amg_batch_submit",
                  "amg_batch_step", "amg_batch_poll", "amg_batch_collect", "amg_batch_slots", "amg_device_bytes",
@@ -515,6 +519,19 @@ class Hierarchy:
         bits every way); the defaults are the library's."""
         self._check(self._lib.amg_set_lump_shapes(self._h, float(wide_mean_row), float(den_wave_mean_row),
                                                   int(small_rows)))
+
+    def grid_use(self) -> int:
+        """2: whole solves in one launch whose workgroups wait for each other, 1: the
+        small levels of the cycle, 0: neither."""
+        use = C.c_int32()
+        self._check(self._lib.amg_grid_use(self._h, C.byref(use)))
+        return use.value
+
+    def set_grid_wait(self, gate_us: float = 1e5, polls: int = 1 << 23, absent: int = 0):
+        """Testing hook: how long those workgroups wait for each other, and whether
+        for one that does not come (1: at the start of a launch, 2: later, 3: at the
+        start of one that resumes a solve); the defaults are the library's."""
+        self._check(self._lib.amg_set_grid_wait(self._h, float(gate_us), int(polls), int(absent)))
 
     def set_relaxation(self, kind: str = "jacobi", block_rows: int = 64):
         """Weighted Jacobi (default) or hybrid symmetric Gauss-Seidel with blocks

@@ -229,7 +229,12 @@ struct amg_ctx {
     double *bcg_r = nullptr, *bcg_p = nullptr, *bcg_q = nullptr, *bcg_z = nullptr;
     int blk_pack_k = 0;
     std::string last_error;
-    unsigned* grid_flags = nullptr;   // the grid launches' barrier words, then their failure word
+    unsigned* grid_words = nullptr;   // the grid launches' barrier words
+    uint32_t* grid_told = nullptr;    // host-coherent: what they report
+    uint32_t* grid_told_dev = nullptr;   // its device address
+    unsigned grid_ticks = kGateTicks, grid_polls = kLatePolls;   // how long they wait (testing hook)
+    int grid_absent = 0;
+    bool grid_off = false;            // a gate was closed or a launch lost: launched step by step from then on
     double* grid_part = nullptr;      // their partial sums
     double* grid_out = nullptr;       // host-coherent: results of a grid solve, then its residual norms
     double* grid_out_dev = nullptr;   // its device address
@@ -921,13 +926,16 @@ size_t grid_tail_layout(amg_ctx* h, int tail, GridArgs<T>* a) {
     return off;
 }
 
+bool told(const amg_ctx* h, int k) { return __atomic_load_n(h->grid_told + k, __ATOMIC_RELAXED) != 0; }
+
 // levels of the cycle from `from` on (0: a whole solve, whose finest operator is
 // gathered in FP64)
 template <class T>
 GridPlan grid_plan(amg_ctx* h, int from) {
     GridPlan p;
     const int L = (int)h->lv.size() - 1;
-    if (!h->grid_flags || h->sp.nu_pre != 1 || h->sp.nu_post != 1 || L < 1) return p;
+    if (!h->grid_off && h->grid_told) h->grid_off = told(h, kToldClosed);
+    if (!h->grid_words || h->grid_off || h->sp.nu_pre != 1 || h->sp.nu_post != 1 || L < 1) return p;
     const size_t limit = grid_lds_limit();
     int tail = 0;
     for (int l = std::max(from + 1, L - kGridTailLevels + 1); l <= L; ++l)
@@ -976,8 +984,7 @@ GridArgs<T> grid_args(amg_ctx* h, const GridPlan& p) {
     a.tail_b = t.b;
     a.tail_out = t.xt;
     a.omega = (T)h->sp.omega;
-    a.flags = h->grid_flags;
-    a.failed = h->grid_flags + kGridWgs + 1;
+    a.words = h->grid_words;
     return a;
 }
 
@@ -988,16 +995,29 @@ void grid_cycle(amg_ctx* h, const GridPlan& p) {
     check_launch();
 }
 
-// After a breakdown: whether a grid cycle's barrier ran out of time (its result
-// is then not a number); its words are set back so that the handle stays
-// usable.
-bool grid_failed(amg_ctx* h) {
-    if (!h->grid_flags) return false;
-    unsigned failed = 0;
-    download(h, &failed, h->grid_flags + kGridWgs + 1, 1);
+// The grid launches' words as before the first one; none may be running.
+void grid_reset(amg_ctx* h) {
     sync(h);
-    if (failed) launch_fill_u32(kGridWgs + 2, h->grid_flags, 0u, h->stream);
-    return failed != 0;
+    const uint64_t told_at = reinterpret_cast<uint64_t>(h->grid_told_dev);
+    unsigned w[kGridWords] = {};
+    w[kWordTicks] = h->grid_ticks;
+    w[kWordPolls] = h->grid_polls;
+    w[kWordAbsent] = (unsigned)h->grid_absent;
+    w[kWordTold] = (unsigned)told_at;
+    w[kWordTold + 1] = (unsigned)(told_at >> 32);
+    upload(h, h->grid_words, w, kGridWords);
+    sync(h);
+    for (int k = 0; k < kToldWords; ++k) __atomic_store_n(h->grid_told + k, 0u, __ATOMIC_RELAXED);
+}
+
+// Reports a launch that was lost (its result, and that of every launch after it,
+// is not a number), once; the handle goes on step by step.  Called where a cycle
+// begins and where a solve has ended.
+void grid_report(amg_ctx* h) {
+    if (!h->grid_told || !told(h, kToldLost)) return;
+    h->grid_off = true;
+    grid_reset(h);
+    throw AmgFailure{AMG_ERR_DEVICE, "the workgroups of an earlier launch did not meet in time"};
 }
 
 // Buffer that receives the zero-guess smoothing sweep omega D^-1 b of level
@@ -1033,6 +1053,7 @@ void vcycle(amg_ctx* h, const T* b0, T* x0, Guess guess0, int dot_slot, bool l0_
         return;
     }
     std::vector<T*> cur(L + 1), alt(L + 1);
+    grid_report(h);
     const GridPlan grid = grid_plan<T>(h, 1);
     const int tail = grid.first > 0 ? 0 : tail_start(h);
     const int down_end = grid.first > 0 ? grid.first : tail > 0 ? tail : L;
@@ -1292,12 +1313,22 @@ amg_status do_reintroduce(amg_ctx* h, int s, double gamma_min, int* first) {
     return AMG_OK;
 }
 
+// Where a solve is taken up whose launch could not run: at the start, or with x and
+// r = b - A x after a reintroduction.
+struct TakenUp {
+    bool yes = false, resumed = false;
+    amg_solve_info info{0, 0, 0, 0, 0.0, 0.0};
+    double nr0 = 0.0, nws = 0.0;
+};
+
 // The solve of a system small enough for one launch (grid_kernels.hip): the
 // launch ends converged, broken down, out of iterations, or where an adaptive
-// window asks for a reintroduction, after which it is resumed.
+// window asks for a reintroduction, after which it is resumed.  If its workgroups
+// were not on the device together (`left`.yes) the solve goes on step by step.
 template <class T>
 amg_status grid_solve(amg_ctx* h, const GridPlan& g, const double* b, double* x, const amg_solve_params& p,
-                      amg_solve_info* info_out, double* hist) {
+                      amg_solve_info* info_out, double* hist, TakenUp& left) {
+    grid_report(h);
     const int n = h->lv[0].n;
     const DevMat& A = h->lv[0].A;
     const double* out = h->grid_out;
@@ -1310,6 +1341,8 @@ amg_status grid_solve(amg_ctx* h, const GridPlan& g, const double* b, double* x,
         bool any = false;
         for (size_t l = 1; l < h->lv.size(); ++l) any = any || h->lv[l].gamma > 0.0;
         GridArgs<T> a = grid_args<T>(h, g);
+        if (h->grid_absent == kAbsentResumed && !first)
+            launch_fill_u32(1, h->grid_words + kWordAbsent, kAbsentAtGate, h->stream);
         // the residual in the cycle's precision
         if constexpr (sizeof(T) == 8) a.lv[0].b = h->cg_r;
         else a.lv[0].b = h->cg_r32;
@@ -1343,9 +1376,15 @@ amg_status grid_solve(amg_ctx* h, const GridPlan& g, const double* b, double* x,
         check_launch();
         await_published(h, s.seq);
         status = (int)out[kGridOutStatus];
-        if (status < 0) {
-            launch_fill_u32(kGridWgs + 2, h->grid_flags, 0u, h->stream);
+        if (status < 0 || told(h, kToldLost)) {
+            h->grid_off = true;
+            grid_reset(h);
             throw AmgFailure{AMG_ERR_DEVICE, "the solve's workgroups did not meet in time"};
+        }
+        if (status == kGridClosed) {
+            left = TakenUp{true, !first, info, nr0, nws};
+            if (hist && !first) std::copy(out + kGridOutInts, out + kGridOutInts + info.iters + 1, hist);
+            return AMG_OK;
         }
         if (first && check) {
             h->check_singular = false;
@@ -1419,44 +1458,50 @@ amg_status solve(amg_ctx* h, const double* b, double* x, const amg_solve_params&
     const int n = f.n;
     const DevMat& A = f.A;
     const bool pcg = p.method == AMG_PCG;
+    TakenUp from;
     if (pcg && !gs_on(h) && !h->profiling && p.maxit > 0 && p.maxit < kGridHist) {
         if (p.precision == 32) ensure_fp32(h);
         const GridPlan g = p.precision == 32 ? grid_plan<float>(h, 0) : grid_plan<double>(h, 0);
-        if (g.first == 0)
-            return p.precision == 32 ? grid_solve<float>(h, g, b, x, p, info_out, hist)
-                                     : grid_solve<double>(h, g, b, x, p, info_out, hist);
+        if (g.first == 0) {
+            const amg_status st = p.precision == 32 ? grid_solve<float>(h, g, b, x, p, info_out, hist, from)
+                                                    : grid_solve<double>(h, g, b, x, p, info_out, hist, from);
+            if (!from.yes) return st;
+            h->grid_off = true;
+        }
     }
     // FP32 V-cycle as the preconditioner (PCG) or as the correction of
     // iterative refinement (stationary); everything else stays FP64
     const bool mixed = p.precision == 32;
     if (mixed) ensure_fp32(h);
-    amg_solve_info info{0, 0, 0, 0, 0.0, 0.0};
+    amg_solve_info info = from.info;
     amg_status st = AMG_ERR_NOT_CONVERGED;
     double* r = h->cg_r;
     launch_fill_f64(S_COUNT, h->scal, 0.0, h->stream);
-    if (p.zero_guess) {
-        // x0 = 0: r0 = b - A 0 = b
-        ProfScope ps(h, AMG_K_VECTOR, 0);
-        launch_zero_guess_start(n, b, x, r, dot_to(h, S_NR2), h->stream);
-        check_launch();
-    } else {
-        row_op(h, AMG_K_RESIDUAL, 0, kResidNorm, A, x, b, nullptr, r, nullptr, S_NR2);
+    double nr0 = from.nr0, nws = from.nws;
+    if (!from.resumed) {
+        if (p.zero_guess) {
+            // x0 = 0: r0 = b - A 0 = b
+            ProfScope ps(h, AMG_K_VECTOR, 0);
+            launch_zero_guess_start(n, b, x, r, dot_to(h, S_NR2), h->stream);
+            check_launch();
+        } else {
+            row_op(h, AMG_K_RESIDUAL, 0, kResidNorm, A, x, b, nullptr, r, nullptr, S_NR2);
+        }
+        // a pivot flag of the coarsest inversion not read yet comes back with the
+        // initial residual norm
+        const bool check = h->check_singular;
+        const double* sc0 = read_scalars(h, check ? h->singular : nullptr);
+        nr0 = nws = std::sqrt(sc0[S_NR2]);
+        if (check) {
+            h->check_singular = false;
+            if (sc0[S_COUNT] != 0.0) throw AmgFailure{AMG_ERR_BAD_MATRIX, "coarsest operator is singular"};
+        }
+        if (hist) hist[0] = nr0;
     }
-    // a pivot flag of the coarsest inversion not read yet comes back with the
-    // initial residual norm
-    const bool check = h->check_singular;
-    const double* sc0 = read_scalars(h, check ? h->singular : nullptr);
-    const double nr0 = std::sqrt(sc0[S_NR2]);
-    if (check) {
-        h->check_singular = false;
-        if (sc0[S_COUNT] != 0.0) throw AmgFailure{AMG_ERR_BAD_MATRIX, "coarsest operator is singular"};
-    }
-    if (hist) hist[0] = nr0;
-    double nws = nr0;
     int inwin = 0;
     int rz_slot = S_RZ0;
     double nrf_read = -1.0;   // the final true residual norm, when the loop has read it
-    double nr_last = nr0, rate = 1.0;   // of the last iteration
+    double nr_last = nws, rate = 1.0;   // of the last iteration
     if (!std::isfinite(nr0)) {
         st = AMG_ERR_BREAKDOWN;
     } else if (nr0 == 0.0) {
@@ -1606,13 +1651,12 @@ amg_status solve(amg_ctx* h, const double* b, double* x, const amg_solve_params&
             }
         }
     }
-    if (st == AMG_ERR_BREAKDOWN && grid_failed(h))
-        throw AmgFailure{AMG_ERR_DEVICE, "the cycle's workgroups did not meet in time"};
     double nrf = nrf_read;
     if (nrf < 0.0) {
         row_op(h, AMG_K_RESIDUAL, 0, kResidNorm, A, x, b, nullptr, r, nullptr, S_NRT);
         nrf = std::sqrt(read_scalars(h)[S_NRT]);
     }
+    grid_report(h);
     info.relres = nr0 > 0.0 ? nrf / nr0 : 0.0;
     info.rho_avg = (info.iters > 0 && info.relres > 0.0) ? std::pow(info.relres, 1.0 / info.iters) : 0.0;
     if (info_out) *info_out = info;
@@ -2499,12 +2543,15 @@ void ensure_published(amg_ctx* h) {
     // the scalar slots, the readback's sequence word, the results of a grid
     // solve: host-coherent so that the device's writes reach the host without a
     // copy (one allocation: each costs about 120 us)
-    constexpr int kFlagAt = S_COUNT + 1, kGridAt = kFlagAt + 8;
+    constexpr int kFlagAt = S_COUNT + 1, kToldAt = kFlagAt + 4, kGridAt = kFlagAt + 8;
     HIP_CHECK(hipHostMalloc((void**)&h->pinned, sizeof(double) * (kGridAt + kGridOutInts + kGridHist),
                             hipHostMallocCoherent | hipHostMallocMapped));
     h->flag_host = reinterpret_cast<uint32_t*>(h->pinned + kFlagAt);
     *h->flag_host = 0;
+    h->grid_told = reinterpret_cast<uint32_t*>(h->pinned + kToldAt);
+    for (int k = 0; k < kToldWords; ++k) h->grid_told[k] = 0;
     HIP_CHECK(hipHostGetDevicePointer((void**)&h->pinned_dev, h->pinned, 0));
+    h->grid_told_dev = reinterpret_cast<uint32_t*>(h->pinned_dev + kToldAt);
     h->flag_dev = reinterpret_cast<uint32_t*>(h->pinned_dev + kFlagAt);
     h->grid_out = h->pinned + kGridAt;
     h->grid_out_dev = h->pinned_dev + kGridAt;
@@ -2565,9 +2612,8 @@ void finish_setup(amg_ctx* h) {
         d.r = dalloc_n<double>(h, d.n);
     }
     // the levels a grid launch may take
-    h->grid_flags = dalloc_n<unsigned>(h, kGridWgs + 2);
+    h->grid_words = dalloc_n<unsigned>(h, kGridWords);
     h->grid_part = dalloc_n<double>(h, 4 * kGridWgs);
-    launch_fill_u32(kGridWgs + 2, h->grid_flags, 0u, h->stream);
     {
         std::vector<DevLevel*> small;
         for (int l = 0; l < L; ++l)
@@ -2603,7 +2649,7 @@ void finish_setup(amg_ctx* h) {
     launch_fill_f64(S_COUNT, h->scal, 0.0, h->stream);
     check_launch();
     ensure_published(h);
-    sync(h);
+    grid_reset(h);
     refresh_coarse_inverse(h);
     h->prof.assign((size_t)AMG_K_NUM * h->lv.size(), ProfAcc{});
 }
@@ -3193,7 +3239,7 @@ void destroy(amg_ctx* h) {
     for (void* q : {(void*)h->bcg_r, (void*)h->bcg_p, (void*)h->bcg_q, (void*)h->bcg_z}) dfree(h, q);
     for (void* p : {(void*)h->coarse_inv, (void*)h->scal, (void*)h->partials,
                     (void*)h->scan_scratch, (void*)h->cnt, (void*)h->sp_cnt, (void*)h->sp_bsum, (void*)h->missing, (void*)h->singular, (void*)h->cg_r,
-                    (void*)h->cg_z, (void*)h->cg_p, (void*)h->cg_q, (void*)h->xw, (void*)h->rt, (void*)h->grid_flags})
+                    (void*)h->cg_z, (void*)h->cg_p, (void*)h->cg_q, (void*)h->xw, (void*)h->rt, (void*)h->grid_words})
         dfree(h, p);
     dfree(h, h->grid_part);
     if (h->pinned) (void)hipHostFree(h->pinned);
@@ -3612,6 +3658,27 @@ amg_status amg_set_lump_shapes(amg_handle h, double wide_mean_row, double den_wa
     h->lump_shapes.wide_mean_row = wide_mean_row;
     h->lump_shapes.den_wave_mean_row = den_wave_mean_row;
     h->lump_shapes.small_rows = small_rows;
+    return AMG_OK;
+}
+
+amg_status amg_set_grid_wait(amg_handle h, double gate_us, int32_t polls, int32_t absent) {
+    if (!h || h->lv.empty() || h->batch) return AMG_ERR_STATE;
+    if (!(gate_us >= 0.0 && gate_us <= 1e7) || polls < 1 || absent < 0 || absent > kAbsentResumed)
+        return AMG_ERR_INVALID_ARG;
+    return guarded(h, [&] {
+        h->grid_ticks = (unsigned)(100.0 * gate_us);
+        h->grid_polls = (unsigned)polls;
+        h->grid_absent = absent;
+        grid_reset(h);
+        h->grid_off = false;
+        return AMG_OK;
+    });
+}
+
+amg_status amg_grid_use(amg_handle h, int32_t* use) {
+    if (!h || h->lv.empty()) return AMG_ERR_STATE;
+    if (!use) return AMG_ERR_INVALID_ARG;
+    *use = grid_plan<double>(h, 0).first == 0 ? 2 : grid_plan<double>(h, 1).first > 0 ? 1 : 0;
     return AMG_OK;
 }
 

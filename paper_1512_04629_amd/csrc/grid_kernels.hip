@@ -7,17 +7,32 @@
 // last workgroup holds the coarsest levels in its LDS and runs them when the
 // others have restricted to them.
 //
-// Barrier: every workgroup stores the number of its barrier in a word of its
-// own, and one wave of each polls all words (two cache lines) until none is
-// behind.  The vectors that cross workgroups are stored and loaded with
+// Barriers: the workgroups wait for each other, so all of them must be on the
+// device at once, which nothing promises: other streams and other processes may
+// hold the compute units.  The first barrier of a launch settles it in one word,
+// the gate: the last workgroup, which has the least to do before, opens it when it
+// has seen all of them, one whose time runs out before that closes it, both with a
+// compare-and-swap, so that all workgroups, the late ones too, find one and the
+// same verdict.  Where it was
+// closed nobody meets: the one that closed it does the cycle alone, far slower and
+// with the same result to rounding (a solve tells the host,
+// which launches it step by step), the others leave.  Past the gate all are
+// running, and every later wait ends.
+//
+// Those later barriers: every workgroup stores the number of its barrier in a
+// word of its own, and one wave of each polls all words (two cache lines) until
+// none is behind.  The vectors that cross workgroups are stored and loaded with
 // agent-scope atomics (relaxed: they go past the L2s, which are not coherent
 // with each other), and every wave waits for its stores before the workgroup's
 // word is written, so no cache is written back or invalidated.  A barrier with
 // the exchange around it is four trips to memory, about 3 us; with release and
 // acquire fences the barrier alone took 5 at 64 workgroups.  The words go on
 // counting from launch to launch: a launch reads the number to start from in
-// its own word, so a captured launch can be replayed.  Every wait ends after
-// kWaitTicks at the latest; the launch then gives up.
+// its own word, so a captured launch can be replayed.  The polls of a wait are
+// counted all the same: should one run out (a device that takes some of a
+// running launch's workgroups off for seconds), the result is not a number, the
+// words are unequal from then on, and `failed` keeps later launches from using
+// them until the host has reported it and set them back.
 //
 // Two barriers a level and cycle: a workgroup forms the residual in all rows its
 // share of the next level restricts from (b and dinv give the first sweep
@@ -36,12 +51,7 @@ namespace {
 
 constexpr int kThreads = 1024;
 constexpr int kAhead = 4;                             // entries a lane requests before a barrier
-// Workgroups of one launch wait for each other, so all must be resident at once.
-// Half a compute unit's LDS at most leaves room for two workgroups on each (as
-// their threads do): 512 on the device, fifteen launches at the same time, where
-// a process has four hardware queues.
 constexpr size_t kLdsShare = 80 * 1024;
-constexpr unsigned long long kWaitTicks = 400000000;  // 4 s of the 100 MHz clock
 
 template <class U>
 using Global = __attribute__((address_space(1))) U*;
@@ -63,11 +73,19 @@ __device__ __forceinline__ void xst(U* p, int i, U v) {
 }
 
 struct Barrier {
-    unsigned* flags;
-    unsigned* failed;
+    unsigned* words;
     unsigned at;         // number of the last barrier announced
-    bool ok;
+    bool ok;             // past every barrier so far
 };
+
+template <class U>
+__device__ __forceinline__ void to_host(U* p, U v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__device__ __forceinline__ uint32_t* told(const Barrier& b) {
+    return (uint32_t*)((uint64_t)xld(b.words, kWordTold) | (uint64_t)xld(b.words, kWordTold + 1) << 32);
+}
 
 // all stores of this wave are at their place
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -76,34 +94,80 @@ __device__ __forceinline__ void announce(Barrier& b) {
     stores_done();
     __syncthreads();
     b.at += 1;
-    if (threadIdx.x == 0)
-        __hip_atomic_store(gp(b.flags) + blockIdx.x, b.at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0) xst(b.words, blockIdx.x, b.at);
 }
 
 // every workgroup has announced this barrier or a later one (differences, so
 // that the count may wrap); false if the wait ran out
 __device__ __forceinline__ bool await_all(Barrier& b) {
     __shared__ int reached;
+    static_assert(kGridWgs < 64);
     if (threadIdx.x < 64) {
-        const unsigned long long start = __builtin_amdgcn_s_memrealtime();
         bool all = false;
-        do {
-            for (int poll = 0; poll < 32 && !all; ++poll) {
-                bool here = true;
-                for (int q = threadIdx.x; q <= kGridWgs; q += 64)
-                    here = here && (int)(__hip_atomic_load(gp(b.flags) + q, __ATOMIC_RELAXED,
-                                                           __HIP_MEMORY_SCOPE_AGENT) - b.at) >= 0;
-                all = __all(here);
-            }
-        } while (!all && __builtin_amdgcn_s_memrealtime() - start < kWaitTicks);
+        for (unsigned poll = 0;; ++poll) {
+            all = __all((int)threadIdx.x > kGridWgs || (int)(xld(b.words, threadIdx.x) - b.at) >= 0);
+            if (all || ((poll & 255) == 255 && poll >= xld(b.words, kWordPolls))) break;
+        }
         if (threadIdx.x == 0) {
             reached = all ? 1 : 0;
-            if (!all) __hip_atomic_store(gp(b.failed), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!all) {
+                xst(b.words, kWordFailed, 1u);
+                to_host(told(b) + kToldLost, 1u);
+            }
         }
     }
     __syncthreads();
     b.ok = b.ok && reached != 0;
     return b.ok;
+}
+
+// The gate: whether the workgroups of this launch met at its first barrier.  The
+// word's values are the barrier's own, so nothing has to be cleared.
+enum Verdict : int {
+    kOpen,      // all are here
+    kClosed,    // leave
+    kAlone      // this workgroup closed it
+};
+
+// the first wave: the gate, seen as g, says v from now on, unless it has said
+// otherwise
+__device__ __forceinline__ bool decide(const Barrier& b, unsigned g, unsigned v) {
+    int won = 0;
+    if (threadIdx.x == 0)
+        while (!won && g != 2u * b.at && g != 2u * b.at + 1u)
+            won = __hip_atomic_compare_exchange_strong(gp(b.words) + kWordGate, &g, v, __ATOMIC_RELAXED,
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __builtin_amdgcn_readfirstlane(won) != 0;
+}
+
+// the first barrier's wait (announced)
+__device__ __forceinline__ Verdict pass_gate(const Barrier& b) {
+    __shared__ int found;
+    if (threadIdx.x < 64) {
+        const unsigned go = 2u * b.at, shut = go + 1u;
+        const unsigned long long start = __builtin_amdgcn_s_memrealtime();
+        const unsigned ticks = xld(b.words, kWordTicks), absent = xld(b.words, kWordAbsent);
+        int verdict = -1;
+        do {
+            unsigned g = 0;
+            for (int poll = 0; poll < 32 && verdict < 0; ++poll) {
+                g = __builtin_amdgcn_readfirstlane(xld(b.words, kWordGate));
+                if (g == go) verdict = kOpen;
+                else if (g == shut) verdict = kClosed;
+                else if (blockIdx.x == kGridWgs && absent != kAbsentAtGate &&
+                         __all((int)threadIdx.x > kGridWgs || (int)(xld(b.words, threadIdx.x) - b.at) >= 0))
+                    verdict = decide(b, g, go) ? kOpen : kClosed;
+            }
+            if (verdict < 0 && __builtin_amdgcn_s_memrealtime() - start >= ticks && decide(b, g, shut))
+                verdict = kAlone;   // (else it was decided meanwhile: the next look says how)
+        } while (verdict < 0);
+        if (threadIdx.x == 0) {
+            found = verdict;
+            if (verdict == kAlone) to_host(told(b) + kToldClosed, 1u);
+        }
+    }
+    __syncthreads();
+    return (Verdict)found;
 }
 
 // rows [lo, hi) and the lanes each is given
@@ -304,33 +368,42 @@ __device__ __forceinline__ void tail_cycle(const GridArgs<T>& a, Lds<unsigned ch
 
 // ---- the cycle -----------------------------------------------------------------
 
-// One cycle from zero: on entry lv[0].b has been exchanged (the barrier after
-// its last store is announced, not awaited); on exit lv[0].xt is stored, its
-// barrier not announced.  ready() runs once the first barrier is passed and
-// returns whether to go on; done(row, value) sees the share's rows of the
-// result.  False: the wait ran out, or ready() said so.
-template <class T, class Ready, class Done>
-__device__ __forceinline__ bool cycle(const GridArgs<T>& a, Barrier& b, Lds<unsigned char> m, Ready&& ready,
-                                      Done&& done) {
+// One cycle from zero: lv[0].b is there once first() says so (its barrier, or the
+// gate of a launch that finds it there); on exit lv[0].xt is stored, its
+// barrier not announced.  ready() runs after first() and returns whether to go on; done(row, value) sees the share's rows of the
+// result.  False: the workgroups do not meet (any more), or ready() said so.
+template <bool GATED, class T, class First, class Ready, class Done>
+__device__ __forceinline__ bool cycle(const GridArgs<T>& a, Barrier& b, Lds<unsigned char> m, First&& first,
+                                      Ready&& ready, Done&& done) {
     const T omega = a.omega;
+    auto meet = [&](int k = 1) {
+        if constexpr (GATED)
+            if (k == 0) return first();
+        return await_all(b);
+    };
     if (blockIdx.x == kGridWgs) {
+        const unsigned absent = xld(b.words, kWordAbsent);
         for (int k = 0; k < a.count; ++k) {
-            if (!await_all(b)) return false;
+            if (!meet(k)) return false;
             if (k == 0 && !ready()) return false;
             if (!a.lv[k].fused) {
                 announce(b);
-                if (!await_all(b)) return false;
+                if (!meet()) return false;
             }
             announce(b);
         }
-        if (!await_all(b)) return false;
+        if (!meet()) return false;
+        if (absent == kAbsentLater) {
+            b.ok = false;
+            return false;
+        }
         tail_cycle(a, m);
         announce(b);
         for (int k = a.count - 1; k > 0; --k) {
-            if (!await_all(b)) return false;
+            if (!meet()) return false;
             announce(b);
         }
-        return await_all(b);
+        return meet();
     }
     for (int k = 0; k < a.count; ++k) {
         const GridLevel<T>& L = a.lv[k];
@@ -344,7 +417,7 @@ __device__ __forceinline__ bool cycle(const GridArgs<T>& a, Barrier& b, Lds<unsi
         const Lds<T> x = (Lds<T>)m;
         Lds<T> r = x + (x1 - x0);
         const Ahead<T> ha = request(L.A, fine);
-        if (!await_all(b)) return false;
+        if (!meet(k)) return false;
         fetch(L.b, x0, x1, [&](int i, T bi) {
             x[i - x0] = omega * (gp(L.dinv)[i] * bi);
             if (i >= fine.lo && i < fine.hi) r[i - fine.lo] = bi;
@@ -361,7 +434,7 @@ __device__ __forceinline__ bool cycle(const GridArgs<T>& a, Barrier& b, Lds<unsi
             __syncthreads();
         } else {
             announce(b);
-            if (!await_all(b)) return false;
+            if (!meet()) return false;
             r = x;
             fetch(L.r, f0, f1, [&](int i, T ri) { r[i - f0] = ri; });
             __syncthreads();
@@ -369,7 +442,7 @@ __device__ __forceinline__ bool cycle(const GridArgs<T>& a, Barrier& b, Lds<unsi
         row_sums(L.R, coarse, hr, r, f0, [&](int i, T t) { xst(nb, i, t); });
         announce(b);
     }
-    if (!await_all(b)) return false;   // the tail's right-hand side
+    if (!meet()) return false;   // the tail's right-hand side
     announce(b);
     for (int k = a.count - 1; k >= 0; --k) {
         const GridLevel<T>& L = a.lv[k];
@@ -383,7 +456,7 @@ __device__ __forceinline__ bool cycle(const GridArgs<T>& a, Barrier& b, Lds<unsi
             if (i >= own.lo && i < own.hi) bo[i - own.lo] = bi;
         });
         const Ahead<T> hp = request(L.P, reach);
-        if (!await_all(b)) return false;
+        if (!meet()) return false;
         fetch(k + 1 < a.count ? a.lv[k + 1].xt : a.tail_out, c0, c1, [&](int i, T v) { xc[i - c0] = v; });
         const Ahead<T> ha = request(L.A, own);
         __syncthreads();
@@ -399,12 +472,52 @@ __device__ __forceinline__ bool cycle(const GridArgs<T>& a, Barrier& b, Lds<unsi
     return true;
 }
 
+// The same cycle by one workgroup, the vectors in memory.
+template <class T, class Get, class Put>
+__device__ __forceinline__ void rows_alone(const GridOp<T>& op, Get&& get, Put&& put) {
+    const int W = op.lanes, lane = (int)threadIdx.x & (W - 1);
+    for (int row = (int)threadIdx.x / W; row < op.rows; row += kThreads / W) {
+        T sum = T(0);
+        for (int p = gp(op.rp)[row] + lane; p < gp(op.rp)[row + 1]; p += W) sum += gp(op.v)[p] * get(gp(op.ci)[p]);
+        for (int o = W / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+        if (lane == 0) put(row, sum);
+    }
+    stores_done();
+    __syncthreads();
+}
+
+template <class T>
+__device__ __forceinline__ void cycle_alone(const GridArgs<T>& a, Lds<unsigned char> m) {
+    for (int k = 0; k < a.count; ++k) {
+        const GridLevel<T>& L = a.lv[k];
+        T* const nb = k + 1 < a.count ? a.lv[k + 1].b : a.tail_b;
+        rows_alone(L.A, [&](int j) { return a.omega * (gp(L.dinv)[j] * xld(L.b, j)); },
+                   [&](int i, T t) { xst(L.r, i, xld(L.b, i) - t); });
+        rows_alone(L.R, [&](int j) { return xld(L.r, j); }, [&](int i, T t) { xst(nb, i, t); });
+    }
+    tail_stage(a, m);
+    stores_done();     // (the loads to LDS count with them)
+    __syncthreads();
+    tail_cycle(a, m);
+    stores_done();
+    __syncthreads();
+    for (int k = a.count - 1; k >= 0; --k) {
+        const GridLevel<T>& L = a.lv[k];
+        const T* const xc = k + 1 < a.count ? a.lv[k + 1].xt : a.tail_out;
+        rows_alone(L.P, [&](int j) { return xld(xc, j); },
+                   [&](int i, T t) { xst(L.r, i, a.omega * (gp(L.dinv)[i] * xld(L.b, i)) + t); });
+        rows_alone(L.A, [&](int j) { return xld(L.r, j); }, [&](int i, T t) {
+            xst(L.xt, i, xld(L.r, i) + a.omega * gp(L.dinv)[i] * (xld(L.b, i) - t));
+        });
+    }
+}
+
 // number of the last barrier of the launches before this one, which are done:
-// every word holds it
+// every workgroup's word holds it, unless one of them was lost
 template <class T>
 __device__ __forceinline__ Barrier first_barrier(const GridArgs<T>& a) {
-    return Barrier{a.flags, a.failed,
-                   __hip_atomic_load(gp(a.flags) + blockIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), true};
+    const unsigned at = xld(a.words, blockIdx.x), failed = xld(a.words, kWordFailed);
+    return Barrier{a.words, (unsigned)__builtin_amdgcn_readfirstlane(at), __builtin_amdgcn_readfirstlane(failed) == 0};
 }
 
 template <class T>
@@ -412,12 +525,17 @@ __global__ __launch_bounds__(kThreads) void grid_cycle_kernel(GridArgs<T> a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const Lds<unsigned char> m = (Lds<unsigned char>)smem;
     Barrier b = first_barrier(a);
-    announce(b);     // nothing to wait for: the launch before stored lv[0].b
-    if (blockIdx.x == kGridWgs) tail_stage(a, m);
-    if (!cycle(a, b, m, [] { return true; }, [](int, T) {}) && !b.ok && blockIdx.x < kGridWgs) {
-        // given up: the result is not a number
+    Verdict gate = kOpen;
+    if (b.ok) {
+        announce(b);     // nothing to wait for: the launch before stored lv[0].b
+        if (blockIdx.x == kGridWgs) tail_stage(a, m);
+        (void)cycle<true>(a, b, m, [&] { return (gate = pass_gate(b)) == kOpen; }, [] { return true; }, [](int, T) {});
+    }
+    if (gate == kAlone) cycle_alone(a, m);
+    if (!b.ok && blockIdx.x < kGridWgs) {
+        // lost: the result is not a number
         const Rows s = share_of(a.lv[0].A);
-        for (int i = s.lo + (int)threadIdx.x; i < s.hi; i += kThreads) gp(a.lv[0].xt)[i] = __builtin_nanf("");
+        for (int i = s.lo + (int)threadIdx.x; i < s.hi; i += kThreads) xst(a.lv[0].xt, i, (T)__builtin_nanf(""));
     }
 }
 
@@ -446,11 +564,6 @@ __device__ __forceinline__ void put_partial(double* part, int slot, double v) {
     }
 }
 
-template <class U>
-__device__ __forceinline__ void to_host(U* p, U v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 enum { kPartNorm = 0, kPartPq = 1, kPartRz = 2, kPartTrue = 3 };
 
 // The iteration of `solve` (amg_lib.hip): the same tests in the same order, all
@@ -461,10 +574,22 @@ __global__ __launch_bounds__(kThreads) void grid_solve_kernel(GridArgs<T> a, Gri
     const Lds<unsigned char> m = (Lds<unsigned char>)smem;
     const Lds<double> win = (Lds<double>)smem;
     const GridLevel<T>& F = a.lv[0];
+    // the end of the launch for the host (one thread)
+    auto tell = [&](double status, int iters) {
+        to_host(s.out + kGridOutStatus, status);
+        to_host(s.out + kGridOutIters, (double)iters);
+        stores_done();
+        to_host(s.done, s.seq);
+    };
     const bool worker = blockIdx.x < kGridWgs, teller = blockIdx.x == 0 && threadIdx.x == 0;
     const Rows own = worker ? share_of(s.A) : Rows{0, 0, 1};
     const int y0 = worker ? window(F, kWinY0) : 0, y1 = worker ? window(F, kWinY1) : 0;
     Barrier b = first_barrier(a);
+    if (!b.ok) {                      // (the host sets the words back before it launches)
+        if (teller) tell(-1.0, s.iters);
+        return;
+    }
+    announce(b);                      // the gate's barrier: workers store what follows before the next one
     if (!worker) tail_stage(a, m);
     // y = b - A x in the share's rows and its squared norm in a slot
     auto residual = [&](double* y, int slot) {
@@ -509,7 +634,13 @@ __global__ __launch_bounds__(kThreads) void grid_solve_kernel(GridArgs<T> a, Gri
     }
     if (worker)
         for (int i = own.lo + (int)threadIdx.x; i < own.hi; i += kThreads) xst(s.xw, i, s.start == 1 ? 0.0 : xld(s.x, i));
+    if (const Verdict gate = pass_gate(b); gate != kOpen) {
+        // x, and for a resumed solve r, are as they were (x = 0 for a zero guess)
+        if (gate == kAlone && threadIdx.x == 0) tell(kGridClosed, iters);
+        return;
+    }
     announce(b);
+    auto meet = [&] { return await_all(b); };
     double *p = s.p, *p2 = s.p2;
     bool fresh = true;                // p = z
     for (;;) {
@@ -559,13 +690,13 @@ __global__ __launch_bounds__(kThreads) void grid_solve_kernel(GridArgs<T> a, Gri
             if (live && iters >= s.maxit) live = false;
             return live;
         };
-        const bool cycled = cycle(a, b, m, ready, [&](int i, T z) { rzp += xld(s.r, i) * (double)z; });
+        const bool cycled = cycle<false>(a, b, m, meet, ready, [&](int i, T z) { rzp += xld(s.r, i) * (double)z; });
         if (!cycled) break;
         if (worker) put_partial(s.part, kPartRz, rzp);
         announce(b);
         // p = z + beta p in the columns the share's rows have, q = A p
         const Ahead<double> h = request(s.A, own);
-        if (!await_all(b)) break;
+        if (!meet()) break;
         const double rz_new = total(s.part, kPartRz);
         const double beta = fresh ? 0.0 : rz_new / rz;
         rz = rz_new;
@@ -600,7 +731,7 @@ __global__ __launch_bounds__(kThreads) void grid_solve_kernel(GridArgs<T> a, Gri
         p2 = was;
         fresh = false;
         announce(b);
-        if (!await_all(b)) break;
+        if (!meet()) break;
         // x += alpha p, r -= alpha q
         const double den = total(s.part, kPartPq);
         if (!(den > 0.0 && isfinite(den))) {
@@ -623,7 +754,7 @@ __global__ __launch_bounds__(kThreads) void grid_solve_kernel(GridArgs<T> a, Gri
         announce(b);
         if (s.adaptive && inwin + 1 == s.k) {
             // a window ends with this iteration: the true residual
-            if (!await_all(b)) break;
+            if (!meet()) break;
             residual(s.rt, kPartTrue);
             announce(b);
         }
@@ -631,21 +762,18 @@ __global__ __launch_bounds__(kThreads) void grid_solve_kernel(GridArgs<T> a, Gri
     // the true residual of the result; a finished window has it
     if (b.ok && nrt < 0.0) {
         announce(b);
-        if (await_all(b)) {
+        if (meet()) {
             residual(s.rt, kPartTrue);
             announce(b);
-            if (await_all(b)) nrt = sqrt(total(s.part, kPartTrue));
+            if (meet()) nrt = sqrt(total(s.part, kPartTrue));
         }
     }
     if (teller) {
-        to_host(s.out + kGridOutStatus, b.ok ? (double)status : -1.0);
-        to_host(s.out + kGridOutIters, (double)iters);
         to_host(s.out + kGridOutNorm0, nr0);
         to_host(s.out + kGridOutTrue, nrt);
         to_host(s.out + kGridOutWindow, nws);
         to_host(s.out + kGridOutSingular, s.singular ? (double)*s.singular : 0.0);
-        stores_done();
-        to_host(s.done, s.seq);
+        tell(b.ok ? (double)status : -1.0, iters);
     }
 }
 

@@ -16,6 +16,21 @@ constexpr int kGridWgs = 32;
 constexpr int kGridLevels = 6;
 constexpr int kGridTailLevels = 4;
 
+// A handle's barrier words, kept from launch to launch: one a workgroup and, in a
+// cache line of their own, the gate of a launch and whether a launch was lost
+// (grid_kernels.hip); then how long workgroups wait, at the gate in ticks of the
+// 100 MHz clock and at later barriers in polls (0.7 us), what a test takes away,
+// and the address of the words the host reads (two words).
+enum {
+    kWordGate = 64, kWordFailed, kWordTicks = 96, kWordPolls, kWordAbsent, kWordTold, kGridWords = kWordTold + 2
+};
+enum { kToldClosed = 0, kToldLost, kToldWords };
+constexpr unsigned kGateTicks = 10000000;   // 0.1 s: the device is shared
+constexpr unsigned kLatePolls = 1u << 23;   // 6 s
+// For tests: the gate does not open, in any launch or in those that resume a
+// solve, or the coarsest levels' workgroup leaves instead of running them.
+enum { kAbsentAtGate = 1, kAbsentLater = 2, kAbsentResumed = 3 };
+
 template <class T>
 struct GridOp {
     const int32_t* rp;
@@ -62,13 +77,13 @@ struct GridArgs {
     uint32_t inv;                            // LDS offset of the coarsest inverse (FP64)
     T *tail_b, *tail_out;                    // in memory: the first tail level's right-hand side and result
     T omega;
-    unsigned* flags;                         // kGridWgs + 1 barrier words, kept from launch to launch
-    unsigned* failed;                        // set if a barrier's wait ran out
+    unsigned* words;                         // kGridWords
 };
 
 // What a solve adds; the cycle's lv[0] is the finest level.  Numbers the host
 // reads are written to host-coherent memory, `done` last.
-enum { kGridConverged = 0, kGridMaxit = 1, kGridBreakdown = 2, kGridReintroduce = 3 };
+// (closed: the workgroups were not there together, nothing was done)
+enum { kGridConverged = 0, kGridMaxit = 1, kGridBreakdown = 2, kGridReintroduce = 3, kGridClosed = 4 };
 enum { kGridOutStatus = 0, kGridOutIters, kGridOutNorm0, kGridOutTrue, kGridOutWindow, kGridOutSingular, kGridOutInts };
 struct GridSolve {
     GridOp<double> A;                        // the finest operator, FP64
