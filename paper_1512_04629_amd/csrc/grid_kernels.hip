@@ -13,10 +13,9 @@
 // the gate: the last workgroup, which has the least to do before, opens it when it
 // has seen all of them, one whose time runs out before that closes it, both with a
 // compare-and-swap, so that all workgroups, the late ones too, find one and the
-// same verdict.  Where it was
-// closed nobody meets: the one that closed it does the cycle alone, far slower and
-// with the same result to rounding (a solve tells the host,
-// which launches it step by step), the others leave.  Past the gate all are
+// same verdict.  Where it was closed nobody meets: the one that closed it does the
+// cycle alone, far slower and with the same result to rounding (a solve tells the
+// host, which launches it step by step), the others leave.  Past the gate all are
 // running, and every later wait ends.
 //
 // Those later barriers: every workgroup stores the number of its barrier in a
@@ -42,6 +41,8 @@
 // small levels) the residual is exchanged instead.  Operator entries of a
 // lane's first row are requested before the barrier.
 #include "grid_kernels.hpp"
+
+#include "per_device.hpp"
 
 #include <algorithm>
 #include <climits>
@@ -846,10 +847,9 @@ void launch_grid_windows(int rows, int coarse, const int32_t* a_rp, const int32_
 }
 
 size_t grid_lds_limit() {
-    static const size_t limit = [] {
-        int dev = 0, per_block = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+    return per_device([](int dev) {
+        int per_block = 0;
+        if (hipDeviceGetAttribute(&per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
             return (size_t)0;
         size_t most = (size_t)per_block;
         for (const void* k : {reinterpret_cast<const void*>(grid_cycle_kernel<double>),
@@ -864,8 +864,7 @@ size_t grid_lds_limit() {
             most = std::min(most, std::min(dyn, kLdsShare - fa.sharedSizeBytes));
         }
         return most;
-    }();
-    return limit;
+    });
 }
 
 void launch_grid_cycle(const GridArgs<double>& a, size_t lds, hipStream_t st) {

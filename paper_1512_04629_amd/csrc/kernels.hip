@@ -8,6 +8,7 @@
 // shuffles and the epilogue (residual, Jacobi update, dot products) is fused
 // into the same pass so that every vector is read once.
 #include "kernels.hpp"
+#include "per_device.hpp"
 #include "row_common.hpp"
 
 #include <hip/hip_ext.h>
@@ -2288,19 +2289,17 @@ int dense_invert_max() { return kDenseInvMax; }
 // cannot be read or raised.
 template <class T>
 size_t tail_lds_limit() {
-    static const size_t limit = [] {
-        int dev = 0, per_block = 0;
+    return per_device([](int dev) {
+        int per_block = 0;
         hipFuncAttributes fa{};
         const void* k = reinterpret_cast<const void*>(coarse_tail_lds_kernel<T>);
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
+        if (hipDeviceGetAttribute(&per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
             hipFuncGetAttributes(&fa, k) != hipSuccess || (size_t)per_block <= fa.sharedSizeBytes)
             return (size_t)0;
         const size_t dyn = (size_t)per_block - fa.sharedSizeBytes;
         if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn) != hipSuccess) return (size_t)0;
         return dyn;
-    }();
-    return limit;
+    });
 }
 
 template <class T>
