@@ -234,6 +234,7 @@ struct amg_ctx {
     uint32_t* grid_told_dev = nullptr;   // its device address
     unsigned grid_ticks = kGateTicks, grid_polls = kLatePolls;   // how long they wait (testing hook)
     int grid_absent = 0;
+    bool grid_stream = false;         // the handle's stream may launch them (GridStreams)
     bool grid_off = false;            // a gate was closed or a launch lost: launched step by step from then on
     double* grid_part = nullptr;      // their partial sums
     double* grid_out = nullptr;       // host-coherent: results of a grid solve, then its residual norms
@@ -926,6 +927,50 @@ size_t grid_tail_layout(amg_ctx* h, int tail, GridArgs<T>* a) {
     return off;
 }
 
+// The streams of a process that launch workgroups waiting for each other: as many
+// for each device as can have such a launch on it at the same time (a stream has
+// one).  Handles of further streams are launched step by step.
+class GridStreams {
+    struct Use {
+        int device;
+        hipStream_t stream;
+        int handles;
+    };
+    std::mutex lock_;
+    std::vector<Use> uses_;
+    // (one value stands for every thread's own stream)
+    static bool shared(hipStream_t st) { return st != hipStreamPerThread; }
+
+public:
+    bool enter(int device, hipStream_t st, int limit) {
+        const std::lock_guard<std::mutex> guard(lock_);
+        int taken = 0;
+        for (Use& u : uses_) {
+            if (u.device != device) continue;
+            if (u.stream == st && shared(st)) {
+                u.handles += 1;
+                return true;
+            }
+            taken += 1;
+        }
+        if (taken >= limit) return false;
+        uses_.push_back(Use{device, st, 1});
+        return true;
+    }
+    void leave(int device, hipStream_t st) {
+        const std::lock_guard<std::mutex> guard(lock_);
+        for (size_t k = 0; k < uses_.size(); ++k)
+            if (uses_[k].device == device && uses_[k].stream == st) {
+                if (--uses_[k].handles == 0) uses_.erase(uses_.begin() + k);
+                return;
+            }
+    }
+};
+GridStreams& grid_streams() {
+    static GridStreams* const all = new GridStreams;   // handles may outlive statics
+    return *all;
+}
+
 bool told(const amg_ctx* h, int k) { return __atomic_load_n(h->grid_told + k, __ATOMIC_RELAXED) != 0; }
 
 // levels of the cycle from `from` on (0: a whole solve, whose finest operator is
@@ -935,8 +980,8 @@ GridPlan grid_plan(amg_ctx* h, int from) {
     GridPlan p;
     const int L = (int)h->lv.size() - 1;
     if (!h->grid_off && h->grid_told) h->grid_off = told(h, kToldClosed);
-    if (!h->grid_words || h->grid_off || h->sp.nu_pre != 1 || h->sp.nu_post != 1 || L < 1) return p;
-    const size_t limit = grid_lds_limit();
+    if (!h->grid_stream || h->grid_off || h->sp.nu_pre != 1 || h->sp.nu_post != 1 || L < 1) return p;
+    const size_t limit = grid_limits().lds;
     int tail = 0;
     for (int l = std::max(from + 1, L - kGridTailLevels + 1); l <= L; ++l)
         if (h->lv[l].n <= kTailRows && (p.lds = grid_tail_layout<T>(h, l, nullptr)) <= limit) {
@@ -2650,6 +2695,10 @@ void finish_setup(amg_ctx* h) {
     check_launch();
     ensure_published(h);
     grid_reset(h);
+    h->grid_stream = true;
+    const bool use = grid_plan<double>(h, 0).first == 0 || grid_plan<double>(h, 1).first > 0 ||
+                     grid_plan<float>(h, 0).first == 0 || grid_plan<float>(h, 1).first > 0;
+    h->grid_stream = use && grid_streams().enter(h->device, h->stream, grid_limits().launches);
     refresh_coarse_inverse(h);
     h->prof.assign((size_t)AMG_K_NUM * h->lv.size(), ProfAcc{});
 }
@@ -3206,6 +3255,7 @@ void setup_device(amg_ctx* h, int64_t n, int64_t nnz, const int32_t* row_ptr, co
 void destroy(amg_ctx* h) {
     if (!h) return;
     (void)hipStreamSynchronize(h->stream);
+    if (h->grid_stream) grid_streams().leave(h->device, h->stream);
     if (h->batch) destroy_batch(h->batch);
     for (auto& d : h->lv) {
         dfree(h, d.gwin);

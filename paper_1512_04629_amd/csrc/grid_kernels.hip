@@ -52,6 +52,8 @@ namespace {
 
 constexpr int kThreads = 1024;
 constexpr int kAhead = 4;                             // entries a lane requests before a barrier
+// Dynamic LDS of a launch: half a compute unit's, so that a workgroup of another
+// kernel finds room beside (of these kernels the registers let one on a unit).
 constexpr size_t kLdsShare = 80 * 1024;
 
 template <class U>
@@ -846,24 +848,31 @@ void launch_grid_windows(int rows, int coarse, const int32_t* a_rp, const int32_
                        p_rp, p_ci, win, most);
 }
 
-size_t grid_lds_limit() {
+GridLimits grid_limits() {
     return per_device([](int dev) {
-        int per_block = 0;
-        if (hipDeviceGetAttribute(&per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-            return (size_t)0;
-        size_t most = (size_t)per_block;
-        for (const void* k : {reinterpret_cast<const void*>(grid_cycle_kernel<double>),
-                              reinterpret_cast<const void*>(grid_cycle_kernel<float>),
-                              reinterpret_cast<const void*>(grid_solve_kernel<double>),
-                              reinterpret_cast<const void*>(grid_solve_kernel<float>)}) {
+        int per_block = 0, cus = 0;
+        if (hipDeviceGetAttribute(&per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+            return GridLimits{};
+        const void* const kernels[] = {
+            reinterpret_cast<const void*>(grid_cycle_kernel<double>), reinterpret_cast<const void*>(grid_cycle_kernel<float>),
+            reinterpret_cast<const void*>(grid_solve_kernel<double>), reinterpret_cast<const void*>(grid_solve_kernel<float>)};
+        size_t lds = (size_t)per_block;
+        for (const void* k : kernels) {
             hipFuncAttributes fa{};
-            if (hipFuncGetAttributes(&fa, k) != hipSuccess || (size_t)per_block <= fa.sharedSizeBytes) return (size_t)0;
+            if (hipFuncGetAttributes(&fa, k) != hipSuccess || (size_t)per_block <= fa.sharedSizeBytes) return GridLimits{};
             const size_t dyn = (size_t)per_block - fa.sharedSizeBytes;
             if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn) != hipSuccess)
-                return (size_t)0;
-            most = std::min(most, std::min(dyn, kLdsShare - fa.sharedSizeBytes));
+                return GridLimits{};
+            lds = std::min(lds, std::min(dyn, kLdsShare - fa.sharedSizeBytes));
         }
-        return most;
+        int per_cu = INT_MAX;
+        for (const void* k : kernels) {
+            int here = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&here, k, kThreads, lds) != hipSuccess) return GridLimits{};
+            per_cu = std::min(per_cu, here);
+        }
+        return GridLimits{lds, grid_launches(cus, per_cu)};
     });
 }
 

@@ -109,8 +109,26 @@ void launch_grid_windows(int rows, int coarse, const int32_t* a_rp, const int32_
                          const int32_t* r_ci, const int32_t* p_rp, const int32_t* p_ci, int32_t* win, int32_t* most,
                          hipStream_t st);
 
-// Dynamic LDS the kernels may use (bytes; 0: not available).
-size_t grid_lds_limit();
+// Launches whose workgroups are on the device together whatever the others do: the
+// workgroups go round the dies of 32 compute units, so the fullest die counts.  At
+// 128 registers and 1,024 threads a unit takes one: six launches on 256 units, one
+// on a partition of 64, none on one of 32.
+constexpr int grid_launches(int cus, int per_cu) {
+    constexpr int kDieCus = 32;
+    const int dies = cus > kDieCus ? cus / kDieCus : 1;
+    const int share = (kGridWgs + 1 + dies - 1) / dies;
+    return cus / dies * per_cu / share;
+}
+static_assert(grid_launches(256, 1) == 6 && grid_launches(256, 2) == 12 && grid_launches(128, 1) == 3 &&
+              grid_launches(64, 1) == 1 && grid_launches(32, 1) == 0 && grid_launches(256, 0) == 0);
+
+// What the current device gives the kernels: dynamic LDS of a launch (bytes) and
+// launches at the same time; 0 if it cannot be found out.
+struct GridLimits {
+    size_t lds = 0;
+    int launches = 0;
+};
+GridLimits grid_limits();
 
 // Levels lv[0..count) and the tail below them: on entry lv[0].b holds the
 // right-hand side, on exit lv[0].xt the result of the cycle from zero.  lds: the
