@@ -34,6 +34,7 @@
 #include "lump_kernels.hpp"
 #include "relax_kernels.hpp"
 #include "setup_kernels.hpp"
+#include "window.hpp"
 
 using namespace amg355;
 
@@ -1379,6 +1380,7 @@ amg_status grid_solve(amg_ctx* h, const GridPlan& g, const double* b, double* x,
     const double* out = h->grid_out;
     amg_solve_info info{0, 0, 0, 0, 0.0, 0.0};
     const bool check = h->check_singular;
+    const double limit = p.adaptive ? window_limit(p.rho_max, p.k) : 0.0;
     double nr0 = 0.0, nws = 0.0, nrt = 0.0;
     int status = kGridReintroduce;
     bool first = true;
@@ -1408,7 +1410,7 @@ amg_status grid_solve(amg_ctx* h, const GridPlan& g, const double* b, double* x,
         s.done = h->flag_dev;
         s.seq = ++h->pub_seq;
         s.rtol = p.rtol;
-        s.rho_pow = std::pow(p.rho_max, (double)p.k);
+        s.window_limit = limit;
         s.nr0 = nr0;
         s.nws = nws;
         s.maxit = p.maxit;
@@ -1653,7 +1655,7 @@ amg_status solve(amg_ctx* h, const double* b, double* x, const amg_solve_params&
             bool restart = false;
             if (window_end) {
                 double nrt = std::sqrt(sc[S_NRT]);
-                const double rho = std::pow(nrt / nws, 1.0 / (double)p.k);
+                const double rho = window_factor(nrt / nws, p.k);
                 bool any = false;
                 for (size_t l = 1; l < h->lv.size(); ++l) any = any || h->lv[l].gamma > 0.0;
                 if (rho > p.rho_max && any) {

@@ -677,7 +677,7 @@ __global__ __launch_bounds__(kThreads) void grid_solve_kernel(GridArgs<T> a, Gri
                     status = kGridConverged;
                     live = false;
                 } else if (window_end) {
-                    if (nrt / nws > s.rho_pow && s.any_gamma) {
+                    if (nrt / nws > s.window_limit && s.any_gamma) {
                         status = kGridReintroduce;
                         live = false;
                     } else {

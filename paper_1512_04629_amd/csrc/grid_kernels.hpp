@@ -95,7 +95,8 @@ struct GridSolve {
     const int* singular;
     uint32_t* done;
     uint32_t seq;
-    double rtol, rho_pow;                    // rho_pow = rho_max^k
+    double rtol;
+    double window_limit;                     // of the residuals' quotient over a window
     double nr0, nws;                         // resumed solves: the first residual norm, the window's
     int maxit, adaptive, k, any_gamma;
     int start;                               // 0: from x, 1: from zero, 2: resumed from r
