@@ -22,8 +22,10 @@
 #include <memory>
 #include <mutex>
 #include <new>
+#include <optional>
 #include <string>
 #include <unordered_map>
+#include <utility>
 #include <vector>
 
 #include "../../include/amg.h"
@@ -279,6 +281,22 @@ void dfree(amg_ctx* h, void* p) {
     if (h->free_fn) h->free_fn(p, bytes, (void*)h->stream, h->user);
     else (void)hipFree(p);
 }
+
+// Device memory that goes back unless it is kept (an allocation after it may be
+// refused).
+template <class T>
+class Held {
+    amg_ctx* h_;
+    T* p_;
+
+public:
+    Held(amg_ctx* h, int64_t n) : h_(h), p_(dalloc_n<T>(h, n)) {}
+    Held(const Held&) = delete;
+    Held& operator=(const Held&) = delete;
+    ~Held() { dfree(h_, p_); }
+    T* get() const { return p_; }
+    T* keep() { return std::exchange(p_, nullptr); }
+};
 
 void free_mat(amg_ctx* h, DevMat& m) {
     dfree(h, m.rp);
@@ -2513,18 +2531,21 @@ bool build_coded(amg_ctx* h, DevMat& m) {
                          (kind == kCodedSquare ? 0.0 : 4.0 * m.rows);
     const double was = kind == kCodedInterp ? 10.0 * m.nnz + 4.0 * m.rows : 9.0 * m.nnz;
     if (bytes > kCodedShare * was) return false;
-    uint32_t* word = dalloc_n<uint32_t>(h, 256 * words * nb);
-    int32_t* tabo = dalloc_n<int32_t>(h, nb * stride);
-    double* tabv = dalloc_n<double>(h, nb * stride);
-    double* tabr = kind == kCodedSquare ? dalloc_n<double>(h, nb * stride) : nullptr;
-    int32_t* base = kind == kCodedSquare ? nullptr : dalloc_n<int32_t>(h, m.rows);
-    launch_coded_fill(m.rows, kind, m.rp, m.ci, m.v, words, word, base, stride, tabo, tabv, tabr, h->stream);
+    Held<uint32_t> word(h, 256 * words * nb);
+    Held<int32_t> tabo(h, nb * stride);
+    Held<double> tabv(h, nb * stride);
+    std::optional<Held<double>> tabr;
+    std::optional<Held<int32_t>> base;
+    if (kind == kCodedSquare) tabr.emplace(h, nb * stride);
+    else base.emplace(h, m.rows);
+    launch_coded_fill(m.rows, kind, m.rp, m.ci, m.v, words, word.get(), base ? base->get() : nullptr, stride,
+                      tabo.get(), tabv.get(), tabr ? tabr->get() : nullptr, h->stream);
     check_launch();
-    m.pc_word = word;
-    m.pc_base = base;
-    m.pc_tabo = tabo;
-    m.pc_tabv = tabv;
-    m.pc_tabr = tabr;
+    m.pc_word = word.keep();
+    m.pc_base = base ? base->keep() : nullptr;
+    m.pc_tabo = tabo.keep();
+    m.pc_tabv = tabv.keep();
+    m.pc_tabr = tabr ? tabr->keep() : nullptr;
     m.pc_stride = stride;
     m.pc_words = words;
     m.pc_kind = kind;
@@ -2667,7 +2688,8 @@ void finish_setup(amg_ctx* h) {
             if (h->lv[l].n <= kGridRows) small.push_back(&h->lv[l]);
         if (!small.empty()) {
             const int64_t words = 3 * (int64_t)small.size();
-            int32_t* most = dalloc_n<int32_t>(h, words);
+            const Held<int32_t> held(h, words);
+            int32_t* const most = held.get();
             launch_fill_u32(words, reinterpret_cast<unsigned*>(most), 0u, h->stream);
             for (size_t k = 0; k < small.size(); ++k) {
                 DevLevel& d = *small[k];
@@ -2679,7 +2701,6 @@ void finish_setup(amg_ctx* h) {
             std::vector<int32_t> top(words);
             download(h, top.data(), most, words);
             sync(h);
-            dfree(h, most);
             for (size_t k = 0; k < small.size(); ++k) {
                 small[k]->gspan = top[3 * k];
                 small[k]->gagain = top[3 * k + 1];
@@ -3294,6 +3315,8 @@ void destroy(amg_ctx* h) {
                     (void*)h->cg_z, (void*)h->cg_p, (void*)h->cg_q, (void*)h->xw, (void*)h->rt, (void*)h->grid_words})
         dfree(h, p);
     dfree(h, h->grid_part);
+    // what a setup that failed had in hand
+    while (!h->blocks.empty()) dfree(h, h->blocks.begin()->first);
     if (h->pinned) (void)hipHostFree(h->pinned);
     for (auto& pe : h->pending) {
         (void)hipEventDestroy(pe.start);
