@@ -2582,7 +2582,8 @@ void set_compact_indices(amg_ctx* h, bool on) {
             if (!m->rp) continue;
             if (!on && m->pc_word) {
                 drop_coded(h, *m);
-                build_sell(h, *m);
+                // (interpolation operators have no SELL-64 copy: finish_setup)
+                if (m != &d.P) build_sell(h, *m);
                 if (h->fp32) sell_fp32(h, *m);
             }
             if (on && build_coded(h, *m)) {
