@@ -2416,17 +2416,23 @@ void compress_indices(amg_ctx* h, DevMat& m) {
 // percent; interpolation operators, whose C and F rows alternate, not)
 constexpr double kSellMaxPadding = 0.10;
 
+// offsets of the slices of m's SELL-64 copy; true if the copy is kept
+bool sell_offsets(amg_ctx* h, const DevMat& m, int32_t* off, int32_t* total) {
+    const int ns = sell_slices(m.rows);
+    launch_sell_widths(m.rows, m.rp, h->cnt, h->stream);
+    launch_exclusive_scan(ns, h->cnt, off, h->scan_scratch, h->stream);
+    check_launch();
+    download(h, total, off + ns, 1);
+    sync(h);
+    return (double)*total <= (1.0 + kSellMaxPadding) * (double)m.nnz;
+}
+
 void build_sell(amg_ctx* h, DevMat& m) {
     if (m.sl_off || m.nnz <= 0 || !sell_candidate(m.view())) return;
     const int ns = sell_slices(m.rows);
     int32_t* off = dalloc_n<int32_t>(h, ns + 1);
-    launch_sell_widths(m.rows, m.rp, h->cnt, h->stream);
-    launch_exclusive_scan(ns, h->cnt, off, h->scan_scratch, h->stream);
-    check_launch();
     int32_t total = 0;
-    download(h, &total, off + ns, 1);
-    sync(h);
-    if ((double)total > (1.0 + kSellMaxPadding) * (double)m.nnz) {
+    if (!sell_offsets(h, m, off, &total)) {
         dfree(h, off);
         return;
     }
@@ -2488,7 +2494,7 @@ void build_sell(amg_ctx* h, DevMat& m) {
 
 // Pair-coded form (coded_kernels.hip) where every block of 256 rows holds few
 // distinct (offset, value) pairs.  Square and restriction operators in place of
-// the SELL-64 copy they would get, with its rounding (one byte a code, two for
+// the SELL-64 copy they would get (and only then), with its rounding (one byte a code, two for
 // the restrictions, whose blocks hold more pairs); interpolation operators of
 // at least kCodedInterpNnz entries in place of the LDS-staged kernel where
 // that sums a row in one lane, with its rounding (smaller ones stay in the
@@ -2531,6 +2537,13 @@ bool build_coded(amg_ctx* h, DevMat& m) {
                          (kind == kCodedSquare ? 0.0 : 4.0 * m.rows);
     const double was = kind == kCodedInterp ? 10.0 * m.nnz + 4.0 * m.rows : 9.0 * m.nnz;
     if (bytes > kCodedShare * was) return false;
+    if (kind != kCodedInterp) {
+        // (one without a SELL-64 copy is served by the LDS-staged kernel, whose sums
+        // round otherwise)
+        const Held<int32_t> off(h, sell_slices(m.rows) + 1);
+        int32_t total = 0;
+        if (!sell_offsets(h, m, off.get(), &total)) return false;
+    }
     Held<uint32_t> word(h, 256 * words * nb);
     Held<int32_t> tabo(h, nb * stride);
     Held<double> tabv(h, nb * stride);
