@@ -371,23 +371,21 @@ __device__ __forceinline__ void tail_cycle(const GridArgs<T>& a, Lds<unsigned ch
 
 // ---- the cycle -----------------------------------------------------------------
 
-// One cycle from zero: lv[0].b is there once first() says so (its barrier, or the
-// gate of a launch that finds it there); on exit lv[0].xt is stored, its
-// barrier not announced.  ready() runs after first() and returns whether to go on; done(row, value) sees the share's rows of the
-// result.  False: the workgroups do not meet (any more), or ready() said so.
+// One cycle from zero: on entry the barrier after lv[0].b's last store is
+// announced, not awaited, or (GATED) lv[0].b is there and first() is the launch's
+// gate, passed before anything is stored; on exit lv[0].xt is stored, its
+// barrier not announced.  ready() runs after the first barrier and returns
+// whether to go on; done(row, value) sees the share's rows of the result.  False:
+// the workgroups do not meet (any more), or ready() said so.
 template <bool GATED, class T, class First, class Ready, class Done>
 __device__ __forceinline__ bool cycle(const GridArgs<T>& a, Barrier& b, Lds<unsigned char> m, First&& first,
                                       Ready&& ready, Done&& done) {
     const T omega = a.omega;
-    auto meet = [&](int k = 1) {
-        if constexpr (GATED)
-            if (k == 0) return first();
-        return await_all(b);
-    };
+    auto meet = [&] { return await_all(b); };
     if (blockIdx.x == kGridWgs) {
         const unsigned absent = xld(b.words, kWordAbsent);
         for (int k = 0; k < a.count; ++k) {
-            if (!meet(k)) return false;
+            if (!(GATED && k == 0 ? first() : meet())) return false;
             if (k == 0 && !ready()) return false;
             if (!a.lv[k].fused) {
                 announce(b);
@@ -420,7 +418,8 @@ __device__ __forceinline__ bool cycle(const GridArgs<T>& a, Barrier& b, Lds<unsi
         const Lds<T> x = (Lds<T>)m;
         Lds<T> r = x + (x1 - x0);
         const Ahead<T> ha = request(L.A, fine);
-        if (!meet(k)) return false;
+        const bool gate = GATED && k == 0;
+        if (!gate && !meet()) return false;
         fetch(L.b, x0, x1, [&](int i, T bi) {
             x[i - x0] = omega * (gp(L.dinv)[i] * bi);
             if (i >= fine.lo && i < fine.hi) r[i - fine.lo] = bi;
@@ -428,6 +427,7 @@ __device__ __forceinline__ bool cycle(const GridArgs<T>& a, Barrier& b, Lds<unsi
         if (k == 0 && !ready()) return false;
         const Ahead<T> hr = request(L.R, coarse);
         __syncthreads();
+        if (gate && !L.fused && !first()) return false;
         row_sums(L.A, fine, ha, x, x0, [&](int i, T t) {
             const T ri = r[i - fine.lo] - t;
             if (L.fused) r[i - fine.lo] = ri;
@@ -435,6 +435,7 @@ __device__ __forceinline__ bool cycle(const GridArgs<T>& a, Barrier& b, Lds<unsi
         });
         if (L.fused) {
             __syncthreads();
+            if (gate && !first()) return false;
         } else {
             announce(b);
             if (!meet()) return false;
