@@ -661,19 +661,20 @@ void sparsify_levels(amg_ctx* h, const std::vector<std::pair<int, double>>& todo
         DevLevel& c = h->lv[t.first];
         if (t.second == 0.0) continue;
         ensure_minimal_pattern(h, t.first);
+        // (an array may be refused: the one that stands for all comes last)
         if (!c.Ahs.rp) {
             c.Ahs.rows = c.Ahs.cols = c.n;
-            c.Ahs.rp = dalloc_n<int32_t>(h, c.n + 1);
-            c.Ahs.ci = dalloc_n<int32_t>(h, c.A.nnz + kCsrPad);
-            c.Ahs.v = dalloc_n<double>(h, c.A.nnz + kCsrPad);
             c.Ahs.shape_nnz = c.A.nnz;
             c.Ahs.width = c.A.width;
+            if (!c.Ahs.ci) c.Ahs.ci = dalloc_n<int32_t>(h, c.A.nnz + kCsrPad);
+            if (!c.Ahs.v) c.Ahs.v = dalloc_n<double>(h, c.A.nnz + kCsrPad);
+            c.Ahs.rp = dalloc_n<int32_t>(h, c.n + 1);
         }
         if (h->fp32 && !c.Ahs32) c.Ahs32 = dalloc_n<float>(h, c.A.nnz + kCsrPad);
         if (h->lumping == AMG_LUMP_STRONG && !c.lump_thr) {
+            if (!c.lump_den) c.lump_den = dalloc_n<double>(h, c.A.nnz);
+            if (!c.lump_dropped) c.lump_dropped = dalloc_n<int32_t>(h, c.A.nnz);
             c.lump_thr = dalloc_n<double>(h, c.n);
-            c.lump_den = dalloc_n<double>(h, c.A.nnz);
-            c.lump_dropped = dalloc_n<int32_t>(h, c.A.nnz);
         }
     }
     bool coarse_changed = false;

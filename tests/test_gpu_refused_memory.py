@@ -104,3 +104,52 @@ def test_a_setup_that_fails_gives_everything_back(lib, name):
     assert st == 0 and at > 30
     lib.amg_destroy(h)
     assert not mem.live
+
+
+def solve(lib, h, A, b, precision=64):
+    from paper_1512_04629_amd import amg
+    p, info = amg.SolveParams(1, 1e-10, 100, 0, 3, 1, 0.5, 0.01, precision, 0), amg.SolveInfo()
+    x = torch.zeros(A.n, dtype=torch.float64, device="cuda")
+    st = lib.amg_solve(h, b.data_ptr(), x.data_ptr(), C.byref(p), C.byref(info), None)
+    assert st == 0, lib.amg_last_error(h)
+    return x.cpu().numpy()
+
+
+@pytest.mark.parametrize("strong", [0, 1])
+def test_a_sparsification_that_fails_can_be_repeated(lib, strong):
+    A = I.poisson3d(20)
+    b = dev(I.rhs(A.n, 3))
+
+    def make(fp32):
+        mem = Refusing()
+        st, h = on_host(lib, A, mem)
+        assert st == 0
+        solve(lib, h, A, b, 32 if fp32 else 64)
+        assert lib.amg_set_lumping(h, strong) == 0
+        return mem, h
+
+    for fp32 in (False, True):
+        mem, h = make(fp32)
+        assert lib.amg_sparsify(h, 0.1, 2) == 0
+        want = solve(lib, h, A, b), solve(lib, h, A, b, 32)
+        lib.amg_destroy(h)
+        at = 1
+        while True:
+            mem, h = make(fp32)
+            mem.arm(at)
+            st = lib.amg_sparsify(h, 0.1, 2)
+            refused = mem.refused
+            assert st == (OUT_OF_MEMORY if refused else 0), at
+            mem.arm(0)
+            if refused:
+                for precision in (64, 32):        # the hierarchy as it was
+                    solve(lib, h, A, b, precision)
+                assert lib.amg_sparsify(h, 0.1, 2) == 0
+                assert np.array_equal(solve(lib, h, A, b), want[0])
+                assert np.array_equal(solve(lib, h, A, b, 32), want[1])
+            lib.amg_destroy(h)
+            assert not mem.live
+            if not refused:
+                break
+            at += 1
+        assert at > 6
