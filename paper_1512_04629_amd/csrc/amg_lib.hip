@@ -2587,30 +2587,41 @@ void sell_fp32(amg_ctx* h, DevMat& m) {
     check_launch();
 }
 
-// builds or drops the 16-bit indices of every level's A, P and R (the
+// builds or drops the compact forms of one operator (`sell`: it may have a SELL-64
+// copy, which interpolation operators do not; finish_setup)
+void switch_compact(amg_ctx* h, DevMat& m, bool on, bool sell) {
+    if (on && build_coded(h, m)) {
+        drop_sell(h, m);
+        return;
+    }
+    if (on) {
+        compress_indices(h, m);
+    } else {
+        drop_coded(h, m);
+        drop_indices(h, m);
+    }
+    // (a copy is rebuilt in the other column width)
+    if (m.sl_off && (m.sl_col == nullptr) != on) drop_sell(h, m);
+    if (sell) build_sell(h, m);
+    if (h->fp32) sell_fp32(h, m);
+}
+
+// builds or drops the compact forms of every level's A, P and R (the
 // sparsified operators keep 32-bit indices)
 void set_compact_indices(amg_ctx* h, bool on) {
     h->compact_idx = on;
     for (auto& d : h->lv) {
         for (DevMat* m : {&d.A, &d.P, &d.R}) {
             if (!m->rp) continue;
-            if (!on && m->pc_word) {
+            try {
+                switch_compact(h, *m, on, m != &d.P);
+            } catch (...) {
+                // an allocation was refused: the CSR arrays serve this operator
                 drop_coded(h, *m);
-                // (interpolation operators have no SELL-64 copy: finish_setup)
-                if (m != &d.P) build_sell(h, *m);
-                if (h->fp32) sell_fp32(h, *m);
-            }
-            if (on && build_coded(h, *m)) {
                 drop_sell(h, *m);
-                continue;
-            }
-            if (on) compress_indices(h, *m);
-            else drop_indices(h, *m);
-            if (m->sl_off && (m->sl_col == nullptr) != on) {
-                // rebuilt in the other column width
-                drop_sell(h, *m);
-                build_sell(h, *m);
-                if (h->fp32) sell_fp32(h, *m);
+                drop_indices(h, *m);
+                if (d.ah_alias) d.Ah = d.A;
+                throw;
             }
         }
         if (d.ah_alias) d.Ah = d.A;

@@ -153,3 +153,42 @@ def test_a_sparsification_that_fails_can_be_repeated(lib, strong):
                 break
             at += 1
         assert at > 6
+
+
+@pytest.mark.parametrize("name", ["device_large", "device_values"])
+def test_a_switch_of_forms_that_fails(lib, name):
+    """Every operator is served by one form or another afterwards, and the switch can
+    be repeated."""
+    make, problem = CASES[name]
+    csr = problem()
+    A = I.poisson3d(64) if name == "device_large" else I.fv3d_lognormal(64)
+    b = dev(I.rhs(A.n, 3))
+    mem = Refusing()
+    st, h = make(lib, csr, mem)
+    assert st == 0
+    want = {}
+    for on in (1, 0, 1):
+        assert lib.amg_set_compact_indices(h, on) == 0
+        want[on] = solve(lib, h, A, b), solve(lib, h, A, b, 32)
+    at, tried = 1, 0
+    while True:
+        refused = 0
+        for on in (0, 1):
+            mem.arm(at)
+            st = lib.amg_set_compact_indices(h, on)
+            assert st == (OUT_OF_MEMORY if mem.refused else 0), (at, on)
+            if mem.refused:
+                refused += 1
+                mem.arm(0)
+                assert np.allclose(solve(lib, h, A, b), want[1][0], rtol=0, atol=1e-8 * abs(want[1][0]).max())
+                assert np.allclose(solve(lib, h, A, b, 32), want[1][0], rtol=0, atol=1e-7 * abs(want[1][0]).max())
+                assert lib.amg_set_compact_indices(h, on) == 0
+            mem.arm(0)
+            assert np.array_equal(solve(lib, h, A, b), want[on][0])
+            assert np.array_equal(solve(lib, h, A, b, 32), want[on][1])
+        tried += 1
+        at += 1
+        if not refused:
+            break
+    lib.amg_destroy(h)
+    assert not mem.live and tried > 2
