@@ -205,7 +205,7 @@ __device__ __forceinline__ typename Vec16<T>::type row_gather_split(const CsrT<T
     const int part = ((int)threadIdx.x / LPR) & (SP - 1), q = (int)threadIdx.x & (LPR - 1);
     const int len = end - beg;
     const int steps = (len + 2 * SP * PS - 1) / (2 * SP * PS);
-    // entry of step t this lane loads; past the row: its last entry, with value 0
+    // entry of step t this lane loads; past the row: column -1 and value 0
     int jn[EL];
     T vn[EL];
     auto load = [&](int t) {
@@ -213,7 +213,7 @@ __device__ __forceinline__ typename Vec16<T>::type row_gather_split(const CsrT<T
         for (int e = 0; e < EL; ++e) {
             const int pos = 2 * (part + SP * (PS * t + q / 2)) + (LPR == 1 ? e : (q & 1));
             const int p = beg + min(pos, len - 1);
-            jn[e] = mat_ld(a.ci + p);
+            jn[e] = pos < len ? mat_ld(a.ci + p) : -1;
             vn[e] = pos < len ? mat_ld(a.v + p) : T(0);
         }
     };
@@ -243,8 +243,10 @@ __device__ __forceinline__ typename Vec16<T>::type row_gather_split(const CsrT<T
                 v0 = __shfl(vc[0], k, LPR);
                 v1 = __shfl(vc[0], k + 1, LPR);
             }
-            const VT g0 = ld16<VT>(g + j0 * K + c0);
-            const VT g1 = ld16<VT>(g + j1 * K + c0);
+            // (past the row nothing is multiplied, whatever the vector holds)
+            const VT l0 = ld16<VT>(g + max(j0, 0) * K + c0);
+            const VT l1 = ld16<VT>(g + max(j1, 0) * K + c0);
+            const VT g0 = j0 < 0 ? VT{} : l0, g1 = j1 < 0 ? VT{} : l1;
             acc.add(false, j0, v0, g0, i);
             acc.add(true, j1, v1, g1, i);
         }
