@@ -29,6 +29,8 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <stdexcept>
+#include <string>
 
 namespace amg355 {
 namespace {
@@ -230,6 +232,13 @@ CsrT<T> directed(const CsrT<T>& a, bool dot) {
     return d;
 }
 
+// An operation or a row of words without an instance would leave its result
+// unwritten.
+[[noreturn]] void no_instance(int kind, int op, int words) {
+    throw std::logic_error("pair-coded form " + std::to_string(kind) + " has no kernel for operation " +
+                           std::to_string(op) + " on rows of " + std::to_string(words) + " words");
+}
+
 #define AMG_CODED_CASE(OPV)                                                                                  \
     case OPV:                                                                                                \
         launch(coded_kernel<T, NW, OPV, CB, FUSED>, dim3(grid), st, a, g, u, dinv, omega, y, y2, dot, nb);   \
@@ -253,8 +262,10 @@ void launch_square(RowOp op, const CsrT<T>& a, const T* g, const T* u, const T* 
                     AMG_CODED_CASE(kResidNorm)
                     AMG_CODED_CASE(kJacobiDot)
                     AMG_CODED_CASE(kSpmvDot)
-                    default: break;
+                    default: no_instance(a.pc_kind, op, NW);
                 }
+            } else {
+                no_instance(a.pc_kind, op, NW);
             }
     }
 }
@@ -269,7 +280,7 @@ void launch_restrict(RowOp op, const CsrT<T>& a, const T* g, const T* u, const T
     switch (op) {
         AMG_CODED_CASE(kSpmv)
         AMG_CODED_CASE(kSpmvScale)
-        default: break;
+        default: no_instance(a.pc_kind, op, NW);
     }
 }
 
@@ -282,7 +293,7 @@ void launch_interp(RowOp op, const CsrT<T>& a, const T* g, const T* u, const T* 
     const int grid = coded_grid(a.rows), nb = coded_blocks(a.rows);
     switch (op) {
         AMG_CODED_CASE(kSpmvAdd)
-        default: break;
+        default: no_instance(a.pc_kind, op, NW);
     }
 }
 #undef AMG_CODED_CASE
@@ -308,7 +319,7 @@ int launch_op(RowOp op, const CsrT<T>& a_in, const T* g, const T* u, const T* di
             AMG_CODED_WORDS(6)
             AMG_CODED_WORDS(8)
 #undef AMG_CODED_WORDS
-            default: break;
+            default: no_instance(a.pc_kind, op, a.pc_words);
         }
     } else {
         switch (a.pc_words) {
@@ -324,7 +335,7 @@ int launch_op(RowOp op, const CsrT<T>& a_in, const T* g, const T* u, const T* di
             AMG_CODED_WORDS(12)
             AMG_CODED_WORDS(16)
 #undef AMG_CODED_WORDS
-            default: break;
+            default: no_instance(a.pc_kind, op, a.pc_words);
         }
     }
 #undef AMG_CODED_ARGS
