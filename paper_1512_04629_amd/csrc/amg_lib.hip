@@ -237,6 +237,7 @@ struct amg_ctx {
     uint32_t* grid_told_dev = nullptr;   // its device address
     unsigned grid_ticks = kGateTicks, grid_polls = kLatePolls;   // how long they wait (testing hook)
     int grid_absent = 0;
+    size_t grid_lds = 0;              // LDS a launch may take on the handle's device
     bool grid_stream = false;         // the handle's stream may launch them (GridStreams)
     bool grid_off = false;            // a gate was closed or a launch lost: launched step by step from then on
     double* grid_part = nullptr;      // their partial sums
@@ -1001,7 +1002,7 @@ GridPlan grid_plan(amg_ctx* h, int from) {
     const int L = (int)h->lv.size() - 1;
     if (!h->grid_off && h->grid_told) h->grid_off = told(h, kToldClosed);
     if (!h->grid_stream || h->grid_off || h->sp.nu_pre != 1 || h->sp.nu_post != 1 || L < 1) return p;
-    const size_t limit = grid_limits().lds;
+    const size_t limit = h->grid_lds;
     int tail = 0;
     for (int l = std::max(from + 1, L - kGridTailLevels + 1); l <= L; ++l)
         if (h->lv[l].n <= kTailRows && (p.lds = grid_tail_layout<T>(h, l, nullptr)) <= limit) {
@@ -2744,10 +2745,12 @@ void finish_setup(amg_ctx* h) {
     check_launch();
     ensure_published(h);
     grid_reset(h);
+    const GridLimits limits = grid_limits();
+    h->grid_lds = limits.lds;
     h->grid_stream = true;
     const bool use = grid_plan<double>(h, 0).first == 0 || grid_plan<double>(h, 1).first > 0 ||
                      grid_plan<float>(h, 0).first == 0 || grid_plan<float>(h, 1).first > 0;
-    h->grid_stream = use && grid_streams().enter(h->device, h->stream, grid_limits().launches);
+    h->grid_stream = use && grid_streams().enter(h->device, h->stream, limits.launches);
     refresh_coarse_inverse(h);
     h->prof.assign((size_t)AMG_K_NUM * h->lv.size(), ProfAcc{});
 }
