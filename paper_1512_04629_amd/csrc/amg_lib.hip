@@ -3048,10 +3048,15 @@ struct RowProduct {
         const int cb = bits_for(cols);
         uint64_t* keys[2] = {t.get<uint64_t>(m + 1), t.get<uint64_t>(m + 1)};
         double* vals[2] = {t.get<double>(m + 1), t.get<double>(m + 1)};
-        tm.begin(AMG_SK_EXPAND, 12.0 * xnnz + 4.0 * a.rows + 8.0 * a.rows + 12.0 * m + 16.0 * m);
-        launch_expand_terms(a, cb, keys[0], vals[0], h->stream);
+        int64_t *terms = t.get<int64_t>(xnnz + 1), *start = t.get<int64_t>(xnnz + 1);
+        tm.begin(AMG_SK_EXPAND, 4.0 * xnnz + 24.0 * xnnz + 20.0 * xnnz + 4.0 * a.rows + 12.0 * m + 16.0 * m);
+        launch_entry_terms(a, xnnz, terms, h->stream);
+        scan_int64(h, t, terms, start, xnnz);
+        launch_expand_terms(a, xnnz, m, start, cb, keys[0], vals[0], h->stream);
         tm.end();
         check_launch();
+        t.release(terms);
+        t.release(start);
         DevMat c = combine_terms(h, t, tm, keys, vals, m, a.rows, cols, cb, bits_for(a.rows) + cb);
         for (void* q : {(void*)keys[0], (void*)keys[1], (void*)vals[0], (void*)vals[1]}) t.release(q);
         launch_loose_rows(a.rows, c.rp, out.off, out.len, h->stream);

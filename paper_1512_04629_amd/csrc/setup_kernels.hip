@@ -375,24 +375,44 @@ __global__ void transpose_keys_kernel(int rows, const int32_t* __restrict__ rp, 
     }
 }
 
-// the terms of X Y: row i lists, for each l of X's row in ascending order,
-// x_il y_lJ over Y's row l
+// terms of each entry of X (nnz + 1 entries, the last 0)
 template <bool LOOSE>
-__global__ void expand_terms_kernel(ProductArgs a, int col_bits, uint64_t* __restrict__ keys,
-                                    double* __restrict__ vals) {
-    GRID_STRIDE(kk, a.rows) {
-        const int k = (int)kk;
-        int64_t o = a.off[k];
-        const uint64_t row = (uint64_t)(uint32_t)k << col_bits;
-        for (int64_t p = a.xrp[k]; p < a.xrp[k + 1]; ++p) {
+__global__ void entry_terms_kernel(ProductArgs a, int64_t nnz, int64_t* __restrict__ terms) {
+    GRID_STRIDE(p, nnz + 1) {
+        int64_t c = 0;
+        if (p < nnz) {
             const int l = a.xci[p];
-            const double x = a.xv[p];
-            const int64_t b = LOOSE ? a.yoff[l] : a.yrp[l], e = LOOSE ? b + a.ylen[l] : a.yrp[l + 1];
-            for (int64_t q = b; q < e; ++q) {
-                keys[o] = row | (uint64_t)(uint32_t)a.yci[q];
-                vals[o] = x * a.yv[q];
-                ++o;
-            }
+            c = LOOSE ? a.ylen[l] : a.yrp[l + 1] - a.yrp[l];
+        }
+        terms[p] = c;
+    }
+}
+
+// The terms of X Y: row i lists, for each l of X's row in ascending order,
+// x_il y_lJ over Y's row l.  G lanes an entry of X, which write next to each other;
+// an entry finds its row in the row pointers.  Entries in parallel, not rows: the
+// coarse rows of dense levels hold thousands of terms each (a thread a row, random
+// graph of 20,000 vertices, all products: 17.9 ms; this 0.40).
+template <int G, bool LOOSE>
+__global__ __launch_bounds__(kSB) void expand_terms_kernel(ProductArgs a, int64_t nnz,
+                                                           const int64_t* __restrict__ start, int col_bits,
+                                                           uint64_t* __restrict__ keys, double* __restrict__ vals) {
+    const int lane = threadIdx.x % G;
+    GRID_STRIDE(t, nnz * G) {
+        const int64_t p = t / G;
+        int lo = 0, hi = a.rows;   // the last row that starts at or before p
+        while (hi - lo > 1) {
+            const int mid = lo + (hi - lo) / 2;
+            if (a.xrp[mid] <= p) lo = mid;
+            else hi = mid;
+        }
+        const uint64_t row = (uint64_t)(uint32_t)lo << col_bits;
+        const int l = a.xci[p];
+        const double x = a.xv[p];
+        const int64_t o = start[p], len = start[p + 1] - o, b = LOOSE ? a.yoff[l] : a.yrp[l];
+        for (int64_t q = lane; q < len; q += G) {
+            keys[o + q] = row | (uint64_t)(uint32_t)a.yci[b + q];
+            vals[o + q] = x * a.yv[b + q];
         }
     }
 }
@@ -508,11 +528,30 @@ void launch_transpose_keys(int rows, const int32_t* rp, const int32_t* ci, const
                        keys, vals);
 }
 
-void launch_expand_terms(const ProductArgs& a, int col_bits, uint64_t* keys, double* vals, hipStream_t st) {
+void launch_entry_terms(const ProductArgs& a, int64_t nnz, int64_t* terms, hipStream_t st) {
+    const dim3 grid(grid_of(nnz + 1));
+    if (a.yrp) hipLaunchKernelGGL(entry_terms_kernel<false>, grid, dim3(kSB), 0, st, a, nnz, terms);
+    else hipLaunchKernelGGL(entry_terms_kernel<true>, grid, dim3(kSB), 0, st, a, nnz, terms);
+}
+
+namespace {
+template <int G>
+void expand_terms(const ProductArgs& a, int64_t nnz, const int64_t* start, int col_bits, uint64_t* keys,
+                  double* vals, hipStream_t st) {
+    const dim3 grid(grid_of(nnz * G));
     if (a.yrp)
-        hipLaunchKernelGGL(expand_terms_kernel<false>, dim3(grid_of(a.rows)), dim3(kSB), 0, st, a, col_bits, keys, vals);
+        hipLaunchKernelGGL((expand_terms_kernel<G, false>), grid, dim3(kSB), 0, st, a, nnz, start, col_bits, keys, vals);
     else
-        hipLaunchKernelGGL(expand_terms_kernel<true>, dim3(grid_of(a.rows)), dim3(kSB), 0, st, a, col_bits, keys, vals);
+        hipLaunchKernelGGL((expand_terms_kernel<G, true>), grid, dim3(kSB), 0, st, a, nnz, start, col_bits, keys, vals);
+}
+}  // namespace
+
+void launch_expand_terms(const ProductArgs& a, int64_t nnz, int64_t m, const int64_t* start, int col_bits,
+                         uint64_t* keys, double* vals, hipStream_t st) {
+    // lanes by the mean number of terms of an entry
+    if (m <= 8 * nnz) expand_terms<4>(a, nnz, start, col_bits, keys, vals, st);
+    else if (m <= 32 * nnz) expand_terms<16>(a, nnz, start, col_bits, keys, vals, st);
+    else expand_terms<64>(a, nnz, start, col_bits, keys, vals, st);
 }
 
 void launch_loose_rows(int rows, const int32_t* rp, int64_t* off, int64_t* len, hipStream_t st) {

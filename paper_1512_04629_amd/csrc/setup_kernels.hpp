@@ -122,8 +122,11 @@ void launch_publish_words(const PublishWords& w, int64_t* host, uint32_t* flag, 
 void launch_transpose_keys(int rows, const int32_t* rp, const int32_t* ci, const double* v, int row_bits,
                            uint64_t* keys, double* vals, hipStream_t st);
 
-// the terms of a product, row by row in order, from off[row] on
-void launch_expand_terms(const ProductArgs& a, int col_bits, uint64_t* keys, double* vals, hipStream_t st);
+// the terms of each of X's nnz entries (terms[nnz] = 0), then the m terms of a
+// product, row by row in order, entry p's from start[p] (the scan) on
+void launch_entry_terms(const ProductArgs& a, int64_t nnz, int64_t* terms, hipStream_t st);
+void launch_expand_terms(const ProductArgs& a, int64_t nnz, int64_t m, const int64_t* start, int col_bits,
+                         uint64_t* keys, double* vals, hipStream_t st);
 // a CSR row pointer as starts and lengths (rows + 1 entries each, the last
 // length 0)
 void launch_loose_rows(int rows, const int32_t* rp, int64_t* off, int64_t* len, hipStream_t st);
