@@ -105,6 +105,7 @@ struct DevMat {
     double* pc_tabr = nullptr;
     int pc_stride = 0, pc_words = 0;
     CodedKind pc_kind = kCodedSquare;
+    bool pc_none = false;             // counted: the form does not fit this operator (its values stay)
     // direction of this operator's next cycle pass (flipped by every pass),
     // shared with the copies that alias the operator (Ah = A), so that
     // passes alternate whichever copy they go through
@@ -1061,17 +1062,23 @@ void grid_cycle(amg_ctx* h, const GridPlan& p) {
     check_launch();
 }
 
-// The grid launches' words as before the first one; none may be running.
-void grid_reset(amg_ctx* h) {
-    sync(h);
+// The grid launches' words as before the first one.
+std::array<unsigned, kGridWords> grid_words(const amg_ctx* h) {
     const uint64_t told_at = reinterpret_cast<uint64_t>(h->grid_told_dev);
-    unsigned w[kGridWords] = {};
+    std::array<unsigned, kGridWords> w{};
     w[kWordTicks] = h->grid_ticks;
     w[kWordPolls] = h->grid_polls;
     w[kWordAbsent] = (unsigned)h->grid_absent;
     w[kWordTold] = (unsigned)told_at;
     w[kWordTold + 1] = (unsigned)(told_at >> 32);
-    upload(h, h->grid_words, w, kGridWords);
+    return w;
+}
+
+// Sets them back; no launch may be running.
+void grid_reset(amg_ctx* h) {
+    sync(h);
+    const auto w = grid_words(h);
+    upload(h, h->grid_words, w.data(), kGridWords);
     sync(h);
     for (int k = 0; k < kToldWords; ++k) __atomic_store_n(h->grid_told + k, 0u, __ATOMIC_RELAXED);
 }
@@ -2518,7 +2525,7 @@ void drop_coded(amg_ctx* h, DevMat& m) {
 }
 
 bool build_coded(amg_ctx* h, DevMat& m) {
-    if (!h->compact_idx || m.nnz <= 0) return false;
+    if (!h->compact_idx || m.nnz <= 0 || m.pc_none) return false;
     if (m.pc_word) return true;
     const CodedKind kind = m.rows == m.cols ? kCodedSquare : m.rows > m.cols ? kCodedInterp : kCodedRestrict;
     if (kind == kCodedInterp ? (m.nnz < kCodedInterpNnz || stream_block_rows(m.view()) != 256)
@@ -2532,19 +2539,23 @@ bool build_coded(amg_ctx* h, DevMat& m) {
     download(h, top, most, 2);
     sync(h);
     const int words = coded_words(kind, top[1]);
-    if (top[0] > coded_limit(kind) || words == 0) return false;
+    auto none = [&] {
+        m.pc_none = true;
+        return false;
+    };
+    if (top[0] > coded_limit(kind) || words == 0) return none();
     const int stride = (top[0] + 7) / 8 * 8;
     const int64_t nb = ((int64_t)m.rows + 255) / 256;
     const double bytes = 1024.0 * words * nb + (kind == kCodedSquare ? 20.0 : 12.0) * stride * nb +
                          (kind == kCodedSquare ? 0.0 : 4.0 * m.rows);
     const double was = kind == kCodedInterp ? 10.0 * m.nnz + 4.0 * m.rows : 9.0 * m.nnz;
-    if (bytes > kCodedShare * was) return false;
+    if (bytes > kCodedShare * was) return none();
     if (kind != kCodedInterp) {
         // (one without a SELL-64 copy is served by the LDS-staged kernel, whose sums
         // round otherwise)
         const Held<int32_t> off(h, sell_slices(m.rows) + 1);
         int32_t total = 0;
-        if (!sell_offsets(h, m, off.get(), &total)) return false;
+        if (!sell_offsets(h, m, off.get(), &total)) return none();
     }
     Held<uint32_t> word(h, 256 * words * nb);
     Held<int32_t> tabo(h, nb * stride);
@@ -2707,8 +2718,11 @@ void finish_setup(amg_ctx* h) {
         d.r = dalloc_n<double>(h, d.n);
     }
     // the levels a grid launch may take
+    ensure_published(h);
     h->grid_words = dalloc_n<unsigned>(h, kGridWords);
     h->grid_part = dalloc_n<double>(h, 4 * kGridWgs);
+    const auto barrier_words = grid_words(h);
+    upload(h, h->grid_words, barrier_words.data(), kGridWords);
     {
         std::vector<DevLevel*> small;
         for (int l = 0; l < L; ++l)
@@ -2743,8 +2757,7 @@ void finish_setup(amg_ctx* h) {
     h->scal = dalloc_n<double>(h, S_COUNT);
     launch_fill_f64(S_COUNT, h->scal, 0.0, h->stream);
     check_launch();
-    ensure_published(h);
-    grid_reset(h);
+    sync(h);
     const GridLimits limits = grid_limits();
     h->grid_lds = limits.lds;
     h->grid_stream = true;
