@@ -16,7 +16,9 @@
 // same verdict.  Where it was closed nobody meets: the one that closed it does the
 // cycle alone, far slower and with the same result to rounding (a solve tells the
 // host, which launches it step by step), the others leave.  Past the gate all are
-// running, and every later wait ends.
+// running, and every later wait ends.  The first residual is formed before the gate
+// has to be passed: a cycle takes no longer with it (501^2: 112 us), a 64^2 solve
+// 366 us instead of 363.
 //
 // Those later barriers: every workgroup stores the number of its barrier in a
 // word of its own, and one wave of each polls all words (two cache lines) until
