@@ -303,8 +303,8 @@ amg_status amg_vcycle(amg_handle h, const double* b, double* x);
    by one workgroup and a solve is launched step by step, with the same result
    to rounding, and the handle keeps to one launch per step from then on.
    A process uses such launches on as many streams of a device as can run them at
-   the same time (six on a whole MI355X); handles created on further streams are
-   launched step by step.
+   the same time (six on a whole MI355X, in the order of their handles' first such
+   call); handles of further streams are launched step by step.
    Should workgroups that did meet lose each other (6 s), the result is not a
    number, and AMG_ERR_DEVICE comes from that solve or, for an asynchronous
    cycle, from the next cycle or solve on the handle; later calls work, launched

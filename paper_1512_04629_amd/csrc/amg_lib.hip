@@ -238,8 +238,8 @@ struct amg_ctx {
     uint32_t* grid_told_dev = nullptr;   // its device address
     unsigned grid_ticks = kGateTicks, grid_polls = kLatePolls;   // how long they wait (testing hook)
     int grid_absent = 0;
-    size_t grid_lds = 0;              // LDS a launch may take on the handle's device
-    bool grid_stream = false;         // the handle's stream may launch them (GridStreams)
+    GridLimits grid_limits{};         // of the handle's device
+    bool grid_asked = false, grid_may = false;   // the handle's stream may launch them (GridStreams)
     bool grid_off = false;            // a gate was closed or a launch lost: launched step by step from then on
     double* grid_part = nullptr;      // their partial sums
     double* grid_out = nullptr;       // host-coherent: results of a grid solve, then its residual norms
@@ -1002,8 +1002,8 @@ GridPlan grid_plan(amg_ctx* h, int from) {
     GridPlan p;
     const int L = (int)h->lv.size() - 1;
     if (!h->grid_off && h->grid_told) h->grid_off = told(h, kToldClosed);
-    if (!h->grid_stream || h->grid_off || h->sp.nu_pre != 1 || h->sp.nu_post != 1 || L < 1) return p;
-    const size_t limit = h->grid_lds;
+    if (!h->grid_words || h->grid_off || h->sp.nu_pre != 1 || h->sp.nu_post != 1 || L < 1) return p;
+    const size_t limit = h->grid_limits.lds;
     int tail = 0;
     for (int l = std::max(from + 1, L - kGridTailLevels + 1); l <= L; ++l)
         if (h->lv[l].n <= kTailRows && (p.lds = grid_tail_layout<T>(h, l, nullptr)) <= limit) {
@@ -1020,6 +1020,12 @@ GridPlan grid_plan(amg_ctx* h, int from) {
         first = l;
     }
     if (first == tail || (from == 0 && first != 0)) return p;
+    // (a handle that never gets here, a block solver's, takes no stream's place)
+    if (!h->grid_asked) {
+        h->grid_asked = true;
+        h->grid_may = grid_streams().enter(h->device, h->stream, h->grid_limits.launches);
+    }
+    if (!h->grid_may) return p;
     p.first = first;
     p.tail = tail;
     return p;
@@ -2758,12 +2764,7 @@ void finish_setup(amg_ctx* h) {
     launch_fill_f64(S_COUNT, h->scal, 0.0, h->stream);
     check_launch();
     sync(h);
-    const GridLimits limits = grid_limits();
-    h->grid_lds = limits.lds;
-    h->grid_stream = true;
-    const bool use = grid_plan<double>(h, 0).first == 0 || grid_plan<double>(h, 1).first > 0 ||
-                     grid_plan<float>(h, 0).first == 0 || grid_plan<float>(h, 1).first > 0;
-    h->grid_stream = use && grid_streams().enter(h->device, h->stream, limits.launches);
+    h->grid_limits = grid_limits();
     refresh_coarse_inverse(h);
     h->prof.assign((size_t)AMG_K_NUM * h->lv.size(), ProfAcc{});
 }
@@ -3325,7 +3326,7 @@ void setup_device(amg_ctx* h, int64_t n, int64_t nnz, const int32_t* row_ptr, co
 void destroy(amg_ctx* h) {
     if (!h) return;
     (void)hipStreamSynchronize(h->stream);
-    if (h->grid_stream) grid_streams().leave(h->device, h->stream);
+    if (h->grid_may) grid_streams().leave(h->device, h->stream);
     if (h->batch) destroy_batch(h->batch);
     for (auto& d : h->lv) {
         dfree(h, d.gwin);
@@ -3800,8 +3801,10 @@ amg_status amg_set_grid_wait(amg_handle h, double gate_us, int32_t polls, int32_
 amg_status amg_grid_use(amg_handle h, int32_t* use) {
     if (!h || h->lv.empty()) return AMG_ERR_STATE;
     if (!use) return AMG_ERR_INVALID_ARG;
-    *use = grid_plan<double>(h, 0).first == 0 ? 2 : grid_plan<double>(h, 1).first > 0 ? 1 : 0;
-    return AMG_OK;
+    return guarded(h, [&] {
+        *use = grid_plan<double>(h, 0).first == 0 ? 2 : grid_plan<double>(h, 1).first > 0 ? 1 : 0;
+        return AMG_OK;
+    });
 }
 
 amg_status amg_set_relaxation(amg_handle h, int32_t relaxation, int32_t block_rows) {

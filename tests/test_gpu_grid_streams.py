@@ -54,5 +54,7 @@ def test_streams_beyond_the_device(lib):
     assert on(streams[15]).grid_use() == 0               # still used by the three
     for h in more:
         h.close()
+    idle = [on(st) for st in streams[1:]]                # neither cycles nor solves: no place taken
     late = on(streams[15])
     assert late.grid_use() == 2 and handles[15].grid_use() == 0
+    assert len(idle) == 15
